@@ -28,6 +28,24 @@ __device__ __forceinline__ uint64_t lanemask_lt()
     return l ? (~0ull >> (64 - l)) : 0ull;
 }
 
+// The lanes of `among` whose bits [kFrom, kFrom + kBits) of x equal this
+// lane's. Per bit: the bit spread over a word, the ballot of it, and one
+// three-input operation per half that collects the lanes that differ (four
+// instructions; written with selects it compiled to nine).
+template <int kBits, int kFrom = 0>
+__device__ __forceinline__ uint64_t match_bits(uint32_t x, uint64_t among)
+{
+    uint32_t lo = 0, hi = 0;
+#pragma unroll
+    for (int b = kFrom; b < kFrom + kBits; b++) {
+        const uint32_t own = (uint32_t)__builtin_amdgcn_sbfe((int)x, b, 1);   // 0 or ~0
+        const uint64_t m = __ballot(own != 0);
+        lo = __builtin_amdgcn_bitop3_b32(lo, (uint32_t)m, own, 0xF6);          // lo | (m ^ own)
+        hi = __builtin_amdgcn_bitop3_b32(hi, (uint32_t)(m >> 32), own, 0xF6);
+    }
+    return among & ~(((uint64_t)hi << 32) | lo);
+}
+
 // DPP lane moves (gfx9 wave shifts): lane i receives lane i-1 (shr) or
 // lane i+1 (shl) of x; the lane without a source receives `edge`.
 __device__ __forceinline__ uint32_t wave_shr1(uint32_t x, uint32_t edge)

@@ -6,7 +6,7 @@
 // Error: for every event with a usable estimate x = est[e] * factor[e]
 // (finite and > 0; no factor = 1), d = x - obs[e]; per group and over all
 // events: count, sum |d|, sum d^2 and sum obs / x. Each block takes a
-// contiguous range of events and accumulates per-group sums in LDS (1024
+// contiguous range of events and accumulates per-group sums in LDS (4096
 // groups per pass over its range) and the all-events sums in registers; it
 // stores its partial sums, and a last kernel adds the blocks' partials in a
 // fixed order and forms MAE = sum|d| / count, RMSE = sqrt(sum d^2 / count),
@@ -21,186 +21,321 @@ namespace ds {
 namespace {
 
 constexpr uint32_t kT = 256;
-constexpr uint32_t kLdsGroups = 1024;   // groups summed in LDS per pass
 constexpr uint32_t kMaxBlocks = 256;
 
-constexpr uint32_t kU = 8;              // events per thread per step
+constexpr uint32_t kEA = 1024;              // threads of an accumulating block
+constexpr uint32_t kWaves = kEA / 64;
+constexpr uint32_t kSlots = 4096;           // sums in LDS
+constexpr uint32_t kWaveSlots = kSlots / kWaves;
+constexpr uint32_t kU = 2;                  // events per thread per step
+constexpr uint32_t kStep = kU * kEA;
+constexpr uint32_t kChunks = kStep / 64;
+constexpr uint32_t kLight = 4;              // lanes on one sum that are added up one by one
+constexpr uint32_t kNone = 0xFFFFFFFFu;
 
 __device__ __forceinline__ bool usable(double x) { return isfinite(x) && x > 0.0; }
 
-// Estimates (times factors) and observed lengths of events b0 + u kT + t,
-// u < kU; events at or past e1 get x = 0 (not usable).
-__device__ __forceinline__ void load_events(const double *__restrict__ est,
-                                            const double *__restrict__ factor,
-                                            const uint32_t *__restrict__ obs, uint64_t b0,
-                                            uint64_t e1, double (&x)[kU], double (&o)[kU])
+struct Sums {
+    double a[kSlots], q[kSlots], r[kSlots];   // sum |d|, sum d^2, sum obs / x
+    uint32_t n[kSlots];
+};
+
+// One step's events in registers.
+struct Step {
+    double x[kU], f[kU];
+    uint32_t o[kU], g[kU];
+};
+
+__device__ __forceinline__ void load_step(const double *__restrict__ est,
+                                          const double *__restrict__ factor,
+                                          const uint32_t *__restrict__ obs,
+                                          const uint32_t *__restrict__ group, uint64_t b0,
+                                          uint64_t e1, Step &s)
 {
-    double f[kU];
 #pragma unroll
     for (uint32_t u = 0; u < kU; u++) {
-        const uint64_t e = b0 + u * kT + threadIdx.x;
+        const uint64_t e = b0 + u * kEA + threadIdx.x;
         const bool in = e < e1;
-        x[u] = in ? est[e] : 0.0;
-        f[u] = in && factor ? factor[e] : 1.0;
-        o[u] = in ? (double)obs[e] : 0.0;
+        s.x[u] = in ? est[e] : 0.0;           // 0: not usable
+        s.f[u] = in && factor ? factor[e] : 1.0;
+        s.o[u] = in ? obs[e] : 0u;
+        s.g[u] = in && group ? group[e] : kNone;
     }
-#pragma unroll
-    for (uint32_t u = 0; u < kU; u++) x[u] = x[u] * f[u];
+}
+
+__device__ __forceinline__ double wave_sum_f64(double v)
+{
+    for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
+    return v;
+}
+
+// s[slot] += v as one LDS instruction (no read back). Only one lane of a wave
+// and one wave of the block ever adds to a slot at a time, and a wave's LDS
+// instructions execute in order, so the order of additions is fixed.
+template <typename T> __device__ __forceinline__ void lds_add(T *p, T v)
+{
+    __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+// Adds one event per lane (where ok) to the sum at `slot`. Lanes share a
+// slot exactly when they share `key` (< 256), and no other wave touches the
+// slot, so a wave settles its collisions by itself: up to kLight lanes of one
+// slot add in lane order, one instruction after another; a slot with more
+// (one tenant holding most of the events) is added up across the wave in a
+// tree first.
+__device__ __forceinline__ void add_events(Sums &S, uint32_t slot, uint32_t key, bool ok, double a,
+                                           double q, double r)
+{
+    const uint32_t lane = (uint32_t)lane_id();
+    uint64_t peers = match_bits<8>(key, __ballot(ok));
+    if (!ok) peers = 0;
+    for (;;) {
+        const uint64_t heavy = __ballot((uint32_t)__popcll(peers) > kLight);
+        if (!heavy) break;
+        const int l = __builtin_ctzll(heavy);
+        const uint64_t m = readlane64(peers, l);
+        const bool in = (m >> lane) & 1u;
+        const double ta = wave_sum_f64(in ? a : 0.0);
+        const double tq = wave_sum_f64(in ? q : 0.0);
+        const double tr = wave_sum_f64(in ? r : 0.0);
+        if ((int)lane == l) {
+            lds_add(&S.n[slot], (uint32_t)__popcll(m));
+            lds_add(&S.a[slot], ta);
+            lds_add(&S.q[slot], tq);
+            lds_add(&S.r[slot], tr);
+        }
+        if (in) peers = 0;
+    }
+    const uint32_t rank = peers ? (uint32_t)__popcll(peers & lanemask_lt()) : kNone;
+    if (rank == 0) lds_add(&S.n[slot], (uint32_t)__popcll(peers));
+    for (uint32_t k = 0; k < kLight && __ballot(rank != kNone && rank >= k); k++) {
+        if (rank == k) {
+            lds_add(&S.a[slot], a);
+            lds_add(&S.q[slot], q);
+            lds_add(&S.r[slot], r);
+        }
+        // keeps the instructions of different ranks apart
+        __builtin_amdgcn_wave_barrier();
+    }
 }
 
 // partial layout: [block][4][G + 1] (count, sum |d|, sum d^2, sum obs/x);
-// slot G holds the all-events sums
-__global__ __launch_bounds__(kT) void k_err_accum(uint64_t n, const double *__restrict__ est,
-                                                  const double *__restrict__ factor,
-                                                  const uint32_t *__restrict__ obs,
-                                                  const uint32_t *__restrict__ group, uint32_t G,
-                                                  double *__restrict__ partial)
+// slot G holds the all-events sums.
+//
+// kOwn false (G <= 256, or no groups): every wave has sums of its own, and
+// where there is room rep = 256 / G (a power of two, at most 64) of them per
+// group, one per lane mod rep, so that lanes of one wave seldom meet.
+// kOwn true: wave w owns the groups g = w (mod 16). A step's 2048 events are
+// split by owner, stably, through LDS (4 ballots per 64 events, one table of
+// counts that every wave scans for itself: two barriers a step), and each
+// wave adds up its own events in event order. The next step's loads are in
+// flight meanwhile (the barriers wait on LDS alone).
+//
+// What bounds it: LDS. At 4,194,304 events over 4,096 groups the block's sums
+// take 112 KB, one block of 16 waves per CU, and the LDS pipe is busy 74% of
+// the time (counters), mostly with the adds to random sums; every event is
+// read and divided once. The form before (1,024 groups per pass, 4 waves that
+// each walked every event of the block) took 634 us there, this one 79. The
+// error statistics as a whole, before and after: 4,194,304 events, 4 groups
+// 464 and 27 us, 256 groups 202 and 30, 4,096 groups 648 and 93, one group
+// holding every event 1,740 and 205; 65,536 events, 1,000 groups 27 and 19.
+template <bool kOwn>
+__global__ __launch_bounds__(kEA) void k_err_accum(uint64_t n, const double *__restrict__ est,
+                                                   const double *__restrict__ factor,
+                                                   const uint32_t *__restrict__ obs,
+                                                   const uint32_t *__restrict__ group, uint32_t G,
+                                                   uint32_t rep, double *__restrict__ partial)
 {
-    __shared__ double lacc[4][kLdsGroups];
-    __shared__ double wsum[4][kT / 64];
+    __shared__ Sums S;
+    struct __align__(16) Staged {
+        double x;
+        uint32_t o, g;
+    };
+    __shared__ Staged st[kOwn ? kStep : 1];
+    __shared__ __align__(16) uint16_t cnt[kOwn ? kWaves * kChunks : 8];   // [owner][chunk of 64]
+    __shared__ double wsum[4][kWaves];
     const uint64_t slots = (uint64_t)G + 1;
     double *mine = partial + (uint64_t)blockIdx.x * 4 * slots;
     const uint64_t per = cdiv(n, gridDim.x);
     const uint64_t e0 = (uint64_t)blockIdx.x * per;
     const uint64_t e1 = e0 + per < n ? e0 + per : n;
+    const uint32_t t = threadIdx.x, lane = (uint32_t)lane_id();
+    const uint32_t w = (uint32_t)__builtin_amdgcn_readfirstlane((int)(t >> 6));
 
-    // all events: registers, then a block reduction; kU events per thread
-    // per step, their loads issued together
-    double c = 0.0, sa = 0.0, sq = 0.0, sr = 0.0;
-    for (uint64_t b0 = e0; b0 < e1; b0 += kU * kT) {
-        double x[kU], o[kU];
-        load_events(est, factor, obs, b0, e1, x, o);
-#pragma unroll
-        for (uint32_t u = 0; u < kU; u++) {
-            if (!usable(x[u])) continue;
-            const double d = x[u] - o[u];
-            c += 1.0;
-            sa += fabs(d);
-            sq += d * d;
-            sr += o[u] / x[u];
+    double c = 0.0, sa = 0.0, sq = 0.0, sr = 0.0;   // all events
+    for (uint32_t c0 = 0; c0 == 0 || c0 < G; c0 += kSlots) {
+        const uint32_t cn = G - c0 < kSlots ? G - c0 : kSlots;
+        for (uint32_t i = t; i < kSlots; i += kEA) {
+            S.n[i] = 0;
+            S.a[i] = S.q[i] = S.r[i] = 0.0;
         }
+        lds_sync();
+        Step cur;
+        load_step(est, factor, obs, group, e0, e1, cur);
+        for (uint64_t b0 = e0; b0 < e1; b0 += kStep) {
+            Step s = cur;
+            if (b0 + kStep < e1) load_step(est, factor, obs, group, b0 + kStep, e1, cur);
+#pragma unroll
+            for (uint32_t u = 0; u < kU; u++) s.x[u] = s.x[u] * s.f[u];
+            if constexpr (!kOwn) {
+#pragma unroll
+                for (uint32_t u = 0; u < kU; u++) {
+                    const bool ok = usable(s.x[u]);
+                    const double o = (double)s.o[u], d = s.x[u] - o;
+                    const double a = fabs(d), q = d * d, r = o / s.x[u];
+                    if (ok) {
+                        c += 1.0;
+                        sa += a;
+                        sq += q;
+                        sr += r;
+                    }
+                    const uint32_t key = (s.g[u] * rep + (lane & (rep - 1))) & (kWaveSlots - 1);
+                    if (G) add_events(S, w * kWaveSlots + key, key, ok && s.g[u] < G, a, q, r);
+                }
+            } else {
+                // the wave's two chunks of 64 events by owner
+                uint64_t peers[kU];
+                bool ok[kU];
+#pragma unroll
+                for (uint32_t u = 0; u < kU; u++) {
+                    s.g[u] -= c0;   // wraps below c0
+                    // events of no group of this pass still count among all events (once)
+                    ok[u] = usable(s.x[u]) && (c0 == 0 || s.g[u] < cn);
+                    const uint64_t among = __ballot(ok[u]);
+                    peers[u] = match_bits<4>(s.g[u], among);
+                    // owner = lane (lanes below 16)
+                    uint64_t all = among;
+#pragma unroll
+                    for (int bb = 0; bb < 4; bb++) {
+                        const uint64_t m = __ballot((s.g[u] >> bb) & 1u);
+                        all &= (lane >> bb) & 1u ? m : ~m;
+                    }
+                    if (lane < kWaves) cnt[lane * kChunks + u * kWaves + w] = (uint16_t)__popcll(all);
+                }
+                lds_sync();
+                // lane l holds owner l / 4, chunks 8 (l % 4) .. + 7
+                const uint4 v = *reinterpret_cast<const uint4 *>(&cnt[lane * 8]);
+                const uint32_t pk[4] = {v.x, v.y, v.z, v.w};
+                uint32_t sum = 0, before = 0;   // before: the lane's chunks below w % 8
+#pragma unroll
+                for (uint32_t k = 0; k < 8; k++) {
+                    if (k == (w & 7u)) before = sum;
+                    sum += (pk[k >> 1] >> (16 * (k & 1u))) & 0xFFFFu;
+                }
+                const uint32_t incl = wave_incl_scan_dpp(sum);
+                const uint32_t at = incl - sum + before;
+                const uint32_t lo = w ? readlane32(incl, (int)(4 * w - 1)) : 0u;
+                const uint32_t hi = readlane32(incl, (int)(4 * w + 3));
+#pragma unroll
+                for (uint32_t u = 0; u < kU; u++) {
+                    const uint32_t ow = s.g[u] & (kWaves - 1);
+                    const uint32_t p = (uint32_t)__shfl((int)at, (int)(4 * ow + 2 * u + (w >> 3)), 64) +
+                                       (uint32_t)__popcll(peers[u] & lanemask_lt());
+                    if (ok[u]) st[p] = {s.x[u], s.o[u], s.g[u]};
+                }
+                lds_sync();
+                for (uint32_t i = lo; i < hi; i += 64) {
+                    const bool in = i + lane < hi;
+                    const Staged ev = st[in ? i + lane : lo];
+                    const double x = ev.x, o = (double)ev.o;
+                    const uint32_t g = ev.g;
+                    const double d = x - o, a = fabs(d), q = d * d, r = o / x;
+                    if (in && c0 == 0) {
+                        c += 1.0;
+                        sa += a;
+                        sq += q;
+                        sr += r;
+                    }
+                    const bool own = in && g < cn;
+                    add_events(S, own ? g : 0u, (g / kWaves) & (kWaveSlots - 1), own, a, q, r);
+                }
+            }
+        }
+        __syncthreads();
+        if constexpr (kOwn) {
+            for (uint32_t i = t; i < cn; i += kEA) {
+                mine[0 * slots + c0 + i] = (double)S.n[i];
+                mine[1 * slots + c0 + i] = S.a[i];
+                mine[2 * slots + c0 + i] = S.q[i];
+                mine[3 * slots + c0 + i] = S.r[i];
+            }
+            __syncthreads();
+        } else if (t < kWaveSlots) {
+            double m[4] = {0.0, 0.0, 0.0, 0.0};
+            for (uint32_t k = 0; k < kWaves; k++) {
+                const uint32_t i = k * kWaveSlots + t;
+                m[0] += (double)S.n[i];
+                m[1] += S.a[i];
+                m[2] += S.q[i];
+                m[3] += S.r[i];
+            }
+            for (uint32_t off = rep >> 1; off >= 1; off >>= 1)
+                for (int k = 0; k < 4; k++) m[k] += __shfl_xor(m[k], (int)off, 64);
+            if ((t & (rep - 1)) == 0 && t / rep < G)
+                for (int k = 0; k < 4; k++) mine[k * slots + t / rep] = m[k];
+        }
+        if (!kOwn) break;
     }
-    for (int off = 32; off >= 1; off >>= 1) {
-        c += __shfl_xor(c, off, 64);
-        sa += __shfl_xor(sa, off, 64);
-        sq += __shfl_xor(sq, off, 64);
-        sr += __shfl_xor(sr, off, 64);
-    }
-    if (lane_id() == 0) {
-        const int w = threadIdx.x >> 6;
+
+    c = wave_sum_f64(c);
+    sa = wave_sum_f64(sa);
+    sq = wave_sum_f64(sq);
+    sr = wave_sum_f64(sr);
+    if (lane == 0) {
         wsum[0][w] = c;
         wsum[1][w] = sa;
         wsum[2][w] = sq;
         wsum[3][w] = sr;
     }
     __syncthreads();
-    if (threadIdx.x < 4) {
-        double s = 0.0;
-        for (int k = 0; k < (int)(kT / 64); k++) s += wsum[threadIdx.x][k];
-        mine[threadIdx.x * slots + G] = s;
-    }
-    if (!group) return;
-
-    // groups, kLdsGroups at a time, in a fixed order: each step's events go
-    // to LDS in event order; wave w owns the groups g = w (mod kWaves) of
-    // the pass and walks the step's events round by round (64 at a time, in
-    // order); the lanes of one group in a round are added up in lane order
-    // by the lowest of them, which adds that to the group's sums. The result
-    // does not depend on scheduling.
-    constexpr uint32_t kWaves = kT / 64, kStep = kU * kT;
-    __shared__ uint32_t sg[kStep];
-    __shared__ double sv[3][kStep];
-    const uint32_t lane = (uint32_t)lane_id(), w = threadIdx.x >> 6;
-    for (uint32_t c0 = 0; c0 < G; c0 += kLdsGroups) {
-        const uint32_t cn = G - c0 < kLdsGroups ? G - c0 : kLdsGroups;
-        for (uint32_t i = threadIdx.x; i < cn; i += kT)
-            lacc[0][i] = lacc[1][i] = lacc[2][i] = lacc[3][i] = 0.0;
-        __syncthreads();
-        for (uint64_t b0 = e0; b0 < e1; b0 += kStep) {
-            double x[kU], o[kU];
-            uint32_t g[kU];
-#pragma unroll
-            for (uint32_t u = 0; u < kU; u++) {
-                const uint64_t e = b0 + u * kT + threadIdx.x;
-                g[u] = e < e1 ? group[e] - c0 : 0xFFFFFFFFu;   // wraps below c0
-            }
-            load_events(est, factor, obs, b0, e1, x, o);
-#pragma unroll
-            for (uint32_t u = 0; u < kU; u++) {
-                const uint32_t slot = u * kT + threadIdx.x;   // event order
-                const bool ok = g[u] < cn && usable(x[u]);
-                const double d = x[u] - o[u];
-                sg[slot] = ok ? g[u] : 0xFFFFFFFFu;
-                sv[0][slot] = ok ? fabs(d) : 0.0;
-                sv[1][slot] = ok ? d * d : 0.0;
-                sv[2][slot] = ok ? o[u] / x[u] : 0.0;
-            }
-            __syncthreads();
-            for (uint32_t r = 0; r < kStep / 64; r++) {
-                const uint32_t slot = r * 64 + lane;
-                const uint32_t gv = sg[slot];
-                const bool own = gv != 0xFFFFFFFFu && gv % kWaves == w;
-                uint64_t peers = __ballot(own);
-#pragma unroll
-                for (int bb = 0; bb < 10; bb++) {   // group bits within the pass (kLdsGroups = 1024)
-                    const bool bit = (gv >> bb) & 1u;
-                    const uint64_t mk = __ballot(bit);
-                    peers &= bit ? mk : ~mk;
-                }
-                if (own && (peers & lanemask_lt()) == 0) {
-                    double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
-                    for (uint64_t m = peers; m; m &= m - 1) {
-                        const uint32_t q = r * 64 + (uint32_t)__builtin_ctzll(m);
-                        s0 += 1.0;
-                        s1 += sv[0][q];
-                        s2 += sv[1][q];
-                        s3 += sv[2][q];
-                    }
-                    lacc[0][gv] += s0;
-                    lacc[1][gv] += s1;
-                    lacc[2][gv] += s2;
-                    lacc[3][gv] += s3;
-                }
-            }
-            __syncthreads();
-        }
-        for (uint32_t i = threadIdx.x; i < cn; i += kT)
-            for (int k = 0; k < 4; k++) mine[k * slots + c0 + i] = lacc[k][i];
-        __syncthreads();
+    if (t < 4) {
+        double v = 0.0;
+        for (uint32_t k = 0; k < kWaves; k++) v += wsum[t][k];
+        mine[t * slots + G] = v;
     }
 }
 
-// stats[4 g ..]: one wave per group slot adds the blocks' partials (lane l
-// takes blocks l, l + 64, ..., then a fixed butterfly), then the means
-__global__ __launch_bounds__(kT) void k_err_final(const double *__restrict__ partial,
-                                                  uint32_t blocks, uint32_t G,
-                                                  uint32_t with_groups, double *__restrict__ stats)
+// stats[4 g ..]: a block per 16 group slots. Lane = (slot, which sum), wave =
+// a sixteenth of the blocks' partials (64-byte and longer runs of a row,
+// sixteen loads in flight), then the sixteen in order, then the means.
+// (4,097 slots x 256 blocks: a wave per slot, lanes on blocks, took 26.6 us,
+// this 11.2.)
+constexpr uint32_t kFS = 16;
+
+__global__ __launch_bounds__(kEA) void k_err_final(const double *__restrict__ partial,
+                                                   uint32_t blocks, uint32_t G,
+                                                   uint32_t with_groups, double *__restrict__ stats)
 {
+    __shared__ double part[kWaves][64];
     const uint64_t slots = (uint64_t)G + 1;
-    const uint64_t g = (uint64_t)blockIdx.x * (kT / 64) + (threadIdx.x >> 6);
-    if (g >= slots) return;
-    const uint32_t lane = (uint32_t)lane_id();
-    double s[4] = {0.0, 0.0, 0.0, 0.0};
-    if (g == G || with_groups)
-        for (uint32_t b = lane; b < blocks; b += 64)
+    const uint32_t lane = (uint32_t)lane_id(), w = threadIdx.x >> 6;
+    const uint64_t g = (uint64_t)blockIdx.x * kFS + (lane & (kFS - 1));
+    const uint32_t k = lane / kFS;
+    double s = 0.0;
+    if (g < slots && (g == G || with_groups)) {
+        double v[kMaxBlocks / kWaves];
 #pragma unroll
-            for (int k = 0; k < 4; k++) s[k] += partial[((uint64_t)b * 4 + k) * slots + g];
+        for (uint32_t i = 0; i < kMaxBlocks / kWaves; i++) {
+            const uint32_t b = i * kWaves + w;
+            v[i] = b < blocks ? partial[((uint64_t)b * 4 + k) * slots + g] : 0.0;
+        }
 #pragma unroll
-    for (int k = 0; k < 4; k++)
-        for (int off = 32; off >= 1; off >>= 1) s[k] += __shfl_xor(s[k], off, 64);
-    if (lane != 0) return;
-    stats[4 * g + 0] = s[0];
-    if (s[0] > 0.0) {
-        stats[4 * g + 1] = s[1] / s[0];
-        const double m2 = s[2] / s[0];
-        stats[4 * g + 2] = sqrt(m2);
-        stats[4 * g + 3] = s[3] / s[0];
-    } else {
-        const double nan = __builtin_nan("");
-        stats[4 * g + 1] = nan;
-        stats[4 * g + 2] = nan;
-        stats[4 * g + 3] = nan;
+        for (uint32_t i = 0; i < kMaxBlocks / kWaves; i++) s += v[i];
     }
+    part[w][lane] = s;
+    __syncthreads();
+    if (w) return;
+    s = 0.0;
+    for (uint32_t i = 0; i < kWaves; i++) s += part[i][lane];
+    const double n = __shfl(s, (int)(lane & (kFS - 1)), 64);
+    if (g >= slots) return;
+    double *out = stats + 4 * g + k;
+    if (k == 0)
+        *out = s;
+    else if (n > 0.0)
+        *out = k == 2 ? sqrt(s / n) : s / n;
+    else
+        *out = __builtin_nan("");
 }
 
 __global__ void k_err_validate(uint64_t n, const uint32_t *__restrict__ group, uint32_t G,
@@ -212,19 +347,35 @@ __global__ void k_err_validate(uint64_t n, const uint32_t *__restrict__ group, u
     if (bad) atomicOr(flag, 1u);
 }
 
-// hist[c * 3 + k]: requests of category c in class k
+__device__ __forceinline__ void hist_add(uint32_t *h, uint32_t c, uint32_t k, uint32_t n_cat)
+{
+    if (c < n_cat && k < 3) atomicAdd(&h[c * 3 + k], 1u);
+}
+
+// hist[c * 3 + k]: requests of category c in class k. kWide: both arrays are
+// 16-byte aligned, 16 requests per load; otherwise byte loads. 4,194,304
+// requests: 17.2 us with byte loads, 10.0 us with wide ones (128 blocks of
+// 1,024 threads 12.2; copies of the cells per lane 9.7, not worth their code).
+template <bool kWide>
 __global__ __launch_bounds__(kT) void k_class_hist(uint32_t n, const uint8_t *__restrict__ category,
-                                                   uint32_t n_cat, const uint8_t *__restrict__ cls,
-                                                   uint32_t *__restrict__ hist)
+                                                    uint32_t n_cat, const uint8_t *__restrict__ cls,
+                                                    uint32_t *__restrict__ hist)
 {
     __shared__ uint32_t h[256 * 3];
     const uint32_t cells = n_cat * 3;
     for (uint32_t i = threadIdx.x; i < cells; i += kT) h[i] = 0;
     __syncthreads();
-    for (uint32_t i = blockIdx.x * kT + threadIdx.x; i < n; i += gridDim.x * kT) {
-        const uint32_t c = category[i], k = cls[i];
-        if (c < n_cat && k < 3) atomicAdd(&h[c * 3 + k], 1u);
+    const uint32_t id = blockIdx.x * kT + threadIdx.x, all = gridDim.x * kT;
+    const uint32_t n16 = kWide ? n / 16 : 0;
+    for (uint32_t i = id; i < n16; i += all) {
+        const uint4 c = reinterpret_cast<const uint4 *>(category)[i];
+        const uint4 k = reinterpret_cast<const uint4 *>(cls)[i];
+        const uint32_t cw[4] = {c.x, c.y, c.z, c.w}, kw[4] = {k.x, k.y, k.z, k.w};
+#pragma unroll
+        for (int b = 0; b < 16; b++)
+            hist_add(h, (cw[b >> 2] >> (8 * (b & 3))) & 0xFFu, (kw[b >> 2] >> (8 * (b & 3))) & 0xFFu, n_cat);
     }
+    for (uint64_t i = (uint64_t)n16 * 16 + id; i < n; i += all) hist_add(h, category[i], cls[i], n_cat);
     __syncthreads();
     for (uint32_t i = threadIdx.x; i < cells; i += kT)
         if (h[i]) atomicAdd(&hist[i], h[i]);
@@ -275,9 +426,17 @@ hipError_t err_launch(uint64_t n, const double *est, const double *factor, const
     }
     double *partial = static_cast<double *>(ws);
     const uint32_t blocks = err_blocks(n, G);
-    hipLaunchKernelGGL(k_err_accum, dim3(blocks), dim3(kT), 0, s, n, est, factor, obs, group, G,
-                       partial);
-    hipLaunchKernelGGL(k_err_final, dim3((uint32_t)cdiv((uint64_t)G + 1, kT / 64)), dim3(kT), 0, s,
+    // up to 256 groups every wave's sums fit LDS beside the others'
+    if (G <= kWaveSlots) {
+        uint32_t rep = 64;
+        while (rep > 1 && rep * G > kWaveSlots) rep >>= 1;
+        hipLaunchKernelGGL(k_err_accum<false>, dim3(blocks), dim3(kEA), 0, s, n, est, factor, obs,
+                           group, G, rep, partial);
+    } else {
+        hipLaunchKernelGGL(k_err_accum<true>, dim3(blocks), dim3(kEA), 0, s, n, est, factor, obs,
+                           group, G, 1u, partial);
+    }
+    hipLaunchKernelGGL(k_err_final, dim3((uint32_t)cdiv((uint64_t)G + 1, kFS)), dim3(kEA), 0, s,
                        (const double *)partial, blocks, G, group ? 1u : 0u, stats);
     return hipGetLastError();
 }
@@ -293,9 +452,13 @@ hipError_t hist_launch(uint32_t n, const uint8_t *category, uint32_t n_cat, cons
     }
     hipError_t e = fill_u32(hist, 0u, (uint64_t)n_cat * 3, s);
     if (e != hipSuccess) return e;
-    if (n)
-        hipLaunchKernelGGL(k_class_hist, dim3(blocks_for(n, 1024)), dim3(kT), 0, s, n, category,
-                           n_cat, cls, hist);
+    if (!n) return hipGetLastError();
+    const bool wide = (((uintptr_t)category | (uintptr_t)cls) & 15u) == 0;
+    const dim3 grid(wide ? blocks_for(cdiv(n, 16), 512) : blocks_for(n, 1024));
+    if (wide)
+        hipLaunchKernelGGL(k_class_hist<true>, grid, dim3(kT), 0, s, n, category, n_cat, cls, hist);
+    else
+        hipLaunchKernelGGL(k_class_hist<false>, grid, dim3(kT), 0, s, n, category, n_cat, cls, hist);
     return hipGetLastError();
 }
 

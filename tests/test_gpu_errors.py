@@ -140,3 +140,46 @@ def test_class_histogram_validate(ds):
     with pytest.raises(ds.DriftSchedError):
         ds.class_histogram(dev(np.array([0, 1], np.uint8)), dev(np.array([0, 3], np.uint8)), 4,
                            validate=True)
+
+
+@pytest.mark.parametrize("n,G", [(2047, 256), (2049, 257), (70001, 64), (70001, 65), (70001, 4096),
+                                 (600000, 4097), (600000, 1)])
+@pytest.mark.parametrize("skew", ["even", "one", "mixed"])
+def test_group_ranges(ds, oracle, n, G, skew):
+    # sums per wave (with copies per lane) up to 256 groups, groups split over
+    # the waves above, 4096 groups per pass; lanes of a wave that share a
+    # group one by one, or most of them (one group holds most events), and
+    # events outside any group, which count in the last row alone
+    rng = np.random.default_rng(n * 3 + G)
+    est = rng.uniform(0.5, 4000, n)
+    est[rng.random(n) < 0.02] = np.nan
+    obs = rng.integers(0, 5000, n)
+    g = rng.integers(0, G, n)
+    if skew == "one":
+        g[:] = G - 1
+    if skew == "mixed":
+        g[rng.random(n) < 0.7] = G // 2
+    check_stats(ds, oracle, est, obs, factor=rng.uniform(0.5, 1.5, n), group=g, n_groups=G)
+    first = gpu_stats(ds, est, obs, group=g, n_groups=G)
+    assert first.tobytes() == gpu_stats(ds, est, obs, group=g, n_groups=G).tobytes()
+    out = g.copy()
+    out[::7] = G + 5
+    got = gpu_stats(ds, est, obs, group=out, n_groups=G)
+    kept = np.arange(n) % 7 != 0
+    want = oracle.error_stats(est[kept], obs[kept], group=g[kept], n_groups=G)
+    assert np.array_equal(got[:-1, 0], want[:-1, 0])
+    assert rel_close(got[:-1, 1:], want[:-1, 1:], 2.0 * n * U + 1e-15)[0]
+    assert got[-1, 0] == first[-1, 0]
+
+
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 4095, 100001])
+@pytest.mark.parametrize("shift", [0, 1, 16])
+def test_class_histogram_alignment(ds, oracle, n, shift):
+    # 16-byte loads need both arrays aligned; views that are not take byte loads
+    rng = np.random.default_rng(n + shift)
+    cat = rng.integers(0, 7, n + shift).astype(np.uint8)
+    cls = rng.integers(0, 3, n + shift).astype(np.uint8)
+    keep = cat[shift:] < 5
+    want = oracle.class_histogram(cat[shift:][keep], cls[shift:][keep], 5).astype(np.int32)
+    got = host(ds.class_histogram(dev(cat)[shift:], dev(cls)[shift:], 5), np.int32)
+    assert np.array_equal(got, want)
