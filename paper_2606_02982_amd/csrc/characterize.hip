@@ -21,12 +21,17 @@
 // bytes), and everything after that is a Boolean function of planes, 32 bytes
 // per instruction: the ASCII separators, the pieces of the multi-byte ones,
 // the word starts. Neighbouring bytes meet through byte and lane shifts of a
-// plane. Per 32 bytes the transposition takes 48 instructions, the ASCII
-// classes 7, a word-start plane with its count 9, all multi-byte separators
-// about 85 (only where the set has a lead byte that can start one).
-// The byte-parallel form before (8 bits per byte, 4 bytes per instruction)
-// took about 140 instructions per 32 bytes of ASCII and listed lead bytes
-// through LDS, one lane to check each.
+// plane. Per 2 KiB set (counters) ASCII text takes 107 vector instructions, a
+// set with leads of multi-byte separators about 70 more, one with prompt
+// boundaries about 60 more; the form before this, 8 bits per byte and 4 bytes
+// per instruction, took 141 for ASCII, listed lead bytes through LDS and went
+// round by round where they were dense or met a boundary.
+// What bounds it: HBM (6.9 TB/s is this card's read rate) on ASCII and on
+// long prompts, the vector units on text of 2- and 3-byte letters. Measured
+// with the final kernel and the scores, before and after: 16,384 long prompts,
+// 5% of the bytes not ASCII, 2.94 GB: 531 and 457 us (6.4 TB/s); 1,048,576
+// chat prompts, 1.2 GB: 238 and 213 us; 65,536 prompts of 2- and 3-byte
+// letters with multi-byte spaces, 310 MB: 286 and 80 us.
 // Word starts are attributed to prompts through prefix sums: each prompt
 // boundary receives the number of word starts in its wave's range before it,
 // each wave its total; a second kernel forms counts[i] from the two
@@ -48,7 +53,6 @@ constexpr uint32_t kBlock = 256;         // 4 independent waves per block
 // wave or by another stream's kernel) leave a short tail, not a long one.
 constexpr uint32_t kRangesPerSlot = 4;
 constexpr uint32_t kMaxWaves = 32768;
-constexpr uint64_t kNone = ~0ull;
 
 typedef unsigned int v4u __attribute__((ext_vector_type(4)));
 
@@ -77,12 +81,6 @@ __device__ __forceinline__ uint32_t load4(const uint8_t *t, uint64_t B, uint64_t
     return w;
 }
 
-__device__ __forceinline__ uint64_t win_load(const uint64_t *off, uint32_t N, uint32_t wb, int lane)
-{
-    uint64_t i = (uint64_t)wb + (uint64_t)lane;
-    return i <= (uint64_t)N ? off[i] : kNone;
-}
-
 // First index i in [0, count) with off[i] >= x, or count (wave-cooperative
 // 64-ary search; every step is one round of loads).
 __device__ uint32_t lower_bound_wave(const uint64_t *off, uint64_t count, uint64_t x, int lane)
@@ -103,10 +101,21 @@ __device__ uint32_t lower_bound_wave(const uint64_t *off, uint64_t count, uint64
     return (uint32_t)(lo + (uint64_t)__popcll(__ballot(lt)));
 }
 
+// A value that is the same in every lane, known so to the compiler.
+__device__ __forceinline__ uint32_t uniform(uint32_t x)
+{
+    return (uint32_t)__builtin_amdgcn_readfirstlane((int)x);
+}
+
+// Positions inside a wave's range are 32-bit distances from its start (a
+// range is a small part of the buffer; kFar stands for anything beyond).
+constexpr uint32_t kFar = 0xFFFFFFFFu;
+
 struct WaveState {
     uint32_t s_ptr;     // first boundary index not yet consumed
     uint32_t wb;        // boundary index held by lane 0 of win
-    uint64_t win;       // offsets[wb + lane] (kNone past the end)
+    uint32_t win;       // offsets[wb + lane] - ws_start (kFar past the range or the end)
+    uint32_t next;      // win of s_ptr
     uint64_t running;   // word starts in [ws_start, current set), less acc
     uint32_t acc;       // per-lane starts not yet in running
     uint32_t ws_prev;   // whitespace bit of the byte before the set
@@ -116,16 +125,25 @@ struct WaveState {
 struct RangeCtx {
     const uint64_t *off;
     uint32_t N;
-    uint64_t ws_start, ws_end;
+    uint64_t ws_start;
+    uint32_t len;       // bytes of the range
     uint32_t *ploc;
 };
 
+__device__ __forceinline__ void load_window(WaveState &st, const RangeCtx &rc, uint32_t s, int lane)
+{
+    const uint64_t i = (uint64_t)s + (uint64_t)lane;
+    st.wb = uniform(s);
+    st.win = kFar;
+    if (i <= (uint64_t)rc.N) {
+        const uint64_t d = rc.off[i] - rc.ws_start;   // wraps far beyond if before the range
+        if (d < rc.len) st.win = (uint32_t)d;
+    }
+}
+
 __device__ __forceinline__ void ensure_window(WaveState &st, const RangeCtx &rc, uint32_t s, int lane)
 {
-    if (s < st.wb || s - st.wb >= 64) {
-        st.wb = s;
-        st.win = win_load(rc.off, rc.N, s, lane);
-    }
+    if (s < st.wb || s - st.wb >= 64) load_window(st, rc, s, lane);
 }
 
 // Does a prompt start at byte x? (rare: only beside a separator that crosses
@@ -147,41 +165,46 @@ __device__ __forceinline__ uint32_t mb_space_len_nb(uint32_t v)
     return two ? 2u : (three ? 3u : 0u);
 }
 
-// The separator that starts at byte p - k (k = 1..3) and ends past or at byte
-// p - 1, given the dwords before and at p (uniform values): bit 3 - k + i of
-// the result for its i-th byte (bits 1, 2 = bytes p - 2, p - 1; bits 3, 4 =
-// bytes p, p + 1). 0 if there is none or a prompt boundary cuts it.
-__device__ __forceinline__ uint32_t separator_before(const RangeCtx &rc, uint32_t before, uint32_t at,
-                                                     uint64_t p, uint32_t k, int lane)
+// Coverage by the separator of len bytes (0: none) that starts at byte p - k
+// (k = 1..3; p counts from the range's start), unless a prompt boundary cuts
+// it: bits 0, 1 = bytes p - 2, p - 1, bits 2, 3 = bytes p, p + 1.
+__device__ __forceinline__ uint32_t coverage(const RangeCtx &rc, uint32_t p, uint32_t k, uint32_t len, int lane)
 {
-    const uint32_t len = mb_space_len_nb((uint32_t)((((uint64_t)at << 32) | before) >> (32 - 8 * k)));
-    if (len < k) return 0;   // none, or it ends before byte p - 1
     for (uint32_t i = 1; i < len; i++)
-        if (boundary_at(rc.off, rc.N, p - k + i, lane)) return 0;
-    return ((1u << len) - 1u) << (3u - k);
+        if (boundary_at(rc.off, rc.N, rc.ws_start + p - k + i, lane)) return 0;
+    return (((1u << len) - 1u) << (3u - k)) >> 1;
 }
 
-// Bits 0..1: coverage of bytes p - 2, p - 1, bits 2..3: of bytes p, p + 1, by
-// separators that start before p and end at or after it.
-__device__ __forceinline__ uint32_t crossing(const RangeCtx &rc, uint32_t before, uint32_t at, uint64_t p,
-                                             int lane)
+// The bytes from p - k on, k = 1..3, of the dwords before and at p.
+__device__ __forceinline__ uint32_t bytes_from(uint32_t before, uint32_t at, uint32_t k)
 {
-    uint32_t bits = 0;
-    if (before >= 0xC2000000u) bits |= separator_before(rc, before, at, p, 1, lane);
-    const uint32_t c2 = (before >> 16) & 0xFFu;
-    if (c2 - 0xE1u <= 2u) {
-        const uint32_t b = separator_before(rc, before, at, p, 2, lane);
-        if (b & 8u) bits |= b;   // reaches byte p
-    }
-    return bits >> 1;
+    return (uint32_t)((((uint64_t)at << 32) | before) >> (32u - 8u * k));
+}
+
+// Coverage of the two bytes before p and the two from p on by a separator that
+// starts before p and ends at or behind it (dwords before and at p: the same
+// values in every lane).
+__device__ __forceinline__ uint32_t crossing(const RangeCtx &rc, uint32_t before, uint32_t at, uint32_t p, int lane)
+{
+    const uint32_t l1 = mb_space_len_nb(bytes_from(before, at, 1));
+    const uint32_t l2 = mb_space_len_nb(bytes_from(before, at, 2));
+    if (!(l1 || l2 == 3)) return 0;
+    return coverage(rc, p, l1 ? 1u : 2u, l1 ? l1 : l2, lane);
+}
+
+// (x & m) | (y & ~m) as one instruction (from the expression the compiler
+// makes several where it sees parts shared)
+__device__ __forceinline__ uint32_t bfi(uint32_t m, uint32_t x, uint32_t y)
+{
+    uint32_t r;
+    asm("v_bfi_b32 %0, %1, %2, %3" : "=v"(r) : "s"(m), "v"(x), "v"(y));
+    return r;
 }
 
 // The eight bit planes of a lane's 32 bytes: a is its chunk of the set's first
 // round, b of the second. Bit 8c + i of plane j is bit j of byte c of dword i
 // (i < 4 in a, else b): an 8 x 8 bit transposition in each byte column, three
 // stages of pairwise exchanges.
-__device__ __forceinline__ uint32_t bfi(uint32_t m, uint32_t x, uint32_t y) { return (x & m) | (y & ~m); }
-
 __device__ __forceinline__ void planes(const uint4 &a, const uint4 &b, uint32_t (&w)[8])
 {
     w[0] = a.x; w[1] = a.y; w[2] = a.z; w[3] = a.w;
@@ -210,35 +233,42 @@ __device__ __forceinline__ uint32_t ascii_space(const uint32_t (&b)[8])
     return m & ~b[7] & ~b[6];
 }
 
-// Planes move by whole bytes of the text. Inside a lane bytes of one dword are
-// 8 bits apart and dwords one bit; a round's lanes follow each other, then
-// the second round. `edge` holds lane 0's (or lane 63's) neighbour bits.
-// prev1: each byte's predecessor; `in` is the bit of the byte before the set.
-__device__ __forceinline__ uint32_t prev1(uint32_t x, uint32_t in)
+// Planes move by whole bytes of the text: inside a lane bytes of one dword are
+// 8 bits apart and dwords one bit; a round's lanes follow each other. Across
+// the rounds' ends only `edge` enters (0 for the pieces of separators, whose
+// crossings of a round's end are looked up apart).
+// prev1: each byte's predecessor; bits 27 and 31 of edge: those of lane 0's
+// first byte in the two rounds.
+__device__ __forceinline__ uint32_t prev1(uint32_t x, uint32_t edge)
 {
-    const uint32_t edge = (in << 27) | ((readlane32(x, 63) << 4) & 0x80000000u);
     const uint32_t z = bfi(0x11111111u, wave_shr1(x, edge) >> 3, x << 1);
     return __builtin_amdgcn_alignbyte(x, z, 3);
 }
 
-// next1: each byte's successor; 0 past the set's end.
-__device__ __forceinline__ uint32_t next1(uint32_t x)
+__device__ __forceinline__ uint32_t prev1(uint32_t x)
 {
-    const uint32_t edge = (readlane32(x, 0) >> 4) & 1u;
-    const uint32_t z = bfi(0x88888888u, wave_shl1(x, edge) << 3, x >> 1);
-    return __builtin_amdgcn_alignbyte(z, x, 1);
+    // (zero into lane 0)
+    const uint32_t p = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x138, 0xF, 0xF, true);
+    return __builtin_amdgcn_alignbyte(x, bfi(0x11111111u, p >> 3, x << 1), 3);
 }
 
-// The bytes covered by multi-byte separators that lie inside the set and
-// inside one prompt (bd: bytes that prompts start at). Leads that can start
-// one: C2, E1, E2, E3.
+// next1: each byte's successor in its round.
+__device__ __forceinline__ uint32_t next1(uint32_t x)
+{
+    const uint32_t n = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x130, 0xF, 0xF, true);
+    return __builtin_amdgcn_alignbyte(bfi(0x88888888u, n << 3, x >> 1), x, 1);
+}
+
+// The bytes covered by multi-byte separators that lie inside one round and
+// inside one prompt (bd: bytes that prompts start at; none continues a
+// separator). Leads that can start one: C2, E1, E2, E3; z: 11x000xx.
 __device__ __forceinline__ uint32_t wide_space(const uint32_t (&b)[8], uint32_t z, uint32_t bd)
 {
     // lead codes: k3 = C2; (k1, k2) = E1: (1, 0), E2: (0, 1), E3: (1, 1)
     const uint32_t k1 = z & b[5] & b[0], k2 = z & b[5] & b[1], k3 = z & ~b[5] & b[1] & ~b[0];
-    const uint32_t q1 = prev1(k1, 0u) & ~bd, q2 = prev1(k2, 0u) & ~bd, q3 = prev1(k3, 0u) & ~bd;
+    const uint32_t q1 = prev1(k1), q2 = prev1(k2), q3 = prev1(k3);
     // second bytes
-    const uint32_t c = b[7] & ~b[6], lo5 = c & ~b[5];
+    const uint32_t c = b[7] & ~b[6] & ~bd, lo5 = c & ~b[5];
     const uint32_t n0 = ~(b[2] | b[1] | b[0]), n1 = n0 & ~b[3] & ~b[4];
     const uint32_t is80 = lo5 & n1;
     const uint32_t top = lo5 & ~b[4] & ~b[3] & ~b[1] & b[0];                // 81 or 85
@@ -252,7 +282,7 @@ __device__ __forceinline__ uint32_t wide_space(const uint32_t (&b)[8], uint32_t 
     const uint32_t u5 = b[3] & ((b[2] & b[1] & b[0]) | ~(b[2] | b[1]));
     const uint32_t u4 = ~b[3] | (~b[2] & ~(b[1] & b[0]));
     const uint32_t wide = c & ~b[4] & ((b[5] & u5) | (~b[5] & u4));
-    const uint32_t pa1 = prev1(pa, 0u) & ~bd, pb1 = prev1(pb, 0u) & ~bd;
+    const uint32_t pa1 = prev1(pa), pb1 = prev1(pb);
     const uint32_t t3 = (pa1 & ((pb1 & wide) | (~pb1 & is80))) | (~pa1 & pb1 & is1a & b[2] & b[0]);
     const uint32_t v = t2 | t3;
     return v | next1(v | next1(t3));
@@ -262,7 +292,7 @@ __device__ __forceinline__ uint32_t wide_space(const uint32_t (&b)[8], uint32_t 
 // window of 64 offsets, m the lanes that hold such boundaries. Returns the
 // first index past them.
 template <typename F>
-__device__ __forceinline__ uint32_t for_boundaries(WaveState &st, const RangeCtx &rc, uint64_t end, int lane,
+__device__ __forceinline__ uint32_t for_boundaries(WaveState &st, const RangeCtx &rc, uint32_t end, int lane,
                                                    F body)
 {
     uint32_t s = st.s_ptr;
@@ -271,25 +301,31 @@ __device__ __forceinline__ uint32_t for_boundaries(WaveState &st, const RangeCtx
         const uint32_t kk = s - st.wb;
         const uint64_t m = __ballot((uint32_t)lane >= kk && st.win < end);
         body(m);
-        if (!((m >> 63) & 1ull)) return st.wb + kk + (uint32_t)__popcll(m);
-        s = st.wb + 64;
+        if (!((m >> 63) & 1ull)) return uniform(st.wb + kk + (uint32_t)__popcll(m));
+        s = uniform(st.wb + 64);
         if (s > rc.N) return s;
     }
 }
 
-// One 2 KiB set at byte sb: word starts counted, boundaries given their
-// prefixes. `last` and `next`: the set's last dword and the one behind it.
+// May a separator begin in the last two bytes of this dword and end behind it?
+__device__ __forceinline__ bool may_cross(uint32_t last)
+{
+    const uint32_t c1 = last >> 24, c2 = (last >> 16) & 0xFFu;
+    return c1 == 0xC2u || c1 - 0xE1u <= 2u || c2 - 0xE1u <= 2u;
+}
+
+// One 2 KiB set, pos bytes into the range: word starts counted, boundaries
+// given their prefixes. next: the dword behind the set.
 __device__ __forceinline__ void process_set(WaveState &st, const RangeCtx &rc, const uint4 &d0, const uint4 &d1,
-                                            uint32_t last, uint32_t next, uint64_t sb, int lane)
+                                            uint32_t next, uint32_t pos, int lane)
 {
     uint32_t b[8];
     planes(d0, d1, b);
-    ensure_window(st, rc, st.s_ptr, lane);
-    const bool bnd = readlane64(st.win, (int)(st.s_ptr - st.wb)) < sb + kSet;
+    const bool bnd = st.next < pos + kSet;
     uint32_t bd = 0;
     if (bnd)
-        for_boundaries(st, rc, sb + kSet, lane, [&](uint64_t m) {
-            const uint32_t wrel = (uint32_t)(st.win - sb);
+        for_boundaries(st, rc, pos + kSet, lane, [&](uint64_t m) {
+            const uint32_t wrel = st.win - pos;
             for (; m; m &= m - 1) {
                 const uint32_t rel = readlane32(wrel, __builtin_ctzll(m));
                 const uint32_t bit = 1u << (8u * (rel & 3u) + 4u * ((rel >> 10) & 1u) + ((rel >> 2) & 3u));
@@ -297,24 +333,42 @@ __device__ __forceinline__ void process_set(WaveState &st, const RangeCtx &rc, c
             }
         });
     uint32_t ws = ascii_space(b);
-    // 110000xx, 111000xx
     const uint32_t z = b[7] & b[6] & ~b[4] & ~b[3] & ~b[2];
     if (__ballot(z != 0)) ws |= wide_space(b, z, bd);
-    // separators across the set's ends
-    const uint32_t cross = last >= 0xC2000000u || (last & 0xFF0000u) >= 0xE10000u
-                               ? crossing(rc, last, next, sb + kSet, lane) : 0u;
-    if (st.spill | cross) {
-        if (lane == 0) ws |= (st.spill & 1u) | ((st.spill & 2u) << 7);
-        if (lane == 63) ws |= ((cross & 1u) << 23) | ((cross & 2u) << 30);
+    // separators across the rounds' ends
+    const uint32_t last0 = readlane32(d0.w, 63), last1 = readlane32(d1.w, 63);
+    uint32_t cross0 = 0, cross1 = 0;
+    if (may_cross(last0) || may_cross(last1)) {
+        // lanes 0..3: the first and the second round's end, from its last
+        // byte and from the one before
+        const bool second = lane & 1, two = lane & 2;
+        const uint32_t before = second ? last1 : last0, at = second ? next : readlane32(d1.x, 0);
+        const uint32_t len = mb_space_len_nb(two ? __builtin_amdgcn_alignbyte(at, before, 2)
+                                                 : __builtin_amdgcn_alignbyte(at, before, 3));
+        uint64_t hits = __ballot(lane < 4 && (two ? len == 3 : len != 0));
+        for (; hits; hits &= hits - 1) {
+            const int l = __builtin_ctzll(hits);
+            const uint32_t c = coverage(rc, pos + (1u + (l & 1)) * kRound, 1u + (uint32_t)(l >> 1), readlane32(len, l), lane);
+            if (l & 1) cross1 |= c;
+            else cross0 |= c;
+        }
     }
-    st.spill = cross >> 2;
-    const uint32_t before = prev1(ws, st.ws_prev);
-    st.ws_prev = readlane32(ws, 63) >> 31;
+    if (st.spill | cross0 | cross1) {
+        // lane 0: bytes 0, 1 of dwords 0 and 4; lane 63: bytes 2, 3 of dwords 3 and 7
+        const uint32_t s0 = cross0 >> 2;
+        if (lane == 0) ws |= (st.spill & 1u) | ((st.spill & 2u) << 7) | ((s0 & 1u) << 4) | ((s0 & 2u) << 11);
+        if (lane == 63)
+            ws |= ((cross0 & 1u) << 19) | ((cross0 & 2u) << 26) | ((cross1 & 1u) << 23) | ((cross1 & 2u) << 30);
+    }
+    st.spill = cross1 >> 2;
+    const uint32_t top = readlane32(ws, 63);
+    const uint32_t before = prev1(ws, (st.ws_prev << 27) | ((top << 4) & 0x80000000u));
+    st.ws_prev = top >> 31;
     uint32_t start = ~ws & (before | bd);
-    if (sb + kSet > rc.ws_end) {   // the text's end: bytes past it do not count
+    if (pos + kSet > rc.len) {   // the text's end: bytes past it do not count
         for (uint32_t i = 0; i < 8; i++)
             for (uint32_t c = 0; c < 4; c++)
-                if (sb + (i >> 2) * kRound + 16u * (uint32_t)lane + 4u * (i & 3u) + c >= rc.ws_end)
+                if (pos + (i >> 2) * kRound + 16u * (uint32_t)lane + 4u * (i & 3u) + c >= rc.len)
                     start &= ~(1u << (8u * c + i));
     }
     if (!bnd) {
@@ -326,8 +380,8 @@ __device__ __forceinline__ void process_set(WaveState &st, const RangeCtx &rc, c
     st.acc = 0;
     const uint32_t cnt = (uint32_t)__popc(start & 0x0F0F0F0Fu) | ((uint32_t)__popc(start & 0xF0F0F0F0u) << 16);
     const uint32_t incl = wave_incl_scan_dpp(cnt), excl = incl - cnt, tot = readlane32(incl, 63);
-    st.s_ptr = for_boundaries(st, rc, sb + kSet, lane, [&](uint64_t m) {
-        const uint32_t rel = (uint32_t)(st.win - sb);
+    st.s_ptr = for_boundaries(st, rc, pos + kSet, lane, [&](uint64_t m) {
+        const uint32_t rel = st.win - pos;
         const int src = (int)((rel >> 4) & 63u);
         const uint32_t ex = (uint32_t)__shfl((int)excl, src, 64), sw = (uint32_t)__shfl((int)start, src, 64);
         const uint32_t r4 = 4u * ((rel >> 10) & 1u), i = r4 + ((rel >> 2) & 3u);
@@ -336,13 +390,16 @@ __device__ __forceinline__ void process_set(WaveState &st, const RangeCtx &rc, c
         const uint32_t cols = (0x01010101u & ((1u << (8u * (rel & 3u))) - 1u)) << i;
         const uint32_t val = (uint32_t)st.running + (r4 ? (tot & 0xFFFFu) + (ex >> 16) : ex & 0xFFFFu) +
                              (uint32_t)__popc(sw & (rows | cols));
-        if (((m >> lane) & 1ull) && st.win >= rc.ws_start && st.win < rc.ws_end)
-            rc.ploc[st.wb + (uint32_t)lane] = val;
+        if ((m >> lane) & 1ull) rc.ploc[st.wb + (uint32_t)lane] = val;
     });
     st.running += (tot & 0xFFFFu) + (tot >> 16);
+    ensure_window(st, rc, st.s_ptr, lane);
+    st.next = readlane32(st.win, (int)(st.s_ptr - st.wb));
 }
 
-__global__ __launch_bounds__(kBlock, 7) void k_char_main(const uint8_t *__restrict__ text, uint64_t B,
+// 8 waves per SIMD (64 registers): 7 cost 1% more, 6 4%; a second super-round
+// in flight per wave (5 or 4 waves) 20%.
+__global__ __launch_bounds__(kBlock, 8) void k_char_main(const uint8_t *__restrict__ text, uint64_t B,
                                                       const uint64_t *__restrict__ off, uint32_t N,
                                                       uint64_t Rw, uint32_t nwaves,
                                                       uint32_t *__restrict__ ploc,
@@ -356,16 +413,20 @@ __global__ __launch_bounds__(kBlock, 7) void k_char_main(const uint8_t *__restri
     rc.off = off;
     rc.N = N;
     rc.ws_start = (uint64_t)w * Rw;
-    rc.ws_end = rc.ws_start + Rw < B ? rc.ws_start + Rw : B;
     rc.ploc = ploc;
     if (rc.ws_start >= B) {
         if (lane == 0) wavetot[w] = 0;
         return;
     }
+    const uint64_t left = B - rc.ws_start;
+    rc.len = (uint32_t)(left < Rw ? left : Rw);
+    // super-rounds that end at or before `whole` bytes into the range have
+    // every chunk and the dword behind them inside the buffer
+    const uint32_t whole = left < 4 ? 0u : (uint32_t)(left - 4 < Rw ? left - 4 : Rw);
     WaveState st;
-    st.s_ptr = lower_bound_wave(off, (uint64_t)N + 1, rc.ws_start, lane);
-    st.wb = st.s_ptr;
-    st.win = win_load(off, N, st.wb, lane);
+    st.s_ptr = uniform(lower_bound_wave(off, (uint64_t)N + 1, rc.ws_start, lane));
+    load_window(st, rc, st.s_ptr, lane);
+    st.next = readlane32(st.win, 0);
     st.running = 0;
     st.acc = 0;
     st.ws_prev = 1;
@@ -373,43 +434,41 @@ __global__ __launch_bounds__(kBlock, 7) void k_char_main(const uint8_t *__restri
     if (rc.ws_start > 0) {   // then ws_start >= Rw >= 4 KiB
         // whether the byte before the range is whitespace, and what a
         // separator begun there covers of the range
-        const uint32_t before = load4(text, B, rc.ws_start - 4), at = load4(text, B, rc.ws_start);
-        const uint32_t c = crossing(rc, before, at, rc.ws_start, lane);
-        const uint32_t p = before >> 24;
+        const uint32_t before = uniform(load4(text, B, rc.ws_start - 4)), at = uniform(load4(text, B, rc.ws_start));
+        const uint32_t c = crossing(rc, before, at, 0u, lane), p = before >> 24;
         st.spill = c >> 2;
-        st.ws_prev = ((c >> 1) & 1u) | (p - 0x09u <= 4u || p - 0x1Cu <= 4u ? 1u : 0u);
-        if (!st.ws_prev && p >= 0x80u && p < 0xC0u)   // the last byte of one
-            st.ws_prev = (((before >> 16) & 0xFFu) == 0xC2u && separator_before(rc, before, at, rc.ws_start, 2, lane)) ||
-                         separator_before(rc, before, at, rc.ws_start, 3, lane);
+        st.ws_prev = (c >> 1) & 1u;
+        if (p - 0x09u <= 4u || p - 0x1Cu <= 4u) st.ws_prev = 1;
+        // or one that ends there
+        if (mb_space_len_nb(bytes_from(before, at, 2)) == 2) st.ws_prev |= coverage(rc, 0u, 2, 2, lane) >> 1;
+        if (mb_space_len_nb(bytes_from(before, at, 3)) == 3) st.ws_prev |= coverage(rc, 0u, 3, 3, lane) >> 1;
     }
-    const uint64_t sr_bytes = (uint64_t)kRound * kLoadRounds;
-    for (uint64_t sb = rc.ws_start; sb < rc.ws_end; sb += sr_bytes) {
-        // whole: every chunk and the trailing dword lie inside the buffer
-        const bool whole = sb + sr_bytes + 4 <= B;
+    constexpr uint32_t sr_bytes = kRound * kLoadRounds;
+    for (uint32_t pos = 0; pos < rc.len; pos += sr_bytes) {
+        const uint8_t *src = text + rc.ws_start + pos;
         uint4 d[kLoadRounds];
         uint32_t tail = 0;
-        if (whole) {
+        if (pos + sr_bytes <= whole) {
 #pragma unroll
             for (uint32_t u = 0; u < kLoadRounds; u++) {
-                v4u v = __builtin_nontemporal_load(
-                    reinterpret_cast<const v4u *>(text + sb + (uint64_t)u * kRound + 16u * (uint32_t)lane));
+                v4u v = __builtin_nontemporal_load(reinterpret_cast<const v4u *>(src + u * kRound + 16u * (uint32_t)lane));
                 d[u] = make_uint4(v.x, v.y, v.z, v.w);
             }
-            tail = *reinterpret_cast<const uint32_t *>(text + sb + sr_bytes);
+            tail = *reinterpret_cast<const uint32_t *>(src + sr_bytes);
         } else {
+            const uint64_t sb = rc.ws_start + pos;
 #pragma unroll
             for (uint32_t u = 0; u < kLoadRounds; u++) {
                 uint64_t c = sb + (uint64_t)u * kRound + 16u * (uint32_t)lane;
                 d[u] = c < B ? load16(text, B, c) : make_uint4(0u, 0u, 0u, 0u);
             }
-            tail = load4(text, B, sb + sr_bytes);
+            tail = uniform(load4(text, B, sb + sr_bytes));
         }
 #pragma unroll
         for (uint32_t u = 0; u < kLoadRounds; u += 2) {
-            const uint64_t pb = sb + (uint64_t)u * kRound;
-            if (pb >= rc.ws_end) break;
+            if (pos + u * kRound >= rc.len) break;
             const uint32_t next = u + 2 < kLoadRounds ? readlane32(d[u + 2 < kLoadRounds ? u + 2 : u].x, 0) : tail;
-            process_set(st, rc, d[u], d[u + 1], readlane32(d[u + 1].w, 63), next, pb, lane);
+            process_set(st, rc, d[u], d[u + 1], next, pos + u * kRound, lane);
         }
     }
     uint64_t total = st.running + readlane32(wave_incl_scan_dpp(st.acc), 63);
