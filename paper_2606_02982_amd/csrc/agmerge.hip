@@ -69,14 +69,7 @@ __device__ __forceinline__ double am_aged(const SortInput &in, uint32_t i, uint3
 // Lanes of the wave holding the same 4-bit class (ok lanes only).
 __device__ __forceinline__ uint64_t class_peers(uint32_t c, bool ok)
 {
-    uint64_t peers = __ballot(ok);
-#pragma unroll
-    for (int bb = 0; bb < 4; bb++) {
-        const bool bit = (c >> bb) & 1u;
-        const uint64_t m = __ballot(bit);
-        peers &= bit ? m : ~m;
-    }
-    return peers;
+    return match_bits<4>(c, __ballot(ok));
 }
 
 __global__ __launch_bounds__(kAmTPB) void k_am_count(AmArgs a)

@@ -46,6 +46,26 @@ __device__ __forceinline__ uint64_t match_bits(uint32_t x, uint64_t among)
     return among & ~(((uint64_t)hi << 32) | lo);
 }
 
+// match_bits<kBits>, and in `mine` the number of lanes of `among` whose low
+// bits of x equal the lane's index (lanes below 2^kBits).
+template <int kBits>
+__device__ __forceinline__ uint64_t match_count(uint32_t x, uint64_t among, uint32_t &mine)
+{
+    uint32_t lo = 0, hi = 0, clo = 0, chi = 0;
+#pragma unroll
+    for (int b = 0; b < kBits; b++) {
+        const uint32_t own = (uint32_t)__builtin_amdgcn_sbfe((int)x, b, 1);
+        const uint32_t ind = (uint32_t)__builtin_amdgcn_sbfe(lane_id(), b, 1);
+        const uint64_t m = __ballot(own != 0);
+        lo = __builtin_amdgcn_bitop3_b32(lo, (uint32_t)m, own, 0xF6);
+        hi = __builtin_amdgcn_bitop3_b32(hi, (uint32_t)(m >> 32), own, 0xF6);
+        clo = __builtin_amdgcn_bitop3_b32(clo, (uint32_t)m, ind, 0xF6);
+        chi = __builtin_amdgcn_bitop3_b32(chi, (uint32_t)(m >> 32), ind, 0xF6);
+    }
+    mine = (uint32_t)__popcll(among & ~(((uint64_t)chi << 32) | clo));
+    return among & ~(((uint64_t)hi << 32) | lo);
+}
+
 // DPP lane moves (gfx9 wave shifts): lane i receives lane i-1 (shr) or
 // lane i+1 (shl) of x; the lane without a source receives `edge`.
 __device__ __forceinline__ uint32_t wave_shr1(uint32_t x, uint32_t edge)

@@ -87,14 +87,7 @@ __device__ inline uint32_t block_excl_scan_digits(uint32_t x, uint32_t *tmp4)
 // the number of them in lower lanes.
 __device__ __forceinline__ uint64_t digit_peers(uint32_t dg, bool ok)
 {
-    uint64_t peers = __ballot(ok);
-#pragma unroll
-    for (int bb = 0; bb < 8; bb++) {
-        const bool bit = (dg >> bb) & 1u;
-        const uint64_t m = __ballot(bit);
-        peers &= bit ? m : ~m;
-    }
-    return peers;
+    return match_bits<8>(dg, __ballot(ok));
 }
 
 }  // namespace ds

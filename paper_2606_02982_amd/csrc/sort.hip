@@ -298,13 +298,7 @@ __global__ __launch_bounds__(TPB) void k_sort_pass(SortBatch b, uint32_t p)
         uint32_t idx = (uint32_t)w * kWaveKeys + (uint32_t)r * 64u + (uint32_t)lane;
         bool ok = idx < cnt;
         uint32_t dg = (uint32_t)(k[r] >> shift) & 255u;
-        uint64_t peers = __ballot(ok);
-#pragma unroll
-        for (int bb = 0; bb < 8; bb++) {
-            bool bit = (dg >> bb) & 1u;
-            uint64_t m = __ballot(bit);
-            peers &= bit ? m : ~m;
-        }
+        uint64_t peers = digit_peers(dg, ok);
         uint32_t below = (uint32_t)__popcll(peers & lanemask_lt());
         uint32_t old = ok ? wcnt[w][dg] : 0u;
         rk[r] = old + below;

@@ -201,16 +201,9 @@ __global__ __launch_bounds__(kEA) void k_err_accum(uint64_t n, const double *__r
                     s.g[u] -= c0;   // wraps below c0
                     // events of no group of this pass still count among all events (once)
                     ok[u] = usable(s.x[u]) && (c0 == 0 || s.g[u] < cn);
-                    const uint64_t among = __ballot(ok[u]);
-                    peers[u] = match_bits<4>(s.g[u], among);
-                    // owner = lane (lanes below 16)
-                    uint64_t all = among;
-#pragma unroll
-                    for (int bb = 0; bb < 4; bb++) {
-                        const uint64_t m = __ballot((s.g[u] >> bb) & 1u);
-                        all &= (lane >> bb) & 1u ? m : ~m;
-                    }
-                    if (lane < kWaves) cnt[lane * kChunks + u * kWaves + w] = (uint16_t)__popcll(all);
+                    uint32_t mine;
+                    peers[u] = match_count<4>(s.g[u], __ballot(ok[u]), mine);
+                    if (lane < kWaves) cnt[lane * kChunks + u * kWaves + w] = (uint16_t)mine;   // owner = lane
                 }
                 lds_sync();
                 // lane l holds owner l / 4, chunks 8 (l % 4) .. + 7
