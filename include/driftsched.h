@@ -104,7 +104,7 @@ typedef enum {
 
 /*
  * Bounded waits. The sorts behind ds_order, ds_order_multi, ds_calibrate
- * (above 4096 groups) and ds_simulate split their work into tiles that wait,
+ * (above 65536 groups, and above 4096 with DS_NO_WAIT) and ds_simulate split their work into tiles that wait,
  * each for at most about 0.2 s, on counts published by tiles of smaller
  * index (decoupled look-back); the orders of more than 2^18 and at most
  * 2^20 requests have no such waits. ds_calibrate of at most 64 chunks of

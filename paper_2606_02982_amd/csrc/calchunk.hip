@@ -1,40 +1,44 @@
-// Stage 2 for up to kCalGroupsLds groups: Eq. (5) with the ratio of Eq. (6)
+// Stage 2 for up to kCalGroupsChunked groups: Eq. (5) with the ratio of Eq. (6)
 // (Sec. "Runtime Calibration and Feedback Adaptation") without a global
 // partition of the events by group, so that every access is coalesced.
 //
-// The events, in completion order, are cut into C chunks of L events (L a
-// multiple of the sub-tile). With M(c, g) the composition of the affine maps
-// x -> (1 - alpha) x + alpha r of group g's events in chunk c (in order):
-//   k_calc_agg    per chunk (one block): each sub-tile (512 or 4096 events) is
+// The events, in completion order, are cut into C chunks of L events. With
+// M(c, g) the composition of the affine maps x -> (1 - alpha) x + alpha r of
+// group g's events in chunk c (in order):
+//   small tables (at most kCalGroupsLds groups):
+//   k_calc_agg    per chunk (one block): each sub-tile of 512 events is
 //                 sorted by group in LDS (stable LSD passes, wave ballots),
 //                 scanned as a segmented scan of maps, and each group's part
 //                 is composed into that group's map in LDS; the chunk writes
-//                 M(c, g) for every group (or "no usable event"). For the
-//                 large tables it also writes each event's map from the
-//                 chunk's start (through the event when only the trace is
-//                 wanted, else to just before it), as a count k of usable
-//                 events (its slope is (1 - alpha)^k) and an offset.
+//                 M(c, g) for every group (or "no usable event").
+//   k_calc_apply  per chunk: the maps of the chunks before it applied to the
+//                 initial factors (k_calc_agg keeps a copy of them), the same
+//                 sub-tile sort and scan; every event then runs the exact
+//                 update from its carried factor, in order, and the traces
+//                 are staged in LDS and written in event order. The last
+//                 chunk's block writes the final factors.
+//   k_calc_one    when besides there are at most kOneChunks chunks of one
+//                 sub-tile each: both in one pass over the events. Each block
+//                 sorts and scans its sub-tile once, publishes its chunk's
+//                 maps, reads those of the chunks before it (a bounded wait
+//                 for words not yet written), and applies the updates; a
+//                 small launch before it marks the words unwritten.
+//   large tables:
+//   k_calc_own    per chunk (one block, or one per range of 8192 groups): the
+//                 waves own the groups between them, and each composes its
+//                 groups' maps event by event in LDS. The chunk writes M(c, g)
+//                 as a count k of usable events (its slope is (1 - alpha)^k)
+//                 and an offset, and for traces each event's map from the
+//                 chunk's start the same way (through the event when only the
+//                 trace is wanted, else to just before it).
 //   k_calc_scan   per 64 groups (one block, lane = group): the group's
 //                 factor before chunk c is M(c-1, g) o ... o M(0, g) applied
 //                 to its initial factor (sixteen stretches of chunks composed
 //                 by sixteen waves, then chained in order); writes those
-//                 carries and the final factor, and the powers of 1 - alpha.
-//   k_calc_ev     large tables, per event: its chunk's carry through its
-//                 map; without the event, followed by the exact update t1 =
-//                 (1 - alpha) c, t2 = alpha r, c = t1 + t2.
-//   k_calc_apply  small tables, per chunk: the same sub-tile sort and scan;
-//                 every event then runs the exact update from its carried
-//                 factor, in order, and the traces are staged in LDS and
-//                 written in event order.
-// When the table of chunk maps is small (C x G <= kSmallTable), k_calc_scan
-// is left out: each k_calc_apply block applies the maps of the chunks before
-// it to the initial factors itself (k_calc_agg keeps a copy of them), and
-// the last chunk's block writes the final factors.
-// When besides there are at most kOneChunks chunks of one sub-tile each,
-// k_calc_one does all of it in one pass over the events: each block sorts
-// and scans its sub-tile once, publishes its chunk's maps, reads those of
-// the chunks before it (a bounded wait for words not yet written), and
-// applies the updates; a small launch before it marks the words unwritten.
+//                 carries and the final factor.
+//   k_calc_ev     per event: its chunk's carry through its map; without the
+//                 event, followed by the exact update t1 = (1 - alpha) c,
+//                 t2 = alpha r, c = t1 + t2.
 // Results match the sequential recurrence up to the rounding of the
 // composed maps (a few ulps; the contract is 1e-12 relative).
 #include "common.h"
@@ -45,16 +49,28 @@ namespace ds {
 namespace {
 
 constexpr int kT = 512;                  // threads per block
-// events per thread per sub-tile (kE) is a template parameter: 1 for the
-// small tables (more, shorter blocks; 1, 2 or 4 in one launch), kBigE for
-// the large ones; kSub = kT * kE events per sub-tile
+// events per thread per sub-tile (kE) is a template parameter: 1, or 2 or 4 in
+// one launch; kSub = kT * kE events per sub-tile
 constexpr int kW = kT / 64;
 constexpr uint32_t kG = kCalGroupsLds;   // groups held in LDS
 constexpr uint32_t kMaxTable = 1u << 20; // C x G entries at most (C >= 1)
+constexpr uint32_t kMaxTableR = 1u << 21;   // the same above kCalGroupsLds groups
 constexpr uint32_t kMaxChunks = 512;
-constexpr uint32_t kSmallTable = 16384;  // C x G up to which the carries are formed in k_calc_apply
+constexpr uint32_t kSmallTable = 16384;  // C x G at most of the one-launch path
+// C x G at most of k_calc_agg and k_calc_apply, and one sub-tile per chunk:
+// every k_calc_apply block reads the maps of all chunks before it. Measured
+// against k_calc_own and its two launches (with the trace): 262,144 events,
+// 4 groups 19.4 and 27.7 us, 16 groups 24.8 and 27.8, 32 groups 33.8 and 27.1;
+// 524,288 events, 4 groups 30.0 and 30.3, 16 groups 34.1 and 30.4.
+constexpr uint32_t kSmallPair = 8192;
 constexpr uint32_t kCarryR = 4;          // chunk maps per thread held in registers for the carry
-constexpr uint32_t kBigE = 8;            // events per thread per sub-tile of the large tables
+
+constexpr int kOT = 1024;                // k_calc_own: threads per block
+constexpr uint32_t kOW = kOT / 64;       // its waves, the owners of the groups g = w (mod kOW)
+constexpr uint32_t kOU = 4;              // events per thread per step
+constexpr uint32_t kOStep = kOT * kOU;
+constexpr uint32_t kOHeavy = 640;        // an owner's events of a step above which chunks combine theirs first
+constexpr uint32_t kRangeGroups = 8192;  // groups per block above kCalGroupsLds groups
 
 struct CalArgs {
     const uint32_t *group;
@@ -67,9 +83,11 @@ struct CalArgs {
     uint32_t passes;         // 8-bit LSD passes over the group key (key < 2^(8 passes))
     uint32_t keybits;        // bits of the largest key (G, for an event outside the groups)
     double *aggA, *aggB;     // [C][G]: M(c, g) = x -> A x + B; A < 0: no usable event
+    uint32_t *aggK;          // large tables instead of aggA: A = (1 - alpha)^K; 0: no usable event
+    uint32_t R;              // large tables: ranges of kRangeGroups groups (1: one block per chunk)
     double *carry;           // [C][G]: factor of g before chunk c
     double *s0;              // [G] the initial factors (small tables: no k_calc_scan)
-    uint32_t small;          // C x G <= kSmallTable
+    uint32_t small;          // a small table
     double *state;           // [G] in: before all events, out: after
     double *trace, *trace_before;
     uint32_t *status;        // the call's wait status word, or NULL: set by a wait that runs out
@@ -156,8 +174,7 @@ struct SubShared {
     uint8_t ok[kSub];        // usable
 };
 
-// The raw events of a sub-tile (wave-major slots as in load_sort_scan),
-// loaded one sub-tile ahead of their use.
+// The raw events of a sub-tile (wave-major slots as in load_sort_scan).
 template <int kE>
 struct Raw {
     uint32_t g[kE], o[kE];
@@ -180,27 +197,6 @@ __device__ __forceinline__ void load_raw(const CalArgs &a, uint32_t s0, uint32_t
             raw.x[r] = a.est[e];
             raw.o[r] = a.obs[e];
         }
-    }
-}
-
-// The big sub-tiles (several per chunk) are loaded one ahead: the current
-// one's events come from `next`, and the following one's loads are issued
-// before the current one is sorted (the barriers there wait on LDS only).
-// The small ones are loaded where they are used.
-template <int kE>
-constexpr bool kPrefetch = kE > 1;
-
-template <int kE>
-__device__ __forceinline__ void fetch(const CalArgs &a, uint64_t s0, uint64_t c1, uint32_t m, Raw<kE> &raw,
-                                      Raw<kE> &next)
-{
-    constexpr uint32_t kSub = kT * kE;
-    if constexpr (kPrefetch<kE>) {
-        raw = next;
-        if (s0 + kSub < c1)
-            load_raw<kE>(a, (uint32_t)(s0 + kSub), (uint32_t)(c1 - s0 - kSub < kSub ? c1 - s0 - kSub : kSub), next);
-    } else {
-        load_raw<kE>(a, (uint32_t)s0, m, raw);
     }
 }
 
@@ -256,14 +252,9 @@ __device__ void load_sort_scan(const CalArgs &a, const Raw<kE> &raw, uint32_t m,
             const uint32_t sl = (uint32_t)w * (64u * kE) + (uint32_t)r * 64u + (uint32_t)lane;
             const bool v = sl < m;
             const uint32_t dg = (key[r] >> (8 * p)) & 255u;
-            uint64_t peers = __ballot(v);
-#pragma unroll
-            for (int bb = 0; bb < 8; bb++) {
-                if (8 * p + bb >= a.keybits) break;   // a bit no key has
-                const bool bit = (dg >> bb) & 1u;
-                const uint64_t mk = __ballot(bit);
-                peers &= bit ? mk : ~mk;
-            }
+            // (four bits at a time; bits no key has are left out)
+            uint64_t peers = match_bits<4>(dg, __ballot(v));
+            if (8 * p + 4 < a.keybits) peers = match_bits<4, 4>(dg, peers);
             const uint32_t below = (uint32_t)__popcll(peers & lanemask_lt());
             const uint32_t old = v ? sh.wcnt[w][dg] : 0u;
             rk[r] = old + below;
@@ -362,77 +353,27 @@ __device__ void load_sort_scan(const CalArgs &a, const Raw<kE> &raw, uint32_t m,
     out.excl = ex;
 }
 
-// kEv: each event's map from the chunk's start to just before it is
-// written as well (xb, xk), so that the updates need no second sort.
-template <int kE, bool kEv>
+template <int kE>
 __global__ __launch_bounds__(kT) void k_calc_agg(CalArgs a)
 {
     constexpr uint32_t kSub = kT * kE;
     __shared__ SubShared<kE> sh;
     __shared__ double sA[kG], sB[kG];   // the chunk's map per group so far (A < 0: none)
-    __shared__ uint32_t sK[kEv ? kG : 1];   // its count of usable events
-    __shared__ uint32_t stK[kEv ? kSub : 1];   // per-event counts staged by slot
     const uint32_t t = threadIdx.x, c = blockIdx.x;
     if (a.clear && a.status && c == 0 && t == 0) *a.status = 0;
     for (uint32_t g = t; g < a.G; g += kT) {
         sA[g] = -1.0;
         sB[g] = 0.0;
-        if constexpr (kEv) sK[g] = 0;
-        if (a.small && c == 0) a.s0[g] = a.state[g];
+        if (c == 0) a.s0[g] = a.state[g];
     }
     const uint64_t c0 = (uint64_t)c * a.L;
     const uint64_t c1 = c0 + a.L < a.E ? c0 + a.L : a.E;
-    Raw<kE> next;
-    if (kPrefetch<kE> && c0 < c1) load_raw<kE>(a, (uint32_t)c0, (uint32_t)(c1 - c0 < kSub ? c1 - c0 : kSub), next);
     for (uint64_t s0 = c0; s0 < c1; s0 += kSub) {
         const uint32_t m = (uint32_t)(c1 - s0 < kSub ? c1 - s0 : kSub);
         Raw<kE> raw;
-        fetch<kE>(a, s0, c1, m, raw, next);
+        load_raw<kE>(a, (uint32_t)s0, m, raw);
         Sub<kE> sub;
         load_sort_scan<kE>(a, raw, m, sh, sub);   // (its first barrier orders the sA/sB writes)
-        if constexpr (kEv) {
-            // each event's map from the chunk's start: the chunk's map of
-            // its group before this sub-tile, then the group's events of
-            // this sub-tile before it; staged by slot, then written in
-            // event order
-            double *stB = sh.b;                  // read into sub by now
-            Map pre = sub.excl;
-#pragma unroll
-            for (int e = 0; e < kE; e++) {
-                const uint32_t i = t * kE + (uint32_t)e;
-                if (i >= m) break;
-                if (sub.flag[e]) pre = Map{0u, 0u, 1.0, 0.0, 0u};
-                Map mp;
-                mp.f = sub.flag[e];
-                mp.u = sub.ok[e];
-                mp.a = sub.ok[e] ? a.oma : 1.0;
-                mp.b = sub.ok[e] ? sub.b[e] : 0.0;
-                mp.k = sub.ok[e];
-                const Map inc = combine(pre, mp);   // the group's events through this one
-                if (a.incl) pre = inc;
-                const uint32_t g = sub.key[e];
-                double xb = pre.u ? pre.b : 0.0;
-                uint32_t xk = pre.k;
-                if (g < a.G && sA[g] >= 0.0) {
-                    const double pb = sB[g];
-                    if (pre.u) {
-                        const double tt = pre.a * pb;
-                        xb = tt + pre.b;
-                    } else {
-                        xb = pb;
-                    }
-                    xk += sK[g];
-                }
-                stB[sub.slot[e]] = xb;
-                stK[sub.slot[e]] = xk;
-                pre = inc;
-            }
-            lds_sync();   // every read of sA, sB, sK above precedes the updates below
-            for (uint32_t i = t; i < m; i += kT) {
-                a.xb[s0 + i] = stB[i];
-                a.xk[s0 + i] = stK[i];
-            }
-        }
         // the segment of each group in this sub-tile, composed into the
         // group's map at the segment's last position (one thread per group)
         Map run = sub.excl;
@@ -454,13 +395,11 @@ __global__ __launch_bounds__(kT) void k_calc_agg(CalArgs a)
                 if (pa < 0.0) {
                     sA[g] = run.a;
                     sB[g] = run.b;
-                    if constexpr (kEv) sK[g] = run.k;
                 } else {
                     // the chunk so far, then this segment
                     sA[g] = run.a * pa;
                     const double tt = run.a * sB[g];
                     sB[g] = tt + run.b;
-                    if constexpr (kEv) sK[g] += run.k;
                 }
             }
         }
@@ -470,6 +409,358 @@ __global__ __launch_bounds__(kT) void k_calc_agg(CalArgs a)
         a.aggA[(uint64_t)c * a.G + g] = sA[g];
         a.aggB[(uint64_t)c * a.G + g] = sB[g];
     }
+}
+
+// ---- large tables ---------------------------------------------------------------
+
+// One step's events in registers (event u * kOT + t of the step).
+struct OwnStep {
+    double x[kOU];
+    uint32_t g[kOU], o[kOU];
+};
+
+__device__ __forceinline__ void own_load(const CalArgs &a, uint64_t s0, uint64_t c1, OwnStep &s)
+{
+#pragma unroll
+    for (uint32_t u = 0; u < kOU; u++) {
+        const uint64_t e = s0 + u * kOT + threadIdx.x;
+        const bool in = e < c1;
+        s.g[u] = in ? a.group[e] : 0xFFFFFFFFu;   // no group
+        s.x[u] = in ? a.est[e] : 0.0;
+        s.o[u] = in ? a.obs[e] : 0u;
+    }
+}
+
+// Where a wave's share of the step lies: `at`: for lane l, the first place of
+// owner l / 4's events of the wave's chunk l % 4; [lo, hi): the places of the
+// wave's own events. heavy: some owner has more than kOHeavy.
+struct OwnPlaces {
+    uint32_t at, lo, hi;
+    bool heavy;
+};
+
+// From the table of counts (every wave scans it for itself). bm: masks of the
+// bytes of a 16-byte run that come before byte w.
+__device__ __forceinline__ OwnPlaces own_places(const uint8_t *cnt, const uint32_t (&bm)[4], uint32_t w)
+{
+    // lane l holds owner l / 4, chunks 16 (l % 4) .. + 15 (of 64 events: u = l % 4)
+    const uint4 v = *reinterpret_cast<const uint4 *>(&cnt[(uint32_t)lane_id() * 16]);
+    uint32_t sum = 0, before = 0;
+    sum = __builtin_amdgcn_sad_u8(v.x, 0u, sum);
+    sum = __builtin_amdgcn_sad_u8(v.y, 0u, sum);
+    sum = __builtin_amdgcn_sad_u8(v.z, 0u, sum);
+    sum = __builtin_amdgcn_sad_u8(v.w, 0u, sum);
+    before = __builtin_amdgcn_sad_u8(v.x & bm[0], 0u, before);
+    before = __builtin_amdgcn_sad_u8(v.y & bm[1], 0u, before);
+    before = __builtin_amdgcn_sad_u8(v.z & bm[2], 0u, before);
+    before = __builtin_amdgcn_sad_u8(v.w & bm[3], 0u, before);
+    const uint32_t incl = wave_incl_scan_dpp(sum);
+    OwnPlaces o;
+    o.at = incl - sum + before;
+    o.lo = w ? readlane32(incl, (int)(4 * w - 1)) : 0u;
+    o.hi = readlane32(incl, (int)(4 * w + 3));
+    uint32_t own = sum + (uint32_t)__shfl_xor((int)sum, 1, 64);
+    own += (uint32_t)__shfl_xor((int)own, 2, 64);
+    o.heavy = __ballot(own > kOHeavy) != 0;
+    return o;
+}
+
+// The lanes of one group (same: the live lanes with this lane's group) chained
+// in lane order: on return A, B is the map of the group's lanes up to this
+// one. rank: live lanes of the group before this one; prev0: the nearest.
+__device__ __forceinline__ void own_chain(uint64_t same, double &A, double &B, uint32_t &rank, int &prev0)
+{
+    const uint64_t below = same & lanemask_lt();
+    rank = (uint32_t)__popcll(below);
+    prev0 = below ? 63 - __clzll((long long)below) : lane_id();
+    int prev = prev0;
+    for (uint32_t st = 1; __ballot(rank >= st); st <<= 1) {
+        const double pA = __shfl(A, prev, 64), pB = __shfl(B, prev, 64);
+        const int pp = __shfl(prev, prev, 64);
+        if (rank >= st) {
+            const double tt = A * pB;
+            B = tt + B;
+            A = A * pA;
+            prev = pp;
+        }
+    }
+}
+
+// The chunk's maps and, with kEv, each event's map from the chunk's start.
+// Wave w owns the groups g = w (mod 16) of the block's range. A step of 4096
+// events is split by owner, stably, through LDS (four ballots per 64 events,
+// one table of counts that every wave scans for itself), and each wave takes
+// its own events 64 at a time, in event order: one ballot match finds the
+// lanes of a group, log2 of the largest such set pointer jumps compose their
+// maps (one jump for two lanes, six if one tenant holds all 64), the group's
+// map so far is read and written once. The next step's loads are in flight
+// meanwhile (the barriers wait on LDS alone). Where one owner would hold more
+// than kOHeavy of a step's events (256 on average; a tenant with a large share
+// of the traffic, or few groups), each wave first composes the lanes of a
+// group in each of its 64 events, so that the owners chain one map per group
+// and 64 events, and the events take their group's map from there.
+//
+// kGr = kCalGroupsLds: one block holds every group, and the events' maps are
+// staged and written in event order; kGr = kRangeGroups: a.R blocks per
+// chunk, each for a range of the groups, write their events' maps directly
+// (the blocks of a chunk sit on one XCD, whose L2 they share).
+//
+// What bounds it: latency inside a CU (one block of 16 waves, 146 KB of LDS).
+// 4,194,304 events over 4,096 groups: 57 us; the form before (sub-tiles of
+// 4096 events sorted by two LSD passes and scanned by 8 waves) 83 us. With one
+// group holding half or all of them: 75 and 57 us (without the heavy steps'
+// combining 145 and 235).
+// 1,048,575 events over 20,011 groups: 39 us; with a radix partition and
+// gathers through it the whole call took 157 us, now 61 us.
+template <uint32_t kGr, bool kEv>
+__global__ __launch_bounds__(kOT) void k_calc_own(CalArgs a)
+{
+    constexpr bool kStage = kEv && kGr == kG;
+    constexpr int kKeyBits = kGr == kG ? 8 : 9;
+    static_assert(kGr <= kOW << kKeyBits, "a wave's groups fit the key");
+    constexpr uint32_t kChunks = kOStep / 64;   // of 64 events per step: u * kOW + wave
+    static_assert(kChunks * kOW == 64 * 16 && kOU == 4, "16 counts per lane");
+    __shared__ double sB[kGr];            // the chunk's map per group so far: offset
+    __shared__ uint32_t sK[kGr];          // and count of usable events
+    __shared__ double stb[kOStep];        // staged events: alpha r (or 0),
+    __shared__ uint32_t stm[kOStep];      // slot | key << 12 | usable << 31
+    __shared__ double ob[kStage ? kOStep : 1];
+    __shared__ uint32_t ok_[kStage ? kOStep : 1];
+    __shared__ __align__(16) uint8_t cnt[kOW * kChunks];   // [owner][chunk]
+    __shared__ double pw64[65];           // powers of 1 - alpha
+    const uint32_t t = threadIdx.x, lane = (uint32_t)lane_id();
+    const uint32_t w = (uint32_t)__builtin_amdgcn_readfirstlane((int)(t >> 6));
+    if (a.clear && a.status && blockIdx.x == 0 && t == 0) *a.status = 0;
+    // block b: XCD b % 8, where it is the (b / 8)-th; the ranges of one chunk
+    // follow each other there
+    uint32_t c = blockIdx.x, r = 0;
+    if (kGr != kG) {
+        const uint32_t y = blockIdx.x / 8u;
+        c = blockIdx.x % 8u + 8u * (y / a.R);
+        r = y % a.R;
+        if (c >= a.C) return;
+    }
+    const uint32_t g0 = r * kGr, gn = a.G - g0 < kGr ? a.G - g0 : kGr;
+    for (uint32_t g = t; g < kGr; g += kOT) {
+        sB[g] = 0.0;
+        sK[g] = 0;
+    }
+    uint32_t bm[4];
+#pragma unroll
+    for (uint32_t q = 0; q < 4; q++)
+        bm[q] = w >= 4 * q + 4 ? 0xFFFFFFFFu : w <= 4 * q ? 0u : (1u << (8 * (w - 4 * q))) - 1u;
+    const uint64_t c0 = (uint64_t)c * a.L;
+    const uint64_t c1 = c0 + a.L < a.E ? c0 + a.L : a.E;
+    OwnStep cur;
+    own_load(a, c0, c1, cur);
+    // (while those loads are in flight) the powers of 1 - alpha: the block's,
+    // and the tables that k_calc_scan and k_calc_ev read
+    if (t <= 64) pw64[t] = pow(a.oma, (double)t);
+    if (blockIdx.x == 0) a.pw[t] = pow(a.oma, (double)(t & 255u) * (double)(1u << (8 * (t >> 8))));
+    lds_sync();
+    for (uint64_t s0 = c0; s0 < c1; s0 += kOStep) {
+        const OwnStep s = cur;
+        if (s0 + kOStep < c1) own_load(a, s0 + kOStep, c1, cur);
+        uint64_t peers[kOU];
+        uint32_t lg[kOU];
+        bool in[kOU];
+#pragma unroll
+        for (uint32_t u = 0; u < kOU; u++) {
+            lg[u] = s.g[u] - g0;   // wraps below g0
+            in[u] = s.g[u] >= g0 && lg[u] < gn;
+            uint32_t mine;
+            peers[u] = match_count<4>(lg[u], __ballot(in[u]), mine);
+            if (lane < kOW) cnt[lane * kChunks + u * kOW + w] = (uint8_t)mine;   // owner = lane
+        }
+        lds_sync();
+        const OwnPlaces pl = own_places(cnt, bm, w);
+        if (pl.heavy) {
+            // per event, its map from its lanes' first: offset B, and slope
+            // (1 - alpha)^k; at: the place of its group's entry, k, the
+            // group's last lane, the group's lane before this one
+            double B[kOU];
+            uint32_t at[kOU];
+            lds_sync();   // (cnt has been read)
+#pragma unroll
+            for (uint32_t u = 0; u < kOU; u++) {
+                const bool use = in[u] && isfinite(s.x[u]) && s.x[u] > 0.0;
+                double A = 1.0;
+                B[u] = 0.0;
+                if (use) {
+                    const double ratio = (double)s.o[u] / s.x[u];
+                    A = a.oma;
+                    B[u] = a.alpha * ratio;
+                }
+                uint64_t same = match_bits<kKeyBits + 4>(lg[u], __ballot(in[u]));
+                if (!in[u]) same = 1ull << lane;
+                uint32_t rank, mine;
+                int prev0;
+                own_chain(same, A, B[u], rank, prev0);
+                const uint32_t k = (uint32_t)__popcll(__ballot(use) & same & lanemask_lt()) + (use ? 1u : 0u);
+                const uint32_t l = 63u - (uint32_t)__clzll((long long)same);
+                at[u] = (uint32_t)__popcll(match_count<4>(lg[u], __ballot(in[u] && l == lane), mine) & lanemask_lt()) |
+                        k << 13 | l << 20 | (uint32_t)prev0 << 26;
+                if (lane < kOW) cnt[lane * kChunks + u * kOW + w] = (uint8_t)mine;
+            }
+            lds_sync();
+            const OwnPlaces ph = own_places(cnt, bm, w);
+#pragma unroll
+            for (uint32_t u = 0; u < kOU; u++) {
+                at[u] += (uint32_t)__shfl((int)ph.at, (int)(4 * (lg[u] & (kOW - 1)) + u), 64);
+                if (in[u] && ((at[u] >> 20) & 63u) == lane) {   // the group's last lane
+                    stb[at[u] & 8191u] = B[u];
+                    stm[at[u] & 8191u] = ((at[u] >> 13) & 127u) | (lg[u] / kOW) << 12;
+                }
+            }
+            lds_sync();
+            for (uint32_t i = ph.lo; i < ph.hi; i += 64) {
+                const bool live = i + lane < ph.hi;
+                const uint32_t q = live ? i + lane : ph.lo;
+                const uint32_t m = stm[q], key = m >> 12, g = key * kOW + w, k = m & 127u;
+                double cA = pw64[k], cB = stb[q];
+                uint64_t cs = match_bits<kKeyBits>(key, __ballot(live));
+                if (!live) cs = 0;
+                uint32_t rank;
+                int prev0;
+                own_chain(cs, cA, cB, rank, prev0);
+                const double gb = sB[g];
+                const uint32_t gk = sK[g];
+                const double tt = cA * gb;
+                const double xb = tt + cB;
+                uint32_t ks = live ? k : 0u;   // the lanes' counts up to this one
+                int prev = prev0;
+                for (uint32_t st = 1; __ballot(rank >= st); st <<= 1) {
+                    const uint32_t pk = (uint32_t)__shfl((int)ks, prev, 64);
+                    const int pp = __shfl(prev, prev, 64);
+                    if (rank >= st) {
+                        ks += pk;
+                        prev = pp;
+                    }
+                }
+                const uint32_t xk = gk + ks;
+                const double qb = __shfl(xb, prev0, 64);
+                const uint32_t qk = (uint32_t)__shfl((int)xk, prev0, 64);
+                if (live) {   // the group's map before these lanes
+                    stb[q] = rank ? qb : gb;
+                    stm[q] = rank ? qk : gk;
+                }
+                if (live && (cs >> lane) >> 1 == 0) {
+                    sB[g] = xb;
+                    sK[g] = xk;
+                }
+            }
+            if constexpr (kEv) {
+                lds_sync();
+#pragma unroll
+                for (uint32_t u = 0; u < kOU; u++) {
+                    const int l = (int)((at[u] >> 20) & 63u), pv = (int)(at[u] >> 26);
+                    const bool last = in[u] && l == (int)lane;
+                    const double hb = last ? stb[at[u] & 8191u] : 0.0;
+                    const uint32_t hk = last ? stm[at[u] & 8191u] : 0u, k = (at[u] >> 13) & 127u;
+                    const double gb = __shfl(hb, l, 64);
+                    const uint32_t gk = (uint32_t)__shfl((int)hk, l, 64);
+                    const double tt = pw64[k] * gb;
+                    double eb = tt + B[u];
+                    uint32_t ek = gk + k;
+                    if (!a.incl) {
+                        const double qb = __shfl(eb, pv, 64);
+                        const uint32_t qk = (uint32_t)__shfl((int)ek, pv, 64);
+                        eb = pv != (int)lane ? qb : gb;
+                        ek = pv != (int)lane ? qk : gk;
+                    }
+                    if (in[u]) {
+                        a.xb[s0 + u * kOT + t] = eb;
+                        a.xk[s0 + u * kOT + t] = ek;
+                    }
+                }
+            }
+            continue;   // (the next step's first writes to LDS are to cnt, then a barrier)
+        }
+#pragma unroll
+        for (uint32_t u = 0; u < kOU; u++) {
+            const uint32_t p = (uint32_t)__shfl((int)pl.at, (int)(4 * (lg[u] & (kOW - 1)) + u), 64) +
+                               (uint32_t)__popcll(peers[u] & lanemask_lt());
+            if (in[u]) {
+                const bool use = isfinite(s.x[u]) && s.x[u] > 0.0;
+                double b = 0.0;
+                if (use) {
+                    const double ratio = (double)s.o[u] / s.x[u];
+                    b = a.alpha * ratio;
+                }
+                stb[p] = b;
+                stm[p] = (u * kOT + t) | (lg[u] / kOW) << 12 | (use ? 0x80000000u : 0u);
+            }
+        }
+        lds_sync();
+        for (uint32_t i = pl.lo; i < pl.hi; i += 64) {
+            const bool live = i + lane < pl.hi;
+            const uint32_t p = live ? i + lane : pl.lo;
+            const uint32_t m = stm[p], key = (m >> 12) & ((1u << kKeyBits) - 1u), g = key * kOW + w;
+            const bool use = live && (m >> 31);
+            double A = use ? a.oma : 1.0, B = stb[p];
+            uint64_t same = match_bits<kKeyBits>(key, __ballot(live));
+            if (!live) same = 0;
+            const uint64_t uses = __ballot(use) & same;
+            uint32_t rank;
+            int prev0;
+            own_chain(same, A, B, rank, prev0);
+            const double gb = sB[g];
+            const uint32_t gk = sK[g];
+            const double tt = A * gb;
+            const double xb = tt + B;
+            const uint32_t xk = gk + (uint32_t)__popcll(uses & lanemask_lt()) + (use ? 1u : 0u);
+            if (live && (same >> lane) >> 1 == 0) {   // the group's last lane
+                sB[g] = xb;
+                sK[g] = xk;
+            }
+            if constexpr (kEv) {
+                double eb = xb;
+                uint32_t ek = xk;
+                if (!a.incl) {   // up to the event before
+                    const double qb = __shfl(xb, prev0, 64);
+                    const uint32_t qk = (uint32_t)__shfl((int)xk, prev0, 64);
+                    eb = rank ? qb : gb;
+                    ek = rank ? qk : gk;
+                }
+                const uint32_t slot = m & (kOStep - 1u);
+                if (live) {
+                    if constexpr (kStage) {
+                        ob[slot] = eb;
+                        ok_[slot] = ek;
+                    } else {
+                        a.xb[s0 + slot] = eb;
+                        a.xk[s0 + slot] = ek;
+                    }
+                }
+            }
+        }
+        if constexpr (kStage) {
+            lds_sync();
+#pragma unroll
+            for (uint32_t u = 0; u < kOU; u++)
+                if (in[u]) {   // (an event of no group has no map)
+                    a.xb[s0 + u * kOT + t] = ob[u * kOT + t];
+                    a.xk[s0 + u * kOT + t] = ok_[u * kOT + t];
+                }
+        }
+    }
+    lds_sync();
+    for (uint32_t g = t; g < gn; g += kOT) {
+        a.aggK[(uint64_t)c * a.G + g0 + g] = sK[g];
+        a.aggB[(uint64_t)c * a.G + g0 + g] = sB[g];
+    }
+}
+
+// (1 - alpha)^k from the base-256 digits of k.
+__device__ __forceinline__ double slope(const double *pw, uint32_t k)
+{
+    double p = pw[k & 255u];
+    p *= pw[256u + ((k >> 8) & 255u)];
+    if (k >> 16) {
+        p *= pw[512u + ((k >> 16) & 255u)];
+        p *= pw[768u + (k >> 24)];
+    }
+    return p;
 }
 
 // Carries before every chunk, and the final factors: one block per 64
@@ -484,11 +775,8 @@ __global__ __launch_bounds__(64 * kScanW) void k_calc_scan(CalArgs a)
 {
     __shared__ double sA[kScanW][64], sB[kScanW][64];
     __shared__ uint32_t sU[kScanW][64];
-    // the powers of 1 - alpha for the per-event maps: digit d of place j
-    if (a.pw && blockIdx.x == 0) {
-        const uint32_t j = threadIdx.x >> 8, d = threadIdx.x & 255u;
-        a.pw[threadIdx.x] = pow(a.oma, (double)d * (double)(1u << (8 * j)));
-    }
+    __shared__ double pw[1024];
+    pw[threadIdx.x] = a.pw[threadIdx.x];
     const uint32_t w = threadIdx.x >> 6;
     const int lane = lane_id();
     const uint32_t g = blockIdx.x * 64u + (uint32_t)lane;
@@ -498,16 +786,20 @@ __global__ __launch_bounds__(64 * kScanW) void k_calc_scan(CalArgs a)
     if (per <= kScanRegs) {
         // the stretch's maps in registers: one round of loads, walked twice
         double A[kScanRegs], B[kScanRegs];
+        uint32_t K[kScanRegs];
         Map agg = {0u, 0u, 1.0, 0.0};
 #pragma unroll
         for (uint32_t r = 0; r < kScanRegs; r++) {
-            A[r] = -1.0;
+            K[r] = 0;
             B[r] = 0.0;
             if (in && cb + r < ce) {
-                A[r] = a.aggA[(uint64_t)(cb + r) * a.G + g];
+                K[r] = a.aggK[(uint64_t)(cb + r) * a.G + g];
                 B[r] = a.aggB[(uint64_t)(cb + r) * a.G + g];
             }
         }
+        __syncthreads();   // pw
+#pragma unroll
+        for (uint32_t r = 0; r < kScanRegs; r++) A[r] = K[r] ? slope(pw, K[r]) : -1.0;
 #pragma unroll
         for (uint32_t r = 0; r < kScanRegs; r++)
             if (A[r] >= 0.0) agg = combine(agg, Map{0u, 1u, A[r], B[r]});
@@ -543,18 +835,22 @@ __global__ __launch_bounds__(64 * kScanW) void k_calc_scan(CalArgs a)
     // four chunks' maps in flight at a time
     constexpr uint32_t kR = 4;
     Map agg = {0u, 0u, 1.0, 0.0};
+    __syncthreads();   // pw
     if (in)
         for (uint32_t c0 = cb; c0 < ce; c0 += kR) {
             double A[kR], B[kR];
+            uint32_t K[kR];
 #pragma unroll
             for (uint32_t r = 0; r < kR; r++) {
-                A[r] = -1.0;
+                K[r] = 0;
                 B[r] = 0.0;
                 if (c0 + r < ce) {
-                    A[r] = a.aggA[(uint64_t)(c0 + r) * a.G + g];
+                    K[r] = a.aggK[(uint64_t)(c0 + r) * a.G + g];
                     B[r] = a.aggB[(uint64_t)(c0 + r) * a.G + g];
                 }
             }
+#pragma unroll
+            for (uint32_t r = 0; r < kR; r++) A[r] = K[r] ? slope(pw, K[r]) : -1.0;
 #pragma unroll
             for (uint32_t r = 0; r < kR; r++)
                 if (A[r] >= 0.0) agg = combine(agg, Map{0u, 1u, A[r], B[r]});
@@ -576,15 +872,18 @@ __global__ __launch_bounds__(64 * kScanW) void k_calc_scan(CalArgs a)
     }
     for (uint32_t c0 = cb; c0 < ce; c0 += kR) {
         double A[kR], B[kR];
+        uint32_t K[kR];
 #pragma unroll
         for (uint32_t r = 0; r < kR; r++) {
-            A[r] = -1.0;
+            K[r] = 0;
             B[r] = 0.0;
             if (c0 + r < ce) {
-                A[r] = a.aggA[(uint64_t)(c0 + r) * a.G + g];
+                K[r] = a.aggK[(uint64_t)(c0 + r) * a.G + g];
                 B[r] = a.aggB[(uint64_t)(c0 + r) * a.G + g];
             }
         }
+#pragma unroll
+        for (uint32_t r = 0; r < kR; r++) A[r] = K[r] ? slope(pw, K[r]) : -1.0;
 #pragma unroll
         for (uint32_t r = 0; r < kR; r++) {
             if (c0 + r >= ce) break;
@@ -657,13 +956,7 @@ __global__ __launch_bounds__(256) void k_calc_ev(CalArgs a)
         if (g[r] < a.G) {
             double v = cv[r];
             if (k[r]) {
-                // (1 - alpha)^k from its base-256 digits
-                const uint32_t kk = k[r];
-                double p = pw[kk & 255u];
-                p *= pw[256u + ((kk >> 8) & 255u)];
-                p *= pw[512u + ((kk >> 16) & 255u)];
-                p *= pw[768u + (kk >> 24)];
-                const double tt = p * v;
+                const double tt = slope(pw, k[r]) * v;
                 v = tt + xb[r];
             }
             before = v;
@@ -734,12 +1027,10 @@ __global__ __launch_bounds__(kT) void k_calc_apply(CalArgs a)
     const uint64_t c1 = c0 + a.L < a.E ? c0 + a.L : a.E;
     const double nan = __builtin_nan("");
     double *tr = sh.b;
-    Raw<kE> next;
-    if (kPrefetch<kE> && c0 < c1) load_raw<kE>(a, (uint32_t)c0, (uint32_t)(c1 - c0 < kSub ? c1 - c0 : kSub), next);
     for (uint64_t s0 = c0; s0 < c1; s0 += kSub) {
         const uint32_t m = (uint32_t)(c1 - s0 < kSub ? c1 - s0 : kSub);
         Raw<kE> raw;
-        fetch<kE>(a, s0, c1, m, raw, next);
+        load_raw<kE>(a, (uint32_t)s0, m, raw);
         Sub<kE> sub;
         load_sort_scan<kE>(a, raw, m, sh, sub);
         if (quick && s0 == c0) {
@@ -1042,6 +1333,7 @@ __global__ __launch_bounds__(kT) void k_calc_one(CalArgs a)
 // would be too many or their table of maps too large for it.
 uint32_t one_e(uint64_t E, uint32_t G)
 {
+    if (G > kG) return 0;
     for (uint32_t e = 1; e <= 4; e *= 2) {
         const uint64_t C = cdiv(E ? E : 1, (uint64_t)kT * e);
         if (C <= kOneChunks && C * G <= kSmallTable) return e;
@@ -1051,7 +1343,7 @@ uint32_t one_e(uint64_t E, uint32_t G)
 
 uint32_t sub_per_chunk(uint64_t E, uint32_t G, uint32_t kSub)
 {
-    uint64_t cmax = kMaxTable / (G ? G : 1);
+    uint64_t cmax = (G > kG ? kMaxTableR : kMaxTable) / (G ? G : 1);
     cmax = cmax < kMaxChunks ? cmax : kMaxChunks;
     cmax = cmax ? cmax : 1;
     const uint64_t subs = cdiv(E, kSub);
@@ -1060,24 +1352,31 @@ uint32_t sub_per_chunk(uint64_t E, uint32_t G, uint32_t kSub)
 
 }  // namespace
 
-// Chunking for kE events per thread: events per chunk and chunks.
-static void chunking(uint64_t n, uint32_t G, uint32_t e, uint32_t &L, uint32_t &C)
+// Chunks of a multiple of sub events: events per chunk and chunks.
+static void chunking(uint64_t n, uint32_t G, uint32_t sub, uint32_t &L, uint32_t &C)
 {
-    const uint32_t sub = kT * e;
     L = sub * sub_per_chunk(n, G, sub);
     C = (uint32_t)cdiv(n ? n : 1, L);
+}
+
+// Whether chunks of 512 events make a small table.
+static bool small_table(uint64_t n, uint32_t G)
+{
+    uint32_t L, C;
+    chunking(n, G, kT, L, C);
+    return G <= kG && L == (uint32_t)kT && (uint64_t)C * G <= kSmallPair;
 }
 
 size_t calc_ws_bytes(uint64_t n, uint32_t G)
 {
     // the larger of the two chunkings' tables
     uint32_t L1, C1, L4, C4;
-    chunking(n, G, 1, L1, C1);
-    chunking(n, G, kBigE, L4, C4);
+    chunking(n, G, kT, L1, C1);
+    chunking(n, G, kOStep, L4, C4);
     const uint64_t C = C1 > C4 ? C1 : C4;
     const size_t base = 3 * align_up(C * G * 8, 256) + align_up((uint64_t)G * 8, 256);
     // the large tables' per-event maps and power tables (k_calc_ev)
-    const bool large = one_e(n, G) == 0 && (uint64_t)C1 * G > kSmallTable;
+    const bool large = one_e(n, G) == 0 && !small_table(n, G);
     return large ? base + align_up(1024 * 8, 256) + align_up(n * 8, 256) + align_up(n * 4, 256) : base;
 }
 
@@ -1086,7 +1385,7 @@ hipError_t calc_launch(const uint32_t *group, const double *est, const uint32_t 
                        void *ws, hipStream_t s, WaitCfg wait)
 {
     if (n == 0) return hipSuccess;
-    if (G == 0 || G > kG) return hipErrorInvalidValue;
+    if (G == 0 || G > kCalGroupsChunked) return hipErrorInvalidValue;
     CalArgs a;
     a.group = group;
     a.est = est;
@@ -1097,23 +1396,24 @@ hipError_t calc_launch(const uint32_t *group, const double *est, const uint32_t 
     a.oma = 1.0 - alpha;
     // few chunks of one sub-tile each: one launch (after the unset words);
     // else sub-tiles of 512 events when the table of chunk maps stays small
-    // (the carries are then formed in k_calc_apply), else of 4096
+    // (the carries are then formed in k_calc_apply), else steps of 4096
     const uint32_t one = one_e(n, G);
     if (one) {
         a.L = kT * one;
         a.C = (uint32_t)cdiv(n, a.L);
         a.small = 1;
     } else {
-        chunking(n, G, 1, a.L, a.C);
-        a.small = (uint64_t)a.C * G <= kSmallTable ? 1u : 0u;
-        if (!a.small) chunking(n, G, kBigE, a.L, a.C);
+        a.small = small_table(n, G) ? 1u : 0u;
+        chunking(n, G, a.small ? kT : kOStep, a.L, a.C);
     }
+    a.R = G > kG ? (uint32_t)cdiv(G, kRangeGroups) : 1u;
     a.passes = G < 256 ? 1u : 2u;   // keys 0..G fit in 8 or 16 bits
     a.keybits = 1;
     while ((1u << a.keybits) <= G) a.keybits++;
     uint8_t *p = static_cast<uint8_t *>(ws);
     const uint64_t tb = align_up((uint64_t)a.C * G * 8, 256);
     a.aggA = reinterpret_cast<double *>(p);
+    a.aggK = reinterpret_cast<uint32_t *>(p);
     a.aggB = reinterpret_cast<double *>(p + tb);
     a.carry = reinterpret_cast<double *>(p + 2 * tb);
     a.s0 = reinterpret_cast<double *>(p + 3 * tb);
@@ -1121,8 +1421,8 @@ hipError_t calc_launch(const uint32_t *group, const double *est, const uint32_t 
     // calc_ws_bytes reserves
     {
         uint32_t L1, C1, L4, C4;
-        chunking(n, G, 1, L1, C1);
-        chunking(n, G, kBigE, L4, C4);
+        chunking(n, G, kT, L1, C1);
+        chunking(n, G, kOStep, L4, C4);
         const uint64_t Cm = C1 > C4 ? C1 : C4;
         uint8_t *q = p + 3 * align_up(Cm * G * 8, 256) + align_up((uint64_t)G * 8, 256);
         a.pw = reinterpret_cast<double *>(q);
@@ -1149,17 +1449,21 @@ hipError_t calc_launch(const uint32_t *group, const double *est, const uint32_t 
         else if (one == 2) hipLaunchKernelGGL(k_calc_one<2>, dim3(a.C), dim3(kT), 0, s, a);
         else hipLaunchKernelGGL(k_calc_one<4>, dim3(a.C), dim3(kT), 0, s, a);
     } else if (a.small) {
-        hipLaunchKernelGGL((k_calc_agg<1, false>), dim3(a.C), dim3(kT), 0, s, a);
+        hipLaunchKernelGGL(k_calc_agg<1>, dim3(a.C), dim3(kT), 0, s, a);
         hipLaunchKernelGGL(k_calc_apply<1>, dim3(a.C), dim3(kT), 0, s, a);
-    } else if (!trace && !trace_before) {
-        // the final factors alone
-        a.pw = nullptr;
-        hipLaunchKernelGGL((k_calc_agg<kBigE, false>), dim3(a.C), dim3(kT), 0, s, a);
-        hipLaunchKernelGGL(k_calc_scan, dim3((G + 63) / 64), dim3(64 * kScanW), 0, s, a);
     } else {
-        hipLaunchKernelGGL((k_calc_agg<kBigE, true>), dim3(a.C), dim3(kT), 0, s, a);
+        const bool ev = trace || trace_before;   // else the final factors alone
+        const dim3 grid(G > kG ? (uint32_t)align_up(a.C, 8) * a.R : a.C);
+        if (G > kG && ev)
+            hipLaunchKernelGGL((k_calc_own<kRangeGroups, true>), grid, dim3(kOT), 0, s, a);
+        else if (G > kG)
+            hipLaunchKernelGGL((k_calc_own<kRangeGroups, false>), grid, dim3(kOT), 0, s, a);
+        else if (ev)
+            hipLaunchKernelGGL((k_calc_own<kG, true>), grid, dim3(kOT), 0, s, a);
+        else
+            hipLaunchKernelGGL((k_calc_own<kG, false>), grid, dim3(kOT), 0, s, a);
         hipLaunchKernelGGL(k_calc_scan, dim3((G + 63) / 64), dim3(64 * kScanW), 0, s, a);
-        hipLaunchKernelGGL(k_calc_ev, dim3((uint32_t)cdiv(n, 1024)), dim3(256), 0, s, a);
+        if (ev) hipLaunchKernelGGL(k_calc_ev, dim3((uint32_t)cdiv(n, 1024)), dim3(256), 0, s, a);
     }
     return hipGetLastError();
 }

@@ -170,8 +170,10 @@ size_t am_partition_ws_bytes(uint64_t n);
 hipError_t am_partition(const SortInput &in, uint32_t *run_pos, uint32_t *run_start, void *ws, hipStream_t s);
 
 // ---- stage 2: calibrate -------------------------------------------------------
-// Up to kCalGroupsLds groups: chunked scan without a global partition.
+// Up to kCalGroupsChunked groups: chunked scan without a global partition
+// (up to kCalGroupsLds one block holds every group's map in LDS).
 constexpr uint32_t kCalGroupsLds = 4096;
+constexpr uint32_t kCalGroupsChunked = 65536;
 size_t calc_ws_bytes(uint64_t n, uint32_t n_groups);
 // wait.status (may be NULL): zeroed by the first kernel when wait.clear, set
 // when a chunk's wait for the maps of the chunks before it runs out.

@@ -189,3 +189,37 @@ def test_one_workspace_across_paths(ds, oracle):
         assert ok, "call %d (%d x %d): trace worst relative difference %.3g" % (k, E, G, worst)
         ok, worst = rel_close(host(st), w_st, RTOL)
         assert ok, "call %d: state worst relative difference %.3g" % (k, worst)
+
+
+# one block for all groups (up to 4096), ranges of 8192 groups above; a chunk
+# of one step and several; 65536 groups the last before the partition
+@pytest.mark.parametrize("E,G", [(30001, 4096), (70000, 4097), (140003, 8192), (140003, 8193),
+                                 (700001, 20011), (4099, 65536), (1200007, 5000), (1310720, 300)])
+@pytest.mark.parametrize("skew", [0.0, 0.3, 1.0])
+def test_large_tables(ds, oracle, E, G, skew):
+    # events spread over the groups, one group holding a share of them (its
+    # owner's events are then combined 64 at a time first) or all of them;
+    # events outside the groups get NaN and touch nothing
+    rng = np.random.default_rng(E + G + int(10 * skew))
+    g = rng.integers(0, G, E).astype(np.uint32)
+    g[rng.random(E) < skew] = G - 1
+    est = rng.uniform(1, 500, E)
+    est[rng.random(E) < 0.05] = np.inf
+    obs = rng.integers(0, 1000, E).astype(np.uint32)
+    st0 = rng.uniform(0.5, 1.5, G)
+    kept = np.arange(E) % 11 != 5
+    w_st, w_tr, w_before = oracle.calibrate(g[kept], est[kept], obs[kept], 0.1, st0, with_before=True)
+    gx = np.where(kept, g, np.uint32(G + 3)).astype(np.uint32)
+    for outs in ("state", "trace", "both"):
+        st = dev(st0.copy())
+        res = ds.calibrate(dev(gx), dev(est), dev(obs), 0.1, st, trace=outs != "state",
+                           trace_before=outs == "both")
+        ok, worst = rel_close(host(st), w_st, RTOL)
+        assert ok, "%s: state worst relative difference %.3g" % (outs, worst)
+        for got, want in ((res[1], w_tr), (res[2] if outs == "both" else None, w_before)):
+            if got is None:
+                continue
+            got = host(got)
+            assert np.isnan(got[~kept]).all()
+            ok, worst = rel_close(got[kept], want, RTOL)
+            assert ok, "%s: worst relative difference %.3g" % (outs, worst)
