@@ -123,12 +123,14 @@ struct LsCopies {
     uint8_t *tier;
 };
 // A batch's Class partition can also lay out the priority classes' runs for
-// the Aging merge (am_merge_launch): each request's aged-score bits and FIFO
+// the Aging order (am_rank_launch): each request's aged-score bits and FIFO
 // position at its Priority place, and the classes' starts (17 words).
 struct LsRuns {
     uint64_t *rk;
     uint32_t *rp;
     uint32_t *cstart;
+    uint64_t *hk;      // the runs' steps
+    uint32_t *hp;
 };
 // SJF's splitter sample drawn beside the FIFO sort (draw: that call draws
 // it): its keys are the budgets of the sampled requests, with the request
@@ -155,17 +157,23 @@ hipError_t lsort_launch(const SortInput &in, const SortJob *jobs, uint32_t njobs
 // n_classes = the number of distinct priorities). wait_status (may be NULL):
 // zeroed by the first kernel (no waits here).
 constexpr uint32_t kAmMaxN = 1u << 24;
+// Every kAmStep-th entry of each run apart (key bits, FIFO position), so that
+// a place in a run is found in a few pages: run c, whose first entry is at
+// `start`, has its steps from am_step_at(start, c) on.
+constexpr uint32_t kAmStep = 64;
+__host__ __device__ constexpr uint32_t am_step_at(uint32_t start, uint32_t c) { return start / kAmStep + c; }
+constexpr uint64_t am_steps(uint64_t n) { return n / kAmStep + 17; }
+constexpr size_t am_steps_bytes(uint64_t n) { return (am_steps(n) * 12 + 511) / 256 * 256; }
+inline uint32_t *am_steps_pos(uint64_t *hk, uint64_t n) { return reinterpret_cast<uint32_t *>(hk + am_steps(n)); }
 size_t am_ws_bytes(uint64_t n);
 hipError_t am_launch(const SortInput &in, uint32_t n_classes, uint32_t *perm, double *key_out, void *ws,
                      hipStream_t s, uint32_t *wait_status);
 // The stable partition of the FIFO sequence by in.cls[tier] alone (16
 // classes): run_pos (n) receives the FIFO positions class by class, each
 // class in FIFO order, run_start (17) each class's first entry and n.
-// The merge rounds alone, over runs formed elsewhere: rk[0] / rp[0] hold
-// the K runs (aged-score bits, FIFO position) one after another from
-// cstart[0], cstart[K..16] = n; rk[1] / rp[1] are scratch of the same size.
-hipError_t am_merge_launch(const SortInput &in, uint32_t n_classes, uint32_t *cstart, uint64_t *const rk[2],
-                           uint32_t *const rp[2], uint32_t *perm, double *key_out, hipStream_t s);
+// The places alone, over runs formed elsewhere (runs.cstart[K..16] = n).
+hipError_t am_rank_launch(const SortInput &in, uint32_t n_classes, const LsRuns &runs, uint32_t *perm,
+                          double *key_out, hipStream_t s);
 size_t am_partition_ws_bytes(uint64_t n);
 hipError_t am_partition(const SortInput &in, uint32_t *run_pos, uint32_t *run_start, void *ws, hipStream_t s);
 

@@ -582,8 +582,14 @@ __device__ __forceinline__ void ls_place_part(const LsArgs &a, const LsRow &R, u
                 const uint32_t j = base + idx;
                 const uint32_t t0 = a.pf.tier ? a.pf.tier[j] : a.in.tier[v[r]];
                 const double x = a.pf.arr ? a.pf.arr[j] : a.in.arrival[v[r]];
-                a.runs.rk[pos] = ordered_bits(ls_aged(a.in, x, t0 < kQ ? t0 : kQ - 1u));
+                const uint64_t e = ordered_bits(ls_aged(a.in, x, t0 < kQ ? t0 : kQ - 1u));
+                a.runs.rk[pos] = e;
                 a.runs.rp[pos] = j;
+                if (kd % kAmStep == 0) {
+                    const uint32_t h = am_step_at(R.start[q], q) + kd / kAmStep;
+                    a.runs.hk[h] = e;
+                    a.runs.hp[h] = j;
+                }
             }
             continue;
         }

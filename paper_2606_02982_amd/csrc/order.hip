@@ -74,12 +74,15 @@ size_t order_ws_bytes(uint64_t n, uint32_t npolicies)
     const size_t sample = ssort_ws_bytes(n < kSsMaxN ? n : kSsMaxN, nss);
     const size_t rs = sort_ws_bytes(n, nrs);
     // (FIFO-ordered copies of arrival, budget and tier for the batch over the
-    // FIFO sequence, and the Aging runs with their merge scratch)
+    // FIFO sequence, and the Aging runs)
     const size_t lb = lsort_ws_bytes(n, 1, 2);
-    const size_t ls = lb ? 2 * align_up(n * 8, 256) + align_up(n, 256) + 2 * align_up(n * 8, 256) +
-                               2 * align_up(n * 4, 256) + align_up(17 * 4, 256) + lsort_sample_bytes(n) + lb
+    const size_t ls = lb ? 2 * align_up(n * 8, 256) + align_up(n, 256) + align_up(n * 8, 256) +
+                               align_up(n * 4, 256) + align_up(17 * 4, 256) + am_steps_bytes(n) +
+                               lsort_sample_bytes(n) + lb
                          : 0;
-    const size_t radix = align_up(n * 4, 256) + (ls > rs ? ls : rs);
+    // (the Aging runs take the radix sorts' place after them)
+    const size_t am = n > kLsMaxN && n <= kAmMaxN ? am_ws_bytes(n) : 0;
+    const size_t radix = align_up(n * 4, 256) + std::max(std::max(ls, rs), am);
     // the larger of the two keeps the size non-decreasing in n
     return n <= kSsMaxN ? sample : (radix > sample ? radix : sample);
 }
@@ -169,18 +172,16 @@ hipError_t order_launch(const OrderArgs &a, void *ws, uint32_t *flag, hipStream_
         q += align_up((uint64_t)n * 8, 256);
         cp.tier = q;
         q += align_up(n, 256);
-        uint64_t *rk[2];
-        uint32_t *rp[2];
-        for (int e = 0; e < 2; e++) {
-            rk[e] = reinterpret_cast<uint64_t *>(q);
-            q += align_up((uint64_t)n * 8, 256);
-        }
-        for (int e = 0; e < 2; e++) {
-            rp[e] = reinterpret_cast<uint32_t *>(q);
-            q += align_up((uint64_t)n * 4, 256);
-        }
-        LsRuns runs = {rk[0], rp[0], reinterpret_cast<uint32_t *>(q)};
+        LsRuns runs;
+        runs.rk = reinterpret_cast<uint64_t *>(q);
+        q += align_up((uint64_t)n * 8, 256);
+        runs.rp = reinterpret_cast<uint32_t *>(q);
+        q += align_up((uint64_t)n * 4, 256);
+        runs.cstart = reinterpret_cast<uint32_t *>(q);
         q += align_up(17 * 4, 256);
+        runs.hk = reinterpret_cast<uint64_t *>(q);
+        runs.hp = am_steps_pos(runs.hk, n);
+        q += am_steps_bytes(n);
         LsSample sjf = lsort_sample_at(n, q);
         q += lsort_sample_bytes(n);
         void *batch_ws = q;
@@ -200,7 +201,7 @@ hipError_t order_launch(const OrderArgs &a, void *ws, uint32_t *flag, hipStream_
         sjf.draw = false;
         in.fifo = fifo;
         // SJF sorts; Priority partitions (and lays out the priority classes'
-        // runs, which the Aging merge then combines); Weighted partitions
+        // runs, from which each request's Aging place follows); Weighted partitions
         const bool prio = a.mask & (1u << 1), aging = a.mask & (1u << 4);
         SortJob jobs[3];
         uint32_t nj = 0;
@@ -212,13 +213,13 @@ hipError_t order_launch(const OrderArgs &a, void *ws, uint32_t *flag, hipStream_
         hipError_t err = lsort_launch(in, jobs, nj, batch_ws, s, a.fifo_in ? nullptr : &cp, nullptr,
                                       aging ? &runs : nullptr, sjf_drawn ? &sjf : nullptr);
         if (err != hipSuccess || !aging) return err;
-        return am_merge_launch(in, n_classes, runs.cstart, rk, rp, a.perm[4], a.key[4], s);
+        return am_rank_launch(in, n_classes, runs, a.perm[4], a.key[4], s);
     }
 
     // the policy sorts over the FIFO sequence; Aging as the merge of the
-    // priority classes' runs of that sequence (agmerge.hip) where its
-    // buffers fit the sort workspace, else as one more radix sort
-    const bool aging_merge = (a.mask & (1u << 4)) && n <= kAmMaxN && am_ws_bytes(n) <= sort_ws_bytes(n, 1);
+    // priority classes' runs of that sequence (agmerge.hip), in the sort
+    // workspace, or above kAmMaxN as one more radix sort
+    const bool aging_merge = (a.mask & (1u << 4)) && n <= kAmMaxN;
     SortJob jobs[kMaxSorts];
     uint32_t nj = 0;
     if (a.mask & (1u << 1)) jobs[nj++] = {SortKind::Class, 8, a.key[1], a.perm[1]};
@@ -241,7 +242,7 @@ hipError_t order_launch(const OrderArgs &a, void *ws, uint32_t *flag, hipStream_
         if (err != hipSuccess) return err;
         in.wait.clear = false;
     }
-    // (after the sorts on the stream: the merge reuses their workspace)
+    // (after the sorts on the stream: the runs reuse their workspace)
     if (aging_merge)
         return am_launch(in, n_classes, a.perm[4], a.key[4], sort_ws, s,
                          in.wait.clear ? in.wait.status : nullptr);

@@ -109,3 +109,22 @@ def test_one_bucket_takes_almost_all(ds, oracle, target, spread):
         bud[pos] = np.arange(S, dtype=np.float64)
     for pol in POLICIES:
         check(ds, oracle, pol, tier, arr, bud, t_now=float(np.max(arr)), aging_rate=0.01)
+
+
+@pytest.mark.parametrize("n", [300007, 1048577])
+@pytest.mark.parametrize("shares", ["even16", "tiny", "one", "gap"])
+def test_aging_places(ds, oracle, n, shares):
+    # each request's place from its run and the entries below it in the other
+    # runs: many classes, runs of a few entries beside runs of all the others
+    # (stretches searched in memory), empty classes, and a floor that cuts a
+    # tile (its clamped entries tie with their neighbours in time, the others
+    # follow every clamped one, far away)
+    rng = np.random.default_rng(n + len(shares))
+    tier, arr, bud = _batch(n + 7, n)
+    k = 16 if shares == "even16" else 4
+    p = {"even16": np.full(16, 1 / 16), "tiny": np.array([0.9, 0.0999, 0.0001, 0.0]),
+         "one": np.array([0.0, 0.0, 1.0, 0.0]), "gap": np.array([0.4, 0.3, 0.2, 0.1])}[shares]
+    tier = rng.choice(k, n, p=p).astype(np.uint8)
+    arr = rng.uniform(0.0, 1000.0, n)
+    check(ds, oracle, ds.AGING, tier, arr, bud, n_tiers=k, weights=(1,) * k,
+          tier_priority=tuple(float(q) for q in range(k)), t_now=1000.0, aging_rate=0.004)
