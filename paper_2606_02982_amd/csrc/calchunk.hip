@@ -1367,14 +1367,17 @@ static bool small_table(uint64_t n, uint32_t G)
     return G <= kG && L == (uint32_t)kT && (uint64_t)C * G <= kSmallPair;
 }
 
+// Non-decreasing in n and in G: the tables of the most chunks that any call
+// of at most n events and G groups makes.
 size_t calc_ws_bytes(uint64_t n, uint32_t G)
 {
-    // the larger of the two chunkings' tables
-    uint32_t L1, C1, L4, C4;
-    chunking(n, G, kT, L1, C1);
-    chunking(n, G, kOStep, L4, C4);
-    const uint64_t C = C1 > C4 ? C1 : C4;
-    const size_t base = 3 * align_up(C * G * 8, 256) + align_up((uint64_t)G * 8, 256);
+    auto table = [n](uint64_t sub, uint64_t cap, uint64_t g) {
+        const uint64_t chunks = cdiv(n ? n : 1, sub), most = (chunks < kMaxChunks ? chunks : kMaxChunks) * g;
+        return most < cap ? most : cap;
+    };
+    uint64_t entries = table(kT, kMaxTable, G < kG ? G : kG);
+    if (G > kG && entries < table(kOStep, kMaxTableR, G)) entries = table(kOStep, kMaxTableR, G);
+    const size_t base = 3 * align_up(entries * 8, 256) + align_up((uint64_t)G * 8, 256);
     // the large tables' per-event maps and power tables (k_calc_ev)
     const bool large = one_e(n, G) == 0 && !small_table(n, G);
     return large ? base + align_up(1024 * 8, 256) + align_up(n * 8, 256) + align_up(n * 4, 256) : base;
@@ -1417,14 +1420,9 @@ hipError_t calc_launch(const uint32_t *group, const double *est, const uint32_t 
     a.aggB = reinterpret_cast<double *>(p + tb);
     a.carry = reinterpret_cast<double *>(p + 2 * tb);
     a.s0 = reinterpret_cast<double *>(p + 3 * tb);
-    // per-event maps (large tables): after the other arrays, at the offsets
-    // calc_ws_bytes reserves
+    // per-event maps (large tables): after the other arrays
     {
-        uint32_t L1, C1, L4, C4;
-        chunking(n, G, kT, L1, C1);
-        chunking(n, G, kOStep, L4, C4);
-        const uint64_t Cm = C1 > C4 ? C1 : C4;
-        uint8_t *q = p + 3 * align_up(Cm * G * 8, 256) + align_up((uint64_t)G * 8, 256);
+        uint8_t *q = p + 3 * tb + align_up((uint64_t)G * 8, 256);
         a.pw = reinterpret_cast<double *>(q);
         q += align_up(1024 * 8, 256);
         a.xb = reinterpret_cast<double *>(q);

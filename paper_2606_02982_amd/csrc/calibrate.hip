@@ -18,6 +18,8 @@
 //      the factor before and after each event (the traces) and, at a
 //      group's last event, the group's final factor.
 // Every combine runs in a fixed order, so results are run-to-run identical.
+#include <algorithm>
+
 #include "common.h"
 #include "kernels.h"
 
@@ -266,7 +268,9 @@ size_t cal_ws_bytes(uint64_t n, uint32_t n_groups)
 {
     if (n_groups <= kCalGroupsLds) return calc_ws_bytes(n, n_groups);
     uint64_t T = cdiv(n, kTile);
-    const size_t part = sort_ws_bytes(n, 1) + align_up(n * 4, 256) +
+    // (the sort's tiles grow above kSsMaxN keys: its size must not fall there)
+    const size_t sort = n > kSsMaxN ? std::max(sort_ws_bytes(n, 1), sort_ws_bytes(kSsMaxN, 1)) : sort_ws_bytes(n, 1);
+    const size_t part = sort + align_up(n * 4, 256) +
                         align_up((uint64_t)n_groups * 8, 256) + 2 * align_up(T * sizeof(Map), 256);
     const size_t chunked = n_groups <= kCalGroupsChunked ? calc_ws_bytes(n, n_groups) : 0;
     return part > chunked ? part : chunked;
