@@ -116,7 +116,7 @@ hipError_t ssort_launch(const SortInput &in, const SortJob *jobs, uint32_t nsort
 // The FIFO sort can write the inputs in FIFO order (LsCopies; bud may be
 // NULL), which a batch over that sequence then reads instead of gathering
 // through in.fifo.
-constexpr uint32_t kLsMaxN = 1u << 20;
+constexpr uint32_t kLsMaxN = 1u << 22;
 struct LsCopies {
     double *arr;
     double *bud;
@@ -139,8 +139,9 @@ struct LsRuns {
 // here. Any sorted splitters give exact results: the bucket sizes come from
 // the counts.
 struct LsSample {
-    uint64_t *raw_k;
-    uint32_t *rpart;
+    uint64_t *srt_k;
+    uint32_t *srt_i;
+    uint16_t *rpart;
     uint64_t *smp_k;
     uint32_t *smp_j;
     bool draw;

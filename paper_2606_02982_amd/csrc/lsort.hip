@@ -1,4 +1,4 @@
-// Dispatch orders of kSsMaxN < n <= kLsMaxN requests (Sec. "Scheduling
+// Dispatch orders of kSsMaxN < n <= kLsMaxN (2^22) requests (Sec. "Scheduling
 // Engine"): one sample sort per policy over a sequence of positions j, by
 // the pair (key(j), j), which is the stable order by key. FIFO sorts the
 // requests by arrival; SJF (and Aging) sort the FIFO sequence by budget (or
@@ -7,15 +7,14 @@
 //
 //   k_ls_gather   the keys of S = 8 per bucket positions, one in each of S
 //                 equal strata of [0, n) (so the sample is in sequence order),
-//                 and each wave's 64 of them sorted (a bitonic network).
-//   k_ls_sample   each sample's rank by counting the samples below it, the
-//                 count of each group of 64 samples spread over four blocks
-//                 (each staging a quarter of the sorted 64-sample blocks in
-//                 LDS, one binary search per block).
-//   k_ls_place    each sample at its rank (the four counts added): the
+//                 sorted in blocks of 1024 (a bitonic network per wave, then
+//                 four merges in LDS).
+//   k_ls_sample   each sample's rank in each sorted block, one binary search
+//                 in LDS.
+//   k_ls_place    each sample at its rank (its ranks in the blocks added): the
 //                 sorted sample, of which every (S/B)-th pair is one of the
 //                 B - 1 splitters.
-//   k_ls_count    per tile of 4096 positions: each position's bucket (a
+//   k_ls_count    per tile of 4096 or 8192 positions: each position's bucket (a
 //                 descent of the splitters' search tree), stored, and the
 //                 tile's count of each bucket; the per-request key output.
 //   k_ls_scan     per bucket: exclusive prefix of its counts over the tiles
@@ -27,12 +26,18 @@
 //                 pair order is total (j is unique), so the bucket sort
 //                 alone fixes the result.
 //   k_ls_bucket   one block per bucket: a bucket of at most kLsCap pairs is
-//                 ranked in LDS (bins over its key range, counting inside a
-//                 bin; stable byte passes over j and then the key when a bin
+//                 ranked in LDS (bins between its splitters' keys, or over its
+//                 key range where those crowd, counting inside a bin; stable byte passes over j and then the key when a bin
 //                 is crowded); a larger one (only for inputs arranged against
 //                 the sampling) is sorted by the same byte passes through
 //                 global memory, chunk by chunk. The values go to their
 //                 places in the output.
+// What bounds it: latency inside the blocks and, above 2^20, the scatter's short
+// runs (two pairs per tile and bucket). Five orders, before and after the
+// 1024-thread tiles, the sorted sample blocks and the bins between splitters:
+// 1,048,576 requests 214 and 188 us; 4,194,303 (radix sorts before) 1,077 and
+// 583 us, of which at 4,194,303 two count launches 85, two scatters 213, two
+// bucket launches 174, the Aging places 61.
 // No atomics on global memory and no wait on another block; the bucket
 // sizes are exact, so nothing overflows.
 #include <string.h>
@@ -47,17 +52,24 @@ namespace ds {
 namespace {
 
 constexpr uint32_t kLsAvg = 1024;                  // target pairs per bucket
-constexpr uint32_t kLsMaxB = kLsMaxN / kLsAvg;     // 1024 buckets at most
+constexpr uint32_t kLsMaxB = kLsMaxN / kLsAvg;     // 4096 buckets at most
 constexpr uint32_t kLsOver = 8;                    // samples per bucket
-constexpr uint32_t kLsMaxS = kLsMaxB * kLsOver;    // 8192
+constexpr uint32_t kSB = 1024;                     // samples per sorted block
+constexpr uint32_t kLsMaxS = kLsMaxB * kLsOver;    // 32768
 constexpr uint32_t kLsCap = 4096;                  // buckets ranked in LDS up to this size
-constexpr uint32_t kJBits = 20;                    // positions j < 2^20
-constexpr uint32_t kJMask = (1u << kJBits) - 1u;
-static_assert(kLsMaxN <= (1u << kJBits), "a position fits its field");
-static_assert(kLsMaxB <= (1u << (32 - kJBits)), "a bucket index fits above the position");
+static_assert(kLsMaxB <= 65536, "a bucket index is stored in 16 bits");
 
-constexpr int kTT = 512, kTR = 8;                  // count and scatter tiles
-constexpr uint32_t kTile = kTT * kTR;              // 4096 positions
+// Count and scatter tiles, by the buckets that a row can have (template
+// parameter kMB): 1024 threads; up to 1024 buckets 4 positions per thread,
+// above 8 (the tables of counts and of a tile's buckets stay in proportion,
+// and 144 KB of LDS hold one scatter tile). 512 threads with 8 positions made
+// the five orders of 1,048,576 requests 13 us slower (217 and 204 us).
+constexpr int kTT = 1024;
+constexpr uint32_t kSmallB = 1024;
+template <uint32_t kMB> constexpr int kTR = kMB > kSmallB ? 8 : 4;
+template <uint32_t kMB> constexpr uint32_t kTile = kTT * kTR<kMB>;
+constexpr uint32_t kIBits = 13;                    // a position's place in its tile
+static_assert(kTile<kLsMaxB> <= (1u << kIBits) && kLsMaxB <= (1u << 12), "a place, a bucket and a tier in 32 bits");
 constexpr int kBT = 512, kBW = kBT / 64, kBR = kLsCap / kBT;   // k_ls_bucket
 constexpr uint32_t kBinBits = 11, kBins = 1u << kBinBits;
 constexpr uint32_t kBinMax = 256;                  // larger bins: byte passes instead
@@ -80,8 +92,9 @@ struct LsRow {
     uint16_t *bid;         // [n] bucket of each position (sorts)
     uint32_t by_req;       // the sample's keys are the budgets of the sampled requests
                            // (request index standing in for the FIFO position)
-    uint64_t *raw_k;       // [S] the sample's keys in sample order
-    uint32_t *rpart;       // [kSmP][S] each part's count of samples below each sample
+    uint64_t *srt_k;       // [S] the sample in sorted blocks of kSB: keys
+    uint32_t *srt_i;       // and sample indices
+    uint16_t *rpart;       // [S / kSB][S] each one's rank in each block
     uint64_t *smp_k;       // [S] the sample in order
     uint32_t *smp_j;
     uint64_t *rk[2];       // [n] bucket regions, and the large-bucket path's second buffer
@@ -243,19 +256,18 @@ __device__ __forceinline__ uint64_t shfl_xor_u64(uint64_t x, int m)
     return ((uint64_t)hi << 32) | lo;
 }
 
-// The sample's keys in sample order (raw_k), and each wave's 64 samples
-// sorted by (key, sample index) with a bitonic network across the lanes,
-// stored as sorted blocks of 64 in smp_k / smp_j for the ranking (the
-// placement overwrites them with the sorted sample).
-__global__ __launch_bounds__(256) void k_ls_gather(LsArgs a)
+// The sample in sorted blocks of kSB by (key, sample index): each wave's 64
+// with a bitonic network across the lanes, then pairs of sorted stretches
+// merged in LDS (each pair's place: its own and its rank in the other).
+__global__ __launch_bounds__(kSB) void k_ls_gather(LsArgs a)
 {
+    __shared__ uint64_t mk[2][kSB];
+    __shared__ uint16_t mi[2][kSB];
     const LsRow &R = a.r[a.srow[blockIdx.y]];
-    const uint32_t s = blockIdx.x * 256u + threadIdx.x;
-    if (blockIdx.x * 256u + (threadIdx.x & ~63u) >= R.S) return;   // a whole wave past S (a multiple of 64)
-    const uint32_t j = ls_pos(s, a.n, R.S);
+    if (blockIdx.x * kSB >= R.S) return;
+    const uint32_t t = threadIdx.x, s0 = blockIdx.x * kSB, j = ls_pos(s0 + t, a.n, R.S);
     uint64_t k = R.by_req ? ordered_bits(a.in.budget[j]) : ls_key(a, R, j);
-    R.raw_k[s] = k;
-    uint32_t i = s;
+    uint32_t i = t;   // the sample index in the block
     const uint32_t lane = (uint32_t)lane_id();
     for (uint32_t kk = 2; kk <= 64; kk <<= 1)
         for (uint32_t jj = kk >> 1; jj > 0; jj >>= 1) {
@@ -268,77 +280,86 @@ __global__ __launch_bounds__(256) void k_ls_gather(LsArgs a)
                 i = pi;
             }
         }
-    R.smp_k[s] = k;
-    R.smp_j[s] = i;
-}
-
-constexpr int kSmT = 1024, kSmW = kSmT / 64;
-
-// Ranks by counting, spread over kSmP blocks per group of 64 samples: block
-// (g, p) stages part p of the sorted 64-sample blocks in LDS and counts, for
-// each of the group's samples (one per lane), the part's samples below it
-// by (key, sample index): one binary search per sorted block (each wave
-// over a share of the part's blocks, the waves' counts added), stored as
-// that part's count. Sample indices increase with the positions, so the
-// order is the pair order by (key, position).
-constexpr uint32_t kSmP = 4;
-
-__global__ __launch_bounds__(kSmT) void k_ls_sample(LsArgs a)
-{
-    __shared__ uint64_t sk[kLsMaxS / kSmP];
-    __shared__ uint16_t si[kLsMaxS / kSmP];
-    __shared__ uint32_t part[kSmW][64];
-    const LsRow &R = a.r[a.srow[blockIdx.y]];
-    const uint32_t g = blockIdx.x / kSmP, pq = blockIdx.x % kSmP;
-    if (g * 64u >= R.S) return;   // a row with a smaller sample than the grid is wide
-    const uint32_t t = threadIdx.x, lane = (uint32_t)lane_id(), w = t >> 6, S = R.S;
-    const uint32_t nb = S / 64u, b0 = pq * nb / kSmP, b1 = (pq + 1u) * nb / kSmP;   // sorted blocks [b0, b1)
-    const uint32_t e0 = b0 * 64u, ne = (b1 - b0) * 64u;   // <= kLsMaxS / kSmP
-    for (uint32_t x = t; x < ne; x += kSmT) {
-        sk[x] = R.smp_k[e0 + x];
-        si[x] = (uint16_t)R.smp_j[e0 + x];
-    }
-    const uint32_t s = g * 64u + lane;
-    const uint64_t ks = R.raw_k[s];
-    __syncthreads();
-    uint32_t c = 0;
-    for (uint32_t b = w; b < b1 - b0; b += kSmW) {
-        // the block's pairs below (ks, s): steps of 32 .. 1, then the last one
-        const uint32_t base = b * 64u;
+    uint32_t buf = 0, at = t;
+    for (uint32_t len = 64; len < kSB; len <<= 1) {
+        mk[buf][at] = k;
+        mi[buf][at] = (uint16_t)i;
+        __syncthreads();
+        k = mk[buf][t];
+        i = mi[buf][t];
+        // the other stretch's pairs below this one's
+        const uint32_t base = (t & ~(2u * len - 1u)) + ((t & len) ? 0u : len);
         uint32_t pos = 0;
-#pragma unroll
-        for (uint32_t step = 32; step > 0; step >>= 1) {
-            const uint32_t q = base + pos + step - 1u;
-            const uint64_t x = sk[q];
-            if (x < ks || (x == ks && si[q] < s)) pos += step;
+        for (uint32_t step = len >> 1; step > 0; step >>= 1) {
+            const uint64_t x = mk[buf][base + pos + step - 1u];
+            if (x < k || (x == k && mi[buf][base + pos + step - 1u] < i)) pos += step;
         }
-        const uint32_t q = base + pos;   // pos <= 63
-        const uint64_t x = sk[q];
-        if (x < ks || (x == ks && si[q] < s)) pos++;
-        c += pos;
+        const uint64_t x = mk[buf][base + pos];   // pos < len
+        if (x < k || (x == k && mi[buf][base + pos] < i)) pos++;
+        at = (t & ~(2u * len - 1u)) + (t & (len - 1u)) + pos;
+        buf ^= 1u;
     }
-    part[w][lane] = c;
-    __syncthreads();
-    if (w == 0) {
-        uint32_t r = 0;
+    R.srt_k[s0 + at] = k;
+    R.srt_i[s0 + at] = s0 + i;
+}
+
+// Block (p, q): sorted block p in LDS, the ranks in it of kSmE samples per
+// thread. Sample indices increase with the positions, so the order is the
+// pair order by (key, position).
+constexpr uint32_t kSmE = 2;
+
+__global__ __launch_bounds__(kSB) void k_ls_sample(LsArgs a)
+{
+    __shared__ uint64_t sk[kSB];
+    __shared__ uint16_t si[kSB];
+    const LsRow &R = a.r[a.srow[blockIdx.y]];
+    const uint32_t S = R.S, nb = S / kSB, p = blockIdx.x % nb, e0 = blockIdx.x / nb * (kSB * kSmE);
+    if (e0 >= S) return;
+    const uint32_t t = threadIdx.x;
+    uint64_t k[kSmE];
+    uint32_t i[kSmE], pos[kSmE];
 #pragma unroll
-        for (int qq = 0; qq < kSmW; qq++) r += part[qq][lane];
-        R.rpart[(uint64_t)pq * S + s] = r;
+    for (uint32_t u = 0; u < kSmE; u++) {
+        const uint32_t e = e0 + u * kSB + t;
+        k[u] = e < S ? R.srt_k[e] : 0;
+        i[u] = e < S ? R.srt_i[e] : 0;
+        pos[u] = 0;
+    }
+    sk[t] = R.srt_k[p * kSB + t];
+    si[t] = (uint16_t)(R.srt_i[p * kSB + t] - p * kSB);   // the block's samples are its stratum's
+    __syncthreads();
+    auto below = [&](uint32_t y, uint32_t u) {
+        const uint64_t x = sk[y];
+        return x < k[u] || (x == k[u] && p * kSB + si[y] < i[u]);
+    };
+#pragma unroll
+    for (uint32_t step = kSB / 2; step > 0; step >>= 1)
+#pragma unroll
+        for (uint32_t u = 0; u < kSmE; u++)
+            if (below(pos[u] + step - 1u, u)) pos[u] += step;
+#pragma unroll
+    for (uint32_t u = 0; u < kSmE; u++) {
+        if (below(pos[u], u)) pos[u]++;   // (pos < kSB before)
+        const uint32_t e = e0 + u * kSB + t;
+        if (e < S) R.rpart[(uint64_t)p * S + e] = (uint16_t)pos[u];
     }
 }
 
-// Each sample at its rank (the sum of its parts' counts).
+// Each sample at its rank (the sum of its ranks in the blocks).
 __global__ __launch_bounds__(256) void k_ls_place(LsArgs a)
 {
     const LsRow &R = a.r[a.srow[blockIdx.y]];
-    const uint32_t s = blockIdx.x * 256u + threadIdx.x, S = R.S;
-    if (s >= S) return;
+    const uint32_t e = blockIdx.x * 256u + threadIdx.x, S = R.S;
+    if (e >= S) return;
     uint32_t r = 0;
-#pragma unroll
-    for (uint32_t p = 0; p < kSmP; p++) r += R.rpart[(uint64_t)p * S + s];
-    R.smp_k[r] = R.raw_k[s];
-    R.smp_j[r] = ls_pos(s, a.n, S);
+#pragma unroll 8
+    for (uint32_t p = 0; p < S / kSB; p++) r += R.rpart[(uint64_t)p * S + e];
+    R.smp_k[r] = R.srt_k[e];
+    R.smp_j[r] = ls_pos(R.srt_i[e], a.n, S);
 }
+
+// The splitter between buckets b - 1 and b, 1 <= b < B: its rank in the sample.
+__device__ __forceinline__ uint32_t ls_split_rank(const LsRow &R, uint32_t b) { return b * R.S / R.B; }   // b S < 2^28
 
 // The splitters in breadth-first (Eytzinger) order of a complete search tree
 // of height hgt: node e (1-based, depth d, p = e - 2^d) holds splitter
@@ -353,7 +374,7 @@ __device__ __forceinline__ void ls_tree(const LsRow &R, uint64_t *tk, uint32_t *
         uint64_t k = ~0ull;
         uint32_t j = ~0u;
         if (i + 1u < R.B) {
-            const uint32_t r = (i + 1u) * R.S / R.B;   // < S; (i + 1) S < 2^23
+            const uint32_t r = ls_split_rank(R, i + 1u);   // < S
             k = R.smp_k[r];
             j = R.smp_j[r];
         }
@@ -364,19 +385,21 @@ __device__ __forceinline__ void ls_tree(const LsRow &R, uint64_t *tk, uint32_t *
 
 // A partition row's tile: the count of each digit, and the per-request keys
 // (Priority: the tier's priority) in request order.
+template <uint32_t kMB>
 __device__ __forceinline__ void ls_count_part(const LsArgs &a, const LsRow &R, uint32_t *h)
 {
-    const uint32_t t = threadIdx.x, n = a.n, base = blockIdx.x * kTile;
-    const uint32_t cnt = n - base < kTile ? n - base : kTile;
-    uint32_t d[kTR];
+    constexpr int kR = kTR<kMB>;
+    const uint32_t t = threadIdx.x, n = a.n, base = blockIdx.x * kTile<kMB>;
+    const uint32_t cnt = n - base < kTile<kMB> ? n - base : kTile<kMB>;
+    uint32_t d[kR];
 #pragma unroll
-    for (int r = 0; r < kTR; r++) {
+    for (int r = 0; r < kR; r++) {
         const uint32_t idx = (uint32_t)r * kTT + t;
         d[r] = idx < cnt ? (uint32_t)ls_key(a, R, base + idx) : kQ;   // kQ: no position
     }
     if (R.key_out && R.kind == SortKind::Class) {
 #pragma unroll
-        for (int r = 0; r < kTR; r++) {
+        for (int r = 0; r < kR; r++) {
             const uint32_t idx = (uint32_t)r * kTT + t;
             if (idx < cnt) ls_key_out(a, R, base + idx);
         }
@@ -384,30 +407,32 @@ __device__ __forceinline__ void ls_count_part(const LsArgs &a, const LsRow &R, u
     if (t < kQ) h[t] = 0;
     __syncthreads();
 #pragma unroll
-    for (int r = 0; r < kTR; r++)
+    for (int r = 0; r < kR; r++)
         if (d[r] < kQ) atomicAdd(&h[d[r]], 1u);
     __syncthreads();
     if (t < kQ) R.tcnt[(uint64_t)blockIdx.x * kQ + t] = h[t];
 }
 
+template <uint32_t kMB>
 __global__ __launch_bounds__(kTT) void k_ls_count(LsArgs a)
 {
-    __shared__ uint64_t tk[kLsMaxB];
-    __shared__ uint32_t tj[kLsMaxB];
-    __shared__ uint32_t h[kLsMaxB];
+    constexpr int kR = kTR<kMB>;
+    __shared__ uint64_t tk[kMB];
+    __shared__ uint32_t tj[kMB];
+    __shared__ uint32_t h[kMB];
     const LsRow &R = a.r[blockIdx.y];
-    const uint32_t t = threadIdx.x, n = a.n, base = blockIdx.x * kTile;
-    const uint32_t cnt = n - base < kTile ? n - base : kTile;
+    const uint32_t t = threadIdx.x, n = a.n, base = blockIdx.x * kTile<kMB>;
+    const uint32_t cnt = n - base < kTile<kMB> ? n - base : kTile<kMB>;
     // (no waits here: the caller's status word is only cleared)
     if (blockIdx.x == 0 && blockIdx.y == 0 && t == 0 && a.in.wait.clear && a.in.wait.status)
         *a.in.wait.status = 0;
     if (is_part(R.kind)) {
-        ls_count_part(a, R, h);
+        ls_count_part<kMB>(a, R, h);
         return;
     }
-    uint64_t k[kTR];
+    uint64_t k[kR];
 #pragma unroll
-    for (int r = 0; r < kTR; r++) {
+    for (int r = 0; r < kR; r++) {
         const uint32_t idx = (uint32_t)r * kTT + t;
         const bool ok = idx < cnt;
         k[r] = ls_key(a, R, base + (ok ? idx : 0u));
@@ -415,7 +440,7 @@ __global__ __launch_bounds__(kTT) void k_ls_count(LsArgs a)
     // the per-request keys, in request order
     if (R.key_out) {
 #pragma unroll
-        for (int r = 0; r < kTR; r++)
+        for (int r = 0; r < kR; r++)
             if ((uint32_t)r * kTT + t < cnt) ls_key_out(a, R, base + (uint32_t)r * kTT + t);
     }
     ls_tree(R, tk, tj);
@@ -424,18 +449,18 @@ __global__ __launch_bounds__(kTT) void k_ls_count(LsArgs a)
     const uint32_t hgt = R.hgt;
     // bucket = splitters <= (key, j): hgt steps down the tree, the rounds
     // side by side so that their LDS reads overlap
-    uint32_t node[kTR];
+    uint32_t node[kR];
 #pragma unroll
-    for (int r = 0; r < kTR; r++) node[r] = 1;
+    for (int r = 0; r < kR; r++) node[r] = 1;
     for (uint32_t l = 0; l < hgt; l++) {
 #pragma unroll
-        for (int r = 0; r < kTR; r++) {
+        for (int r = 0; r < kR; r++) {
             const uint32_t j = base + (uint32_t)r * kTT + t;
             node[r] = 2u * node[r] + (pair_less(k[r], j, tk[node[r]], tj[node[r]]) ? 0u : 1u);
         }
     }
 #pragma unroll
-    for (int r = 0; r < kTR; r++) {
+    for (int r = 0; r < kR; r++) {
         const uint32_t idx = (uint32_t)r * kTT + t;
         if (idx < cnt) {
             const uint32_t b = node[r] - (1u << hgt);
@@ -448,21 +473,23 @@ __global__ __launch_bounds__(kTT) void k_ls_count(LsArgs a)
     for (uint32_t b = t; b < R.B; b += kTT) row[b] = h[b];
 }
 
-// Block c: buckets 64 c .. 64 c + 63 over all tiles (at most 256), staged in
-// LDS; wave w scans the columns w, w + 16, ... (four tiles per lane).
+// Block c: buckets 64 c .. 64 c + 63 over all tiles (at most kMT), staged in
+// LDS; wave w scans the columns w, w + 16, ... (kMT / 64 tiles per lane).
 constexpr int kScT = 1024, kScW = kScT / 64;
-constexpr uint32_t kMaxTiles = kLsMaxN / kTile;   // 256
+template <uint32_t kMB> constexpr uint32_t kMT = kMB * kLsAvg / kTile<kMB>;   // 256 or 512
 
+template <uint32_t kMB>
 __global__ __launch_bounds__(kScT) void k_ls_scan(LsArgs a)
 {
-    __shared__ uint32_t col[kMaxTiles][65];
+    constexpr uint32_t kL = kMT<kMB> / 64;
+    __shared__ uint32_t col[kMT<kMB>][65];
     __shared__ uint32_t tot[64];
     __shared__ uint16_t per[kWrrMaxWeightSum];
     const LsRow &R = a.r[blockIdx.y];
     const uint32_t t = threadIdx.x, lane = (uint32_t)lane_id(), w = t >> 6;
     const uint32_t b0 = blockIdx.x * 64u, T = a.tiles, B = R.B;
     if (b0 >= B) return;   // a row with fewer buckets than the grid is wide
-    constexpr int kPer = kMaxTiles * 64 / kScT;   // 16 loads per thread, in flight together
+    constexpr int kPer = kMT<kMB> * 64 / kScT;   // loads per thread, in flight together
     {
         uint32_t x[kPer];
 #pragma unroll
@@ -478,18 +505,18 @@ __global__ __launch_bounds__(kScT) void k_ls_scan(LsArgs a)
     }
     __syncthreads();
     for (uint32_t bb = w; bb < 64u; bb += kScW) {
-        uint32_t v[4], sum = 0;
+        uint32_t v[kL], sum = 0;
 #pragma unroll
-        for (int q = 0; q < 4; q++) {
-            const uint32_t tl = 4u * lane + (uint32_t)q;
+        for (uint32_t q = 0; q < kL; q++) {
+            const uint32_t tl = kL * lane + q;
             v[q] = tl < T ? col[tl][bb] : 0u;
             sum += v[q];
         }
         const uint32_t incl = wave_incl_scan_dpp(sum);
         uint32_t ex = incl - sum;
 #pragma unroll
-        for (int q = 0; q < 4; q++) {
-            const uint32_t tl = 4u * lane + (uint32_t)q;
+        for (uint32_t q = 0; q < kL; q++) {
+            const uint32_t tl = kL * lane + q;
             if (tl < T) col[tl][bb] = ex;
             ex += v[q];
         }
@@ -520,19 +547,22 @@ __global__ __launch_bounds__(kScT) void k_ls_scan(LsArgs a)
 
 // A partition row's tile: each position's rank among the sequence's
 // positions of its digit (the tile's first slot in the digit, from the scan,
-// plus its stable rank in the tile: wave w holds the tile's positions
-// 512 w .. 512 w + 511 in order, ranked round by round with ballots), then
+// plus its stable rank in the tile: wave w holds the tile's positions from
+// 64 kTR w on in order, ranked round by round with ballots), then
 // its place: Priority at the class's start plus that rank, Weighted at the
 // round-robin position of the rank-th request of the tier.
-__device__ __forceinline__ void ls_place_part(const LsArgs &a, const LsRow &R, uint32_t (*wc)[kQ], WrrPlanHead &wh)
+template <uint32_t kMB>
+__device__ __forceinline__ void ls_place_part(const LsArgs &a, const LsRow &R, uint32_t tile, uint32_t (*wc)[kQ],
+                                              WrrPlanHead &wh)
 {
-    constexpr uint32_t kWK = 64u * kTR;
-    const uint32_t t = threadIdx.x, n = a.n, base = blockIdx.x * kTile;
+    constexpr int kR = kTR<kMB>;
+    constexpr uint32_t kWK = 64u * kR;
+    const uint32_t t = threadIdx.x, n = a.n, base = tile * kTile<kMB>;
     const int w = (int)(t >> 6), lane = lane_id();
-    const uint32_t cnt = n - base < kTile ? n - base : kTile;
-    uint32_t d[kTR], v[kTR], rk[kTR];
+    const uint32_t cnt = n - base < kTile<kMB> ? n - base : kTile<kMB>;
+    uint32_t d[kR], v[kR], rk[kR];
 #pragma unroll
-    for (int r = 0; r < kTR; r++) {
+    for (int r = 0; r < kR; r++) {
         const uint32_t idx = (uint32_t)w * kWK + (uint32_t)r * 64u + (uint32_t)lane;
         const uint32_t j = base + (idx < cnt ? idx : 0u);
         d[r] = (uint32_t)ls_key(a, R, j);   // < kQ
@@ -545,10 +575,10 @@ __device__ __forceinline__ void ls_place_part(const LsArgs &a, const LsRow &R, u
             reinterpret_cast<uint32_t *>(&wh)[i] = reinterpret_cast<const uint32_t *>(&a.plan->h)[i];
     __syncthreads();
 #pragma unroll
-    for (int r = 0; r < kTR; r++) {
+    for (int r = 0; r < kR; r++) {
         const uint32_t idx = (uint32_t)w * kWK + (uint32_t)r * 64u + (uint32_t)lane;
         const bool ok = idx < cnt;
-        const uint64_t peers = digit_peers(d[r], ok);
+        const uint64_t peers = match_bits<4>(d[r], __ballot(ok));
         const uint32_t below = (uint32_t)__popcll(peers & lanemask_lt());
         const uint32_t old = ok ? wc[w][d[r]] : 0u;
         rk[r] = old + below;
@@ -557,7 +587,7 @@ __device__ __forceinline__ void ls_place_part(const LsArgs &a, const LsRow &R, u
     }
     __syncthreads();
     if (t < kQ) {
-        uint32_t acc = R.tcnt[(uint64_t)blockIdx.x * kQ + t];   // the tile's first slot in digit t
+        uint32_t acc = R.tcnt[(uint64_t)tile * kQ + t];   // the tile's first slot in digit t
 #pragma unroll
         for (int q = 0; q < kTT / 64; q++) {
             const uint32_t c = wc[q][t];
@@ -568,7 +598,7 @@ __device__ __forceinline__ void ls_place_part(const LsArgs &a, const LsRow &R, u
     __syncthreads();
     const uint32_t nq = a.in.n_tiers < kQ ? a.in.n_tiers : kQ;
 #pragma unroll
-    for (int r = 0; r < kTR; r++) {
+    for (int r = 0; r < kR; r++) {
         const uint32_t idx = (uint32_t)w * kWK + (uint32_t)r * 64u + (uint32_t)lane;
         if (idx >= cnt) continue;
         const uint32_t q = d[r], kd = wc[w][q] + rk[r];   // rank among the digit's requests
@@ -611,102 +641,110 @@ __device__ __forceinline__ void ls_place_part(const LsArgs &a, const LsRow &R, u
     }
 }
 
+// The dispatcher deals blocks to the 8 XCDs round robin; consecutive tiles go
+// to one XCD, so that the short runs they write to a bucket meet in one L2
+// (five orders of 1,048,576 requests: 217 and 210 us).
+template <uint32_t kMB>
 __global__ __launch_bounds__(kTT) void k_ls_scatter(LsArgs a)
 {
-    static_assert(2 * kTT == kLsMaxB, "two buckets per thread");
-    __shared__ uint32_t h[kLsMaxB], texcl[kLsMaxB], gb[kLsMaxB];
-    __shared__ uint64_t lk[kTile];
-    __shared__ uint32_t lj[kTile];
-    __shared__ uint16_t lb[kTile];
+    constexpr int kR = kTR<kMB>;
+    constexpr uint32_t kT = kTile<kMB>, kPB = kMB / kTT;   // buckets per thread
+    static_assert(kPB * kTT == kMB, "");
+    __shared__ uint32_t h[kMB], texcl[kMB], gb[kMB];
+    __shared__ uint64_t lk[kT];
+    __shared__ uint32_t lj[kT];
     __shared__ uint32_t wsum[kTT / 64];
     __shared__ uint32_t pwc[kTT / 64][kQ];
     __shared__ WrrPlanHead wh;
     const LsRow &R = a.r[blockIdx.y];
+    const uint32_t per = a.tiles / 8u, x8 = blockIdx.x;
+    const uint32_t tile = x8 < per * 8u ? (x8 % 8u) * per + x8 / 8u : x8;
     if (is_part(R.kind)) {
-        ls_place_part(a, R, pwc, wh);
+        ls_place_part<kMB>(a, R, tile, pwc, wh);
         return;
     }
-    const uint32_t t = threadIdx.x, n = a.n, B = R.B, base = blockIdx.x * kTile;
-    const uint32_t cnt = n - base < kTile ? n - base : kTile;
-    uint64_t k[kTR];
-    uint32_t b[kTR], sl[kTR];
+    const uint32_t t = threadIdx.x, n = a.n, B = R.B, base = tile * kT;
+    const uint32_t cnt = n - base < kT ? n - base : kT;
+    uint64_t k[kR];
+    uint32_t b[kR], sl[kR];
 #pragma unroll
-    for (int r = 0; r < kTR; r++) {
+    for (int r = 0; r < kR; r++) {
         const uint32_t idx = (uint32_t)r * kTT + t;
         const uint32_t j = base + (idx < cnt ? idx : 0u);
         k[r] = ls_key(a, R, j);
         b[r] = R.bid[j];
+        if (R.rt) {   // the tier rides above the bucket
+            const uint32_t q = a.in.tier[j];
+            b[r] |= (q < kQ ? q : kQ - 1u) << 12;
+        }
     }
-    // the regions: exclusive scan of the sizes (thread t: buckets 2t, 2t + 1)
-    const uint32_t b0 = 2u * t, b1 = b0 + 1u;
-    const uint32_t z0 = b0 < B ? R.size[b0] : 0u, z1 = b1 < B ? R.size[b1] : 0u;
-    h[b0] = 0;
-    h[b1] = 0;
-    const uint32_t rs = blk_excl_scan<kTT>(z0 + z1, wsum);   // (its barriers order the clears)
+    // the regions: exclusive scan of the sizes (thread t: buckets kPB t ..)
+    uint32_t z[kPB], zs = 0;
 #pragma unroll
-    for (int r = 0; r < kTR; r++) {
+    for (uint32_t e = 0; e < kPB; e++) {
+        const uint32_t bb = kPB * t + e;
+        z[e] = bb < B ? R.size[bb] : 0u;
+        zs += z[e];
+        h[bb] = 0;
+    }
+    uint32_t rs = blk_excl_scan<kTT>(zs, wsum);   // (its barriers order the clears)
+#pragma unroll
+    for (int r = 0; r < kR; r++) {
         const uint32_t idx = (uint32_t)r * kTT + t;
-        sl[r] = idx < cnt ? atomicAdd(&h[b[r]], 1u) : 0u;
+        sl[r] = idx < cnt ? atomicAdd(&h[b[r] & 4095u], 1u) : 0u;
     }
     __syncthreads();
-    const uint32_t h0 = h[b0], h1 = h[b1];
-    const uint32_t te = blk_excl_scan<kTT>(h0 + h1, wsum);
-    texcl[b0] = te;
-    texcl[b1] = te + h0;
-    if (blockIdx.x == 0) {
-        if (b0 < B) R.start[b0] = rs;
-        if (b1 < B) R.start[b1] = rs + z0;
+    uint32_t hs = 0;
+#pragma unroll
+    for (uint32_t e = 0; e < kPB; e++) hs += h[kPB * t + e];
+    uint32_t te = blk_excl_scan<kTT>(hs, wsum);
+    const uint32_t *row = R.tcnt + (uint64_t)tile * B;
+#pragma unroll
+    for (uint32_t e = 0; e < kPB; e++) {
+        const uint32_t bb = kPB * t + e;
+        texcl[bb] = te;
+        te += h[bb];
+        if (tile == 0 && bb < B) R.start[bb] = rs;
+        gb[bb] = rs + (bb < B ? row[bb] : 0u);
+        rs += z[e];
     }
-    const uint32_t *row = R.tcnt + (uint64_t)blockIdx.x * B;
-    gb[b0] = rs + (b0 < B ? row[b0] : 0u);
-    gb[b1] = rs + z0 + (b1 < B ? row[b1] : 0u);
     __syncthreads();
 #pragma unroll
-    for (int r = 0; r < kTR; r++) {
+    for (int r = 0; r < kR; r++) {
         const uint32_t idx = (uint32_t)r * kTT + t;
         if (idx < cnt) {
-            const uint32_t p = texcl[b[r]] + sl[r];
+            const uint32_t p = texcl[b[r] & 4095u] + sl[r];
             lk[p] = k[r];
-            lj[p] = (base + idx) | (b[r] << kJBits);
+            lj[p] = idx | (b[r] << kIBits);
         }
     }
     __syncthreads();
-    const bool pay = R.rv || R.rt;
     for (uint32_t s = t; s < cnt; s += kTT) {
-        const uint32_t x = lj[s], bb = x >> kJBits;
+        const uint32_t x = lj[s], bb = (x >> kIBits) & 4095u;
         const uint32_t g = gb[bb] + (s - texcl[bb]);   // < n: a region holds its bucket's pairs
         R.rk[0][g] = lk[s];
-        R.rj[0][g] = x & kJMask;
-        if (pay) lb[s] = (uint16_t)bb;
+        R.rj[0][g] = base + (x & ((1u << kIBits) - 1u));
+        if (R.rt) R.rt[g] = (uint8_t)(x >> (kIBits + 12u));
     }
-    if (!pay) return;
+    if (!R.rv && !R.rb) return;
     // the payloads ride along the same way (read in sequence order, staged
     // in the same places, written in the same runs), so that the bucket sort
     // gathers nothing: the value of a sort over in.fifo, or the FIFO sort's
-    // tier and budget
+    // budget
     __syncthreads();
 #pragma unroll
-    for (int r = 0; r < kTR; r++) {
+    for (int r = 0; r < kR; r++) {
         const uint32_t idx = (uint32_t)r * kTT + t;
         if (idx < cnt) {
-            const uint32_t p = texcl[b[r]] + sl[r], j = base + idx;
-            if (R.rv) {
-                lj[p] = ls_value(a, R, j);
-            } else {
-                lj[p] = a.in.tier[j];
-                if (R.rb) lk[p] = (uint64_t)__double_as_longlong(a.in.budget[j]);
-            }
+            const uint32_t p = texcl[b[r] & 4095u] + sl[r], j = base + idx;
+            lk[p] = R.rv ? ls_value(a, R, j) : (uint64_t)__double_as_longlong(a.in.budget[j]);
         }
     }
     __syncthreads();
     for (uint32_t s = t; s < cnt; s += kTT) {
-        const uint32_t bb = lb[s], g = gb[bb] + (s - texcl[bb]);
-        if (R.rv) {
-            R.rv[g] = lj[s];
-        } else {
-            R.rt[g] = (uint8_t)lj[s];
-            if (R.rb) R.rb[g] = __longlong_as_double((long long)lk[s]);
-        }
+        const uint32_t bb = (lj[s] >> kIBits) & 4095u, g = gb[bb] + (s - texcl[bb]);
+        if (R.rv) R.rv[g] = (uint32_t)lk[s];
+        else R.rb[g] = __longlong_as_double((long long)lk[s]);
     }
 }
 
@@ -768,15 +806,16 @@ __device__ __forceinline__ void blk_reduce(BkLs &sh, uint64_t &v0, uint64_t &v1,
 // pos[r] = the entry's place among the m in the pass order; sh.texcl: the
 // digits' exclusive starts, sh.dtot: their counts. sh.wc must be zero on
 // entry and is left zero. Ends with a barrier.
+template <int kR>
 __device__ __forceinline__ void ls_byte_rank(BkLs &sh, const uint64_t *k, const uint32_t *j, bool sel,
                                              uint32_t sh8, uint32_t reff, uint32_t m, uint32_t *pos)
 {
     const uint32_t t = threadIdx.x;
     const int w = (int)(t >> 6), lane = lane_id();
     const uint32_t wk = 64u * reff;
-    uint32_t rk[kBR], dg[kBR];
+    uint32_t rk[kR], dg[kR];
 #pragma unroll
-    for (int r = 0; r < kBR; r++) {
+    for (int r = 0; r < kR; r++) {
         rk[r] = 0;
         dg[r] = 0;
         if ((uint32_t)r < reff) {
@@ -811,7 +850,7 @@ __device__ __forceinline__ void ls_byte_rank(BkLs &sh, const uint64_t *k, const 
     }
     __syncthreads();
 #pragma unroll
-    for (int r = 0; r < kBR; r++)
+    for (int r = 0; r < kR; r++)
         if ((uint32_t)r < reff) pos[r] = sh.texcl[dg[r]] + sh.wc[w][dg[r]] + rk[r];
     __syncthreads();
     for (uint32_t i = t; i < kBW * 256u; i += kBT) (&sh.wc[0][0])[i] = 0;
@@ -868,7 +907,7 @@ __device__ void ls_big_bucket(const LsArgs &a, const LsRow &R, BkLs &sh, uint32_
                 k[r] = ok ? R.rk[src][off + c0 + idx] : 0ull;
                 j[r] = ok ? R.rj[src][off + c0 + idx] : 0u;
             }
-            ls_byte_rank(sh, k, j, sel, sh8, reff, cm, pos);
+            ls_byte_rank<kBR>(sh, k, j, sel, sh8, reff, cm, pos);
 #pragma unroll
             for (int r = 0; r < kBR; r++) {
                 const uint32_t idx = (uint32_t)w * wk + (uint32_t)r * 64u + (uint32_t)lane;
@@ -889,58 +928,65 @@ __device__ void ls_big_bucket(const LsArgs &a, const LsRow &R, BkLs &sh, uint32_
         ls_emit(a, R, off + i, R.rk[src][off + i], ls_pay_gather(a, R, R.rj[src][off + i]));
 }
 
-__global__ __launch_bounds__(kBT) void k_ls_bucket(LsArgs a)
+// A bucket of m <= kR kBT pairs at [off, off + m), sh.bin zero.
+template <int kR>
+__device__ void ls_bucket(const LsArgs &a, const LsRow &R, BkLs &sh, uint32_t bkt, uint32_t off, uint32_t m)
 {
-    __shared__ BkLs sh;
-    const LsRow &R = a.r[blockIdx.y];
-    const uint32_t t = threadIdx.x, bkt = blockIdx.x;
-    if (bkt >= R.B) return;   // a row with fewer buckets than the grid is wide
+    const uint32_t t = threadIdx.x;
     const int w = (int)(t >> 6), lane = lane_id();
-    const uint32_t m = R.size[bkt], off = R.start[bkt];
-    for (uint32_t i = t; i <= kBins; i += kBT) sh.bin[i] = 0;
-    for (uint32_t i = t; i < kBW * 256u; i += kBT) (&sh.wc[0][0])[i] = 0;
-    __syncthreads();
-    if (m > kLsCap) {
-        ls_big_bucket(a, R, sh, off, m);
-        return;
-    }
     const uint32_t reff = (m + kBT - 1) / kBT, wk = 64u * reff;
-    uint64_t k[kBR];
-    uint32_t j[kBR], rank[kBR];
-    uint64_t kmn = ~0ull, kmx = 0, jmn = ~0ull, jmx = 0;
+    uint64_t k[kR];
+    uint32_t j[kR], rank[kR];
 #pragma unroll
-    for (int r = 0; r < kBR; r++) {
+    for (int r = 0; r < kR; r++) {
         const uint32_t idx = (uint32_t)w * wk + (uint32_t)r * 64u + (uint32_t)lane;
         const bool ok = (uint32_t)r < reff && idx < m;
         k[r] = ok ? R.rk[0][off + idx] : 0ull;
         j[r] = ok ? R.rj[0][off + idx] : 0u;
         rank[r] = 0;
-        if (ok) {
-            kmn = k[r] < kmn ? k[r] : kmn;
-            kmx = k[r] > kmx ? k[r] : kmx;
-            jmn = j[r] < jmn ? j[r] : jmn;
-            jmx = j[r] > jmx ? j[r] : jmx;
-        }
     }
-    blk_reduce<Red::Min, Red::Max, Red::Min, Red::Max>(sh, kmn, kmx, jmn, jmx);
-    // the primary key of the bins: the key, or j when every key is equal
-    const bool byj = kmn == kmx;
     bool permuted = false;   // the byte passes moved the entries (their payloads are gathered)
-    if (m <= 1) {
-        // nothing to order
-    } else {
+    // the range the bins cover: the splitters' keys on either side of the
+    // bucket, or the pairs' own range for the first and the last bucket and
+    // where the first choice crowds a bin (no reduction otherwise)
+    bool own = bkt == 0 || bkt + 1u == R.B;
+    while (m > 1) {
+        uint64_t kmn, kmx, jmn, jmx;
+        if (own) {
+            kmn = jmn = ~0ull;
+            kmx = jmx = 0;
+#pragma unroll
+            for (int r = 0; r < kR; r++) {
+                const uint32_t idx = (uint32_t)w * wk + (uint32_t)r * 64u + (uint32_t)lane;
+                if ((uint32_t)r < reff && idx < m) {
+                    kmn = k[r] < kmn ? k[r] : kmn;
+                    kmx = k[r] > kmx ? k[r] : kmx;
+                    jmn = j[r] < jmn ? j[r] : jmn;
+                    jmx = j[r] > jmx ? j[r] : jmx;
+                }
+            }
+            blk_reduce<Red::Min, Red::Max, Red::Min, Red::Max>(sh, kmn, kmx, jmn, jmx);
+        } else {
+            const uint32_t s0 = ls_split_rank(R, bkt), s1 = ls_split_rank(R, bkt + 1u);
+            kmn = R.smp_k[s0];
+            kmx = R.smp_k[s1];
+            jmn = R.smp_j[s0];
+            jmx = R.smp_j[s1];
+        }
+        // the primary key of the bins: the key, or j when every key is equal
+        const bool byj = kmn == kmx;
         const uint64_t pmn = byj ? jmn : kmn, pmx = byj ? jmx : kmx;
-        const uint64_t span = pmx - pmn;   // > 0: the pairs differ in p when m > 1
+        const uint64_t span = pmx - pmn;   // > 0: the pairs (or the splitters) differ
         const uint32_t bl = 64u - (uint32_t)__clzll((long long)span);
         const uint32_t shift = bl > kBinBits ? bl - kBinBits : 0u;
-        uint32_t db[kBR];
+        uint32_t db[kR];
 #pragma unroll
-        for (int r = 0; r < kBR; r++) {
+        for (int r = 0; r < kR; r++) {
             const uint32_t idx = (uint32_t)w * wk + (uint32_t)r * 64u + (uint32_t)lane;
             db[r] = 0;
             if ((uint32_t)r < reff && idx < m) {
                 const uint64_t p = byj ? (uint64_t)j[r] : k[r];
-                const uint32_t q = (uint32_t)((p - pmn) >> shift);   // < kBins
+                const uint32_t q = (uint32_t)((p - pmn) >> shift) & (kBins - 1u);
                 db[r] = q | (atomicAdd(&sh.bin[q], 1u) << kBinBits);
             }
         }
@@ -973,11 +1019,17 @@ __global__ __launch_bounds__(kBT) void k_ls_bucket(LsArgs a)
             for (int q = 0; q < kBW; q++) maxbin = sh.wmax[q] > maxbin ? sh.wmax[q] : maxbin;
             __syncthreads();
         }
+        if (maxbin > kBinMax && !own) {   // try the pairs' own range
+            own = true;
+            for (uint32_t i = t; i < kBins; i += kBT) sh.bin[i] = 0;
+            __syncthreads();
+            continue;
+        }
         if (maxbin <= kBinMax) {
             // each pair in its bin, then its rank = the bin's start + the
             // pairs of the bin below it
 #pragma unroll
-            for (int r = 0; r < kBR; r++) {
+            for (int r = 0; r < kR; r++) {
                 const uint32_t idx = (uint32_t)w * wk + (uint32_t)r * 64u + (uint32_t)lane;
                 if ((uint32_t)r < reff && idx < m) {
                     const uint32_t p = sh.bin[db[r] & (kBins - 1u)] + (db[r] >> kBinBits);
@@ -987,7 +1039,7 @@ __global__ __launch_bounds__(kBT) void k_ls_bucket(LsArgs a)
             }
             __syncthreads();
 #pragma unroll
-            for (int r = 0; r < kBR; r++) {
+            for (int r = 0; r < kR; r++) {
                 const uint32_t idx = (uint32_t)w * wk + (uint32_t)r * 64u + (uint32_t)lane;
                 if ((uint32_t)r < reff && idx < m) {
                     const uint32_t q = db[r] & (kBins - 1u);
@@ -1015,7 +1067,7 @@ __global__ __launch_bounds__(kBT) void k_ls_bucket(LsArgs a)
             // the bits that vary: some pair differs there from the minimum
             uint64_t kor = 0, jor = 0, z0 = 0, z1 = 0;
 #pragma unroll
-            for (int r = 0; r < kBR; r++) {
+            for (int r = 0; r < kR; r++) {
                 const uint32_t idx = (uint32_t)w * wk + (uint32_t)r * 64u + (uint32_t)lane;
                 if ((uint32_t)r < reff && idx < m) {
                     kor |= k[r] ^ kmn;
@@ -1027,10 +1079,10 @@ __global__ __launch_bounds__(kBT) void k_ls_bucket(LsArgs a)
                 const bool sel = pass < 3;
                 const uint32_t sh8 = 8u * (sel ? pass : pass - 3u);
                 if ((((sel ? jor : kor) >> sh8) & 255u) == 0) continue;
-                uint32_t pos[kBR];
-                ls_byte_rank(sh, k, j, sel, sh8, reff, m, pos);
+                uint32_t pos[kR];
+                ls_byte_rank<kR>(sh, k, j, sel, sh8, reff, m, pos);
 #pragma unroll
-                for (int r = 0; r < kBR; r++) {
+                for (int r = 0; r < kR; r++) {
                     const uint32_t idx = (uint32_t)w * wk + (uint32_t)r * 64u + (uint32_t)lane;
                     if ((uint32_t)r < reff && idx < m) {
                         sh.lk[pos[r]] = k[r];
@@ -1039,7 +1091,7 @@ __global__ __launch_bounds__(kBT) void k_ls_bucket(LsArgs a)
                 }
                 __syncthreads();
 #pragma unroll
-                for (int r = 0; r < kBR; r++) {
+                for (int r = 0; r < kR; r++) {
                     const uint32_t idx = (uint32_t)w * wk + (uint32_t)r * 64u + (uint32_t)lane;
                     if ((uint32_t)r < reff && idx < m) {
                         k[r] = sh.lk[idx];
@@ -1049,17 +1101,37 @@ __global__ __launch_bounds__(kBT) void k_ls_bucket(LsArgs a)
                 __syncthreads();
             }
 #pragma unroll
-            for (int r = 0; r < kBR; r++) rank[r] = (uint32_t)w * wk + (uint32_t)r * 64u + (uint32_t)lane;
+            for (int r = 0; r < kR; r++) rank[r] = (uint32_t)w * wk + (uint32_t)r * 64u + (uint32_t)lane;
             permuted = true;
         }
+        break;
     }
 #pragma unroll
-    for (int r = 0; r < kBR; r++) {
+    for (int r = 0; r < kR; r++) {
         const uint32_t idx = (uint32_t)w * wk + (uint32_t)r * 64u + (uint32_t)lane;
         if ((uint32_t)r < reff && idx < m)
             ls_emit(a, R, off + rank[r], k[r],
                     permuted ? ls_pay_gather(a, R, j[r]) : ls_pay_region(a, R, off + idx, j[r]));
     }
+}
+
+__global__ __launch_bounds__(kBT, 4) void k_ls_bucket(LsArgs a)
+{
+    __shared__ BkLs sh;
+    const LsRow &R = a.r[blockIdx.y];
+    const uint32_t t = threadIdx.x, bkt = blockIdx.x;
+    if (bkt >= R.B) return;   // a row with fewer buckets than the grid is wide
+    const uint32_t m = R.size[bkt], off = R.start[bkt];
+    for (uint32_t i = t; i <= kBins; i += kBT) sh.bin[i] = 0;
+    for (uint32_t i = t; i < kBW * 256u; i += kBT) (&sh.wc[0][0])[i] = 0;
+    __syncthreads();
+    if (m > kLsCap) {
+        ls_big_bucket(a, R, sh, off, m);
+        return;
+    }
+    // (the common sizes with half the registers: no spills at 128)
+    if (m <= 4u * kBT) ls_bucket<4>(a, R, sh, bkt, off, m);
+    else ls_bucket<kBR>(a, R, sh, bkt, off, m);
 }
 
 struct LsLayout {
@@ -1073,9 +1145,8 @@ LsLayout ls_layout(uint64_t n)
     if (l.B < 2) l.B = 2;
     l.hgt = 0;
     while ((1u << l.hgt) < l.B) l.hgt++;
-    const uint64_t s = align_up((uint64_t)kLsOver * l.B, 64);
-    l.S = (uint32_t)(s < kLsMaxS ? s : kLsMaxS);
-    l.tiles = (uint32_t)cdiv(n, kTile);
+    l.S = (uint32_t)align_up((uint64_t)kLsOver * l.B, kSB);   // <= kLsMaxS; S <= n
+    l.tiles = (uint32_t)cdiv(n, l.B <= kSmallB ? kTile<kSmallB> : kTile<kLsMaxB>);
     return l;
 }
 
@@ -1085,7 +1156,7 @@ size_t lsort_sample_bytes(uint64_t n)
 {
     if (n <= kSsMaxN || n > kLsMaxN) return 0;
     const LsLayout l = ls_layout(n);
-    return 2 * align_up(l.S * 8, 256) + align_up(l.S * 4, 256) + align_up(kSmP * l.S * 4, 256);
+    return 2 * align_up(l.S * 8, 256) + 2 * align_up(l.S * 4, 256) + align_up((uint64_t)l.S / kSB * l.S * 2, 256);
 }
 
 LsSample lsort_sample_at(uint64_t n, void *p)
@@ -1093,13 +1164,15 @@ LsSample lsort_sample_at(uint64_t n, void *p)
     const LsLayout l = ls_layout(n > kSsMaxN ? n : kSsMaxN + 1);
     uint8_t *q = static_cast<uint8_t *>(p);
     LsSample y;
-    y.raw_k = reinterpret_cast<uint64_t *>(q);
+    y.srt_k = reinterpret_cast<uint64_t *>(q);
     q += align_up(l.S * 8, 256);
     y.smp_k = reinterpret_cast<uint64_t *>(q);
     q += align_up(l.S * 8, 256);
     y.smp_j = reinterpret_cast<uint32_t *>(q);
     q += align_up(l.S * 4, 256);
-    y.rpart = reinterpret_cast<uint32_t *>(q);
+    y.srt_i = reinterpret_cast<uint32_t *>(q);
+    q += align_up(l.S * 4, 256);
+    y.rpart = reinterpret_cast<uint16_t *>(q);
     y.draw = true;
     return y;
 }
@@ -1108,12 +1181,16 @@ size_t lsort_ws_bytes(uint64_t n, uint32_t nsort, uint32_t npart)
 {
     if (n <= kSsMaxN || n > kLsMaxN) return 0;
     const LsLayout l = ls_layout(n);
-    const uint64_t sort = 2 * align_up(l.B * 4, 256) + align_up((uint64_t)l.tiles * l.B * 4, 256) +
-                          2 * align_up(l.S * 8, 256) + align_up(l.S * 4, 256) + align_up(kSmP * l.S * 4, 256) +
+    // (the tables as with the smaller tiles throughout, so that the size does
+    // not fall where the tiles grow)
+    const uint64_t tiles = cdiv(n, kTile<kSmallB>);
+    const uint64_t sort = 2 * align_up(l.B * 4, 256) + align_up(tiles * l.B * 4, 256) +
+                          2 * align_up(l.S * 8, 256) + 2 * align_up(l.S * 4, 256) +
+                          align_up((uint64_t)l.S / kSB * l.S * 2, 256) +
                           align_up(n * 2, 256) +
                           2 * (align_up(n * 8, 256) + align_up(n * 4, 256)) +
                           align_up(n * 4, 256) + align_up(n, 256) + align_up(n * 8, 256);   // payloads
-    const uint64_t part = 2 * align_up((kQ + 1) * 4, 256) + align_up((uint64_t)l.tiles * kQ * 4, 256);
+    const uint64_t part = 2 * align_up((kQ + 1) * 4, 256) + align_up(tiles * kQ * 4, 256);
     const uint64_t wrr = npart ? align_up(sizeof(WrrPlan), 256) + align_up(n * 4, 256) : 0;
     return (size_t)(nsort * sort + npart * part + wrr);
 }
@@ -1170,8 +1247,9 @@ hipError_t lsort_launch(const SortInput &in, const SortJob *jobs, uint32_t njobs
             R.size = reinterpret_cast<uint32_t *>(take(l.B * 4));
             R.start = reinterpret_cast<uint32_t *>(take(l.B * 4));
             R.tcnt = reinterpret_cast<uint32_t *>(take((uint64_t)l.tiles * l.B * 4));
-            R.raw_k = reinterpret_cast<uint64_t *>(take(l.S * 8));
-            R.rpart = reinterpret_cast<uint32_t *>(take(kSmP * l.S * 4));
+            R.srt_k = reinterpret_cast<uint64_t *>(take(l.S * 8));
+            R.srt_i = reinterpret_cast<uint32_t *>(take(l.S * 4));
+            R.rpart = reinterpret_cast<uint16_t *>(take((uint64_t)l.S / kSB * l.S * 2));
             R.smp_k = reinterpret_cast<uint64_t *>(take(l.S * 8));
             R.smp_j = reinterpret_cast<uint32_t *>(take(l.S * 4));
             if (k == SortKind::Budget && sjf && !sjf->draw) {
@@ -1206,7 +1284,8 @@ hipError_t lsort_launch(const SortInput &in, const SortJob *jobs, uint32_t njobs
         R.B = l.B;
         R.S = l.S;
         R.hgt = l.hgt;
-        R.raw_k = sjf->raw_k;
+        R.srt_k = sjf->srt_k;
+        R.srt_i = sjf->srt_i;
         R.rpart = sjf->rpart;
         R.smp_k = sjf->smp_k;
         R.smp_j = sjf->smp_j;
@@ -1214,13 +1293,20 @@ hipError_t lsort_launch(const SortInput &in, const SortJob *jobs, uint32_t njobs
     }
     const uint32_t maxb = a.nsort ? l.B : kQ;
     if (a.nsamp) {
-        hipLaunchKernelGGL(k_ls_gather, dim3(cdiv(l.S, 256), a.nsamp), dim3(256), 0, s, a);
-        hipLaunchKernelGGL(k_ls_sample, dim3(l.S / 64 * kSmP, a.nsamp), dim3(kSmT), 0, s, a);
+        hipLaunchKernelGGL(k_ls_gather, dim3(l.S / kSB, a.nsamp), dim3(kSB), 0, s, a);
+        hipLaunchKernelGGL(k_ls_sample, dim3((uint32_t)(l.S / kSB * cdiv(l.S, kSB * kSmE)), a.nsamp), dim3(kSB), 0,
+                           s, a);
         hipLaunchKernelGGL(k_ls_place, dim3(cdiv(l.S, 256), a.nsamp), dim3(256), 0, s, a);
     }
-    hipLaunchKernelGGL(k_ls_count, dim3(l.tiles, a.nrows), dim3(kTT), 0, s, a);
-    hipLaunchKernelGGL(k_ls_scan, dim3(cdiv(maxb, 64), a.nrows), dim3(kScT), 0, s, a);
-    hipLaunchKernelGGL(k_ls_scatter, dim3(l.tiles, a.nrows), dim3(kTT), 0, s, a);
+    if (l.B <= kSmallB) {
+        hipLaunchKernelGGL(k_ls_count<kSmallB>, dim3(l.tiles, a.nrows), dim3(kTT), 0, s, a);
+        hipLaunchKernelGGL(k_ls_scan<kSmallB>, dim3(cdiv(maxb, 64), a.nrows), dim3(kScT), 0, s, a);
+        hipLaunchKernelGGL(k_ls_scatter<kSmallB>, dim3(l.tiles, a.nrows), dim3(kTT), 0, s, a);
+    } else {
+        hipLaunchKernelGGL(k_ls_count<kLsMaxB>, dim3(l.tiles, a.nrows), dim3(kTT), 0, s, a);
+        hipLaunchKernelGGL(k_ls_scan<kLsMaxB>, dim3(cdiv(maxb, 64), a.nrows), dim3(kScT), 0, s, a);
+        hipLaunchKernelGGL(k_ls_scatter<kLsMaxB>, dim3(l.tiles, a.nrows), dim3(kTT), 0, s, a);
+    }
     if (a.nsort) hipLaunchKernelGGL(k_ls_bucket, dim3(l.B, a.nsort), dim3(kBT), 0, s, a);
     return hipGetLastError();
 }

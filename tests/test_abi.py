@@ -288,3 +288,20 @@ def test_param_struct_layouts_match_the_header(ds, tmp_path):
         assert int(got[cname]) == ctypes.sizeof(cls), cname
         for fname, _ in cls._fields_:
             assert int(got["%s.%s" % (cname, fname)]) == getattr(cls, fname).offset, (cname, fname)
+
+
+def test_workspace_sizes_do_not_fall(ds):
+    # a workspace sized for the largest batch serves every smaller one, also
+    # where a larger batch takes another path
+    edges = [1, 4096, 131072, 131073, 262144, 262145, 425984, 430000, (1 << 20) - 1, 1 << 20, (1 << 20) + 1,
+             3 << 20, 1 << 22, (1 << 22) + 1, 5 << 20, 1 << 24, (1 << 24) + 1]
+    for op in (ds.OP_ORDER, ds.OP_ORDER_MULTI):
+        sizes = [ds.workspace_bytes(op, n) for n in edges]
+        assert sizes == sorted(sizes), (op, sizes)
+    groups = (1, 16, 64, 300, 4096, 4097, 20011, 65536)
+    for G in groups:
+        sizes = [ds.workspace_bytes(ds.OP_CALIBRATE, n, G) for n in edges]
+        assert sizes == sorted(sizes), (G, sizes)
+    for n in edges:
+        sizes = [ds.workspace_bytes(ds.OP_CALIBRATE, n, G) for G in groups]
+        assert sizes == sorted(sizes), (n, sizes)

@@ -128,3 +128,21 @@ def test_aging_places(ds, oracle, n, shares):
     arr = rng.uniform(0.0, 1000.0, n)
     check(ds, oracle, ds.AGING, tier, arr, bud, n_tiers=k, weights=(1,) * k,
           tier_priority=tuple(float(q) for q in range(k)), t_now=1000.0, aging_rate=0.004)
+
+
+# the larger tiles and tables above 2^20, up to the last size before the radix
+# passes and the first one with them
+@pytest.mark.parametrize("n,pols", [(1500001, POLICIES), (4194304, (0, 3)), (4194305, (0, 3))])
+def test_sizes_above_2_20(ds, oracle, n, pols):
+    tier, arr, bud = _batch(n + 3, n)
+    for pol in pols:
+        check(ds, oracle, pol, tier, arr, bud, t_now=10.0, aging_rate=0.1)
+
+
+@pytest.mark.parametrize("pol", POLICIES)
+@pytest.mark.parametrize("pattern", ["ties", "constant", "skewed", "clusters"])
+def test_layouts_above_2_20(ds, oracle, pol, pattern):
+    n = 1100003
+    rng = np.random.default_rng(n + len(pattern))
+    tier, arr, bud = _layout(pattern, n, rng)
+    check(ds, oracle, pol, tier, arr, bud, t_now=100.0, aging_rate=0.01, aging_floor=-np.inf)
