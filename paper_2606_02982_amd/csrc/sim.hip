@@ -234,8 +234,8 @@ struct ListLds {
 // before k0 (FIFO positions below A0 have arrived, total0 requests have been
 // dispatched and carry their tick in tick_of); the pending list is rebuilt
 // from those.
-__device__ void engine_list(const EngineArgs &a, ListLds &L, uint32_t k0 = 0, uint32_t A0 = 0,
-                            uint32_t total0 = 0)
+__device__ __forceinline__ void engine_list(const EngineArgs &a, ListLds &L, uint32_t k0, uint32_t A0,
+                                            uint32_t total0)
 {
     auto &s_w = L.s_w;
     auto &s_hist = L.s_hist;
@@ -649,7 +649,7 @@ struct QueueLds {
 // phases are separated by LDS-only barriers, and each batch's factor
 // updates run on one wave (lane i: the i-th event).
 template <bool kL>
-__device__ void engine_queues(const EngineArgs &a, QueueLds &Q)
+__device__ __forceinline__ void engine_queues(const EngineArgs &a, QueueLds &Q)
 {
     auto &s_head = Q.s_head;
     auto &s_tail = Q.s_tail;
@@ -902,8 +902,8 @@ static_assert(kWin == kTPB && kDirtyMax == kTPB && kPool < kTPB, "a thread per s
 // The class structure of a launch's requests, shared by its SJF runs.
 struct ClassShared {
     const uint32_t *ctl;             // [0]: classes C; [1]: non-zero if an input is out of range
-    const uint32_t *clist;           // request ids by (class, words, FIFO position)
-    const uint32_t *lw, *lf, *lobs;  // words, FIFO position, observed length of each list entry
+    const uint4 *rec;                // the requests by (class, words, FIFO position): words, FIFO position,
+                                     // observed length and request of each list entry, one load for all
     const uint32_t *pos_f, *cls_f;   // list position and class of each FIFO position
     const double *arr_f;             // arrival of each FIFO position
     const uint32_t *cstart;          // first list position of each class, then n
@@ -961,7 +961,7 @@ __device__ __forceinline__ uint64_t ld_relaxed64(const uint64_t *p)
 
 // Ascending bitonic sort of N (a power of two, at most 2 kTPB) pairs with two
 // payloads, in LDS, by the whole block.
-__device__ void bitonic(uint64_t *k, uint32_t *j, uint32_t *v, uint32_t *u, uint32_t N)
+__device__ __forceinline__ void bitonic(uint64_t *k, uint32_t *j, uint32_t *v, uint32_t *u, uint32_t N)
 {
     const uint32_t t = threadIdx.x;
     for (uint32_t size = 2; size <= N; size <<= 1) {
@@ -991,7 +991,7 @@ __device__ void bitonic(uint64_t *k, uint32_t *j, uint32_t *v, uint32_t *u, uint
 // Adds class c to the touched set. Callers check the count before each
 // insertion, so with at most kTPB threads inserting at once the table never
 // fills; past kDirtyMax members the set overflows (the next tick rebuilds).
-__device__ void mark_dirty(uint32_t c, ClassLds &S)
+__device__ __forceinline__ void mark_dirty(uint32_t c, ClassLds &S)
 {
     if (*(volatile uint32_t *)&S.cnt[0] >= kDirtyMax) {
         S.cnt[1] = 1;
@@ -1026,14 +1026,14 @@ __device__ __forceinline__ bool is_dirty(uint32_t c, const ClassLds &S)
 // and that member's list position H, all ones if it has none; the class's
 // head moves up to that member. ok turns false if the class breaks the
 // conditions of its static order.
-__device__ void class_key(const EngineArgs &a, const ClassShared &cs, uint32_t c, uint64_t &K, uint32_t &J,
-                          uint32_t &H, bool &ok)
+__device__ __forceinline__ void class_key(const EngineArgs &a, const ClassShared &cs, uint32_t c, uint64_t &K,
+                                          uint32_t &J, uint32_t &H, bool &ok)
 {
     const uint32_t b0 = cs.cstart[c], e = cs.cstart[c + 1];
     const double tb = cs.ctb[c], s = cs.cs[c];
     const double B = a.state[cs.cg[c]];
     const uint32_t h0 = ld_relaxed(&a.cls_head[c]);
-    const double wmax = (double)cs.lw[e > b0 ? e - 1 : b0];
+    const double wmax = (double)cs.rec[e > b0 ? e - 1 : b0].x;
     uint32_t p = e;
     if (h0 < e) {
         uint32_t wi = h0 >> 6;
@@ -1061,19 +1061,20 @@ __device__ void class_key(const EngineArgs &a, const ClassShared &cs, uint32_t c
         J = kNone;
         return;
     }
-    const double wd = (double)cs.lw[p];
+    const uint4 head = cs.rec[p];
+    const double wd = (double)head.x;
     double b = E * (1.0 + wd / a.f_ref);
     b = wd + b;
     K = ordered_bits(b);
-    J = cs.lf[p];
+    J = head.y;
 }
 
 // (TK, TJ) with exactly `need` of the C pairs (kk, kj) at or below it, need
 // at most the number of finite pairs: an MSD radix select over the 96-bit
 // pair, a byte per pass, until the bucket of the need-th pair is exactly
 // what remains to select.
-__device__ void select_pairs(const uint64_t *kk, const uint32_t *kj, uint32_t C, uint32_t need, uint64_t &TK,
-                             uint32_t &TJ, ClassLds &S)
+__device__ __forceinline__ void select_pairs(const uint64_t *kk, const uint32_t *kj, uint32_t C, uint32_t need,
+                                             uint64_t &TK, uint32_t &TJ, ClassLds &S)
 {
     uint64_t mK = 0;
     uint32_t mJ = 0;
@@ -1175,7 +1176,7 @@ __device__ __forceinline__ uint32_t rank_in(const uint64_t *k, const uint32_t *j
 // computation tightens its class's head bound with a plain store, done by
 // the next tick's first barrier. A dispatch does not move head bounds (a
 // bound below the first pending member stays valid); it touches the class.
-__device__ Resume engine_class(const EngineArgs &a, const ClassShared &cs, ClassLds &S)
+__device__ __forceinline__ Resume engine_class(const EngineArgs &a, const ClassShared &cs, ClassLds &S)
 {
     const uint32_t tid = threadIdx.x, lane = (uint32_t)lane_id(), w = tid >> 6;
     const uint32_t n = a.n, batch = a.batch;
@@ -1407,7 +1408,8 @@ __device__ Resume engine_class(const EngineArgs &a, const ClassShared &cs, Class
             if (act && hl < got) {
                 // written by lanes of this wave above (LDS is in order per wave)
                 const uint32_t p = S.wpos[r][hl];
-                const uint32_t words = cs.lw[p], J = cs.lf[p], id = cs.clist[p], obs = cs.lobs[p];
+                const uint4 v = cs.rec[p];
+                const uint32_t words = v.x, J = v.y, obs = v.z, id = v.w;
                 const double wd = (double)words;
                 const double F = 1.0 + wd / a.f_ref;
                 double b = E * F;
@@ -1504,11 +1506,588 @@ __device__ Resume engine_class(const EngineArgs &a, const ClassShared &cs, Class
     return Resume{a.n_ticks, A, total};
 }
 
-// LDS of the three engines (a run uses one at a time).
+// ---- SJF on class lists, every class in registers ----------------------------
+//
+// The class lists as above, for up to kDirC classes and kDirN requests: each
+// thread owns the classes tid, tid + kTPB, ... and keeps their keys and
+// constants in registers, and the pending bitmap, the head bounds and the
+// factors are in LDS, so that no pool has to be kept in order and what a tick
+// still reads from global memory one after the other is the words of moved
+// heads and the requests of the windows. A tick:
+//   * arrivals (loaded a tick ahead) set their bits, pull their class's head
+//     bound back and flag the class;
+//   * the owners of flagged classes, and of those whose group's factor moved
+//     in the last batch, recompute their keys;
+//   * the classes at or below tau are gathered, at least m of them (or all
+//     that have a key) and at most kDirCand; tau moves by a radix select over
+//     the registers' keys when the count leaves that range, and comes down to
+//     the kDirAim-th key when the gathered ones grow past kDirHigh;
+//   * the m best of them are ranked by counting and their windows taken as
+//     above; the candidates are ranked, and one wave dispatches them and
+//     updates the factors while another stores the results.
+// Any tau gives the same result: the gathered classes hold every class among
+// the m best, and no other class is used.
+//
+// A tick is a chain of dependent LDS and global reads, barriers and
+// arithmetic; nothing in it is bound by a rate. 65,536 requests of 256
+// classes, 2,064 ticks of 32 (one block): 32.6 ms on the pool engine above,
+// of which the pool's upkeep was 26%, the touched classes' keys 16% and the
+// windows 22%; 13.7 ms here (keys 12%, gathering and ranking 26%, windows
+// 27%, candidates 17%, factors 13%). With 4,096 classes 25.8 ms and 24.5 ms.
+constexpr uint32_t kDirC = 4096;         // classes
+constexpr uint32_t kDirN = 1u << 18;     // requests (the bitmap's words in LDS)
+constexpr uint32_t kDirCand = 128;       // gathered classes: two per lane
+constexpr uint32_t kDirHigh = 64, kDirAim = 48;   // (96 and 64: 14.3 ms for 13.7)
+static_assert(kDirAim >= kClsMaxBatch && kDirAim <= kDirHigh && kDirHigh <= kDirCand, "tau keeps a batch's classes");
+
+struct DirectLds {
+    uint64_t elig[kDirN / 64];           // pending bitmap over the class lists
+    double B[kDirC];                     // each group's factor, at its first class
+    uint32_t moved[kDirC];               // tick count at which that factor last moved
+    uint32_t head[kDirC];                // a position at or before the class's first pending member
+    uint8_t flag[kDirC];                 // arrivals or dispatches since the last key
+    struct {                             // gathered classes
+        uint64_t k[kDirCand];
+        double E[kDirCand], TS[kDirCand];
+        uint32_t j[kDirCand], c[kDirCand], h[kDirCand], e[kDirCand], gf[kDirCand];
+    } c;
+    struct {                             // window candidates
+        uint64_t k[kWin];
+        double x[kWin];                  // B-free estimate
+        uint32_t j[kWin], id[kWin], obs[kWin], p[kWin], c[kWin], gf[kWin];
+    } w;
+    uint32_t sel[kClsMaxBatch];          // gathered class of each rank
+    uint32_t pick[kClsMaxBatch];         // window candidate of each dispatch place
+    double t2[kClsMaxBatch];             // alpha x its Eq. (6) ratio
+    uint64_t tk;                         // a lower tau, and its FIFO position
+    uint32_t tj, lower;
+    uint32_t aw[2][kNW];                 // arrivals per wave
+    uint32_t gathered[2], cand[2];       // counters, by the parity of the tick
+    uint32_t fail, sw[kNW], hist[256], bin[3];
+};
+
+// Ranks of the len pairs (k, j) by the whole block, 16 lanes to a pair (the
+// waves holding all pairs and counting by ballots took as long): f(i, rank)
+// on one lane.
+template <typename F>
+__device__ __forceinline__ void rank_small(const uint64_t *k, const uint32_t *j, uint32_t len, F &&f)
+{
+    const uint32_t part = threadIdx.x & 15u;
+    for (uint32_t i0 = 0; i0 < len; i0 += kTPB / 16) {
+        const uint32_t i = i0 + (threadIdx.x >> 4);
+        const uint64_t K = i < len ? k[i] : 0ull;
+        const uint32_t J = i < len ? j[i] : 0u;
+        uint32_t r = 0;
+        for (uint32_t u0 = 0; u0 < len; u0 += 64) {
+            uint64_t ku[4];
+            uint32_t ju[4];
+#pragma unroll
+            for (uint32_t v = 0; v < 4; v++) {
+                const uint32_t u = u0 + v * 16 + part;
+                ku[v] = u < len ? k[u] : ~0ull;
+                ju[v] = u < len ? j[u] : kNone;
+            }
+#pragma unroll
+            for (uint32_t v = 0; v < 4; v++) r += pair_lt(ku[v], ju[v], K, J) ? 1u : 0u;
+        }
+        r = row_sum_u32(r);
+        if (part == 0 && i < len) f(i, r);
+    }
+}
+
+// Position of the t-th set bit of x (t below its number of set bits).
+__device__ __forceinline__ uint32_t nth_bit(uint64_t x, uint32_t t)
+{
+    uint32_t v = (uint32_t)x, p = 0;
+    uint32_t c = (uint32_t)__popc(v);
+    if (t >= c) {
+        t -= c;
+        v = (uint32_t)(x >> 32);
+        p = 32;
+    }
+#pragma unroll
+    for (uint32_t s = 16; s >= 1; s >>= 1) {
+        c = (uint32_t)__popc(v & ((1u << s) - 1u));
+        if (t >= c) {
+            t -= c;
+            v >>= s;
+            p += s;
+        }
+    }
+    return p;
+}
+
+template <int kPer>
+__device__ __forceinline__ Resume engine_direct(const EngineArgs &a, const ClassShared &cs, DirectLds &S)
+{
+    const uint32_t tid = threadIdx.x, lane = (uint32_t)lane_id(), w = tid >> 6;
+    const uint32_t n = a.n, batch = a.batch;
+    const double oma = 1.0 - a.alpha;
+    const uint32_t C = cs.ctl[0];
+    if (cs.ctl[1] != 0 || C == 0 || C > kPer * kTPB || n > kDirN) return Resume{0, 0, 0};   // uniform
+
+    // F = 1 + words / f_ref; for a power of two the reciprocal and the product
+    // with it are exact, and spare the chain a division
+    const bool pow2 = (__double_as_longlong(a.f_ref) & 0xFFFFFFFFFFFFFll) == 0 && a.f_ref >= 0x1p-64 &&
+                      a.f_ref <= 0x1p64;
+    const double inv = pow2 ? 1.0 / a.f_ref : 0.0;
+    auto length_factor = [&](double words) {
+        const double q = pow2 ? words * inv : words / a.f_ref;
+        return 1.0 + q;
+    };
+    // the thread's classes: end, first class of the group, the key of the
+    // first pending member (list position H, FIFO position J), E = (T_base B)
+    // S_tenant and T_base S_tenant. With one class per thread also the
+    // constants and the member's words and F = 1 + words / f_ref; with more,
+    // these are read again for a flagged class, or the registers run out.
+    constexpr bool kOne = kPer == 1;
+    uint32_t ce[kPer], gf[kPer];
+    uint64_t K[kPer];
+    uint32_t J[kPer], H[kPer];
+    double E[kPer], TS[kPer];
+    double tb1 = 0.0, sc1 = 0.0, wmax1 = 0.0, fmax1 = 0.0, wd1 = 0.0, F1 = 0.0;
+    for (uint32_t i = tid; i < (n + 63u) / 64u; i += kTPB) S.elig[i] = 0;
+    if (tid < 2) {
+        S.gathered[tid] = 0;
+        S.cand[tid] = 0;
+    }
+    if (tid == 0) {
+        S.fail = 0;
+        S.lower = 0;
+    }
+    bool ok = true;
+#pragma unroll
+    for (int q = 0; q < kPer; q++) {
+        const uint32_t c = (uint32_t)q * kTPB + tid;
+        ce[q] = H[q] = gf[q] = 0;
+        E[q] = TS[q] = 0.0;
+        K[q] = ~0ull;
+        J[q] = kNone;
+        if (c < C) {
+            const uint32_t b0 = cs.cstart[c];
+            ce[q] = cs.cstart[c + 1];
+            gf[q] = cs.gfirst[c];
+            const double tb = cs.ctb[c], sc = cs.cs[c], B = a.state[cs.cg[c]];
+            const double wmax = (double)cs.rec[ce[q] > b0 ? ce[q] - 1 : b0].x, fmax = length_factor(wmax);
+            TS[q] = tb * sc;
+            H[q] = ce[q];
+            S.head[c] = ce[q];
+            S.flag[c] = 0;
+            if (gf[q] == c) S.B[c] = B;
+            S.moved[c] = kNone;
+            double e0 = tb * B;
+            e0 = e0 * sc;
+            double top = e0 * fmax;
+            top = wmax + top;
+            if (!(e0 >= 0.0 && top <= kBudgetTop)) ok = false;
+            if constexpr (kOne) {
+                tb1 = tb;
+                sc1 = sc;
+                wmax1 = wmax;
+                fmax1 = fmax;
+            }
+        }
+    }
+    if (__syncthreads_or(!ok)) return Resume{0, 0, 0};
+    uint64_t tK = ~0ull;                      // tau
+    uint32_t tJ = kNone;
+    uint32_t A = 0, P = 0, total = 0;         // FIFO positions arrived, pending, dispatched
+    uint32_t ph = 0, par = 0;                 // ticks with pending requests; arrival counter in use
+    // FIFO position A + tid: arrival, list position, class
+    double na = 0.0;
+    uint32_t npos = 0, ncls = 0;
+    auto fetch = [&]() {
+        const uint32_t j = A + tid;
+        if (j < n) {
+            na = cs.arr_f[j];
+            npos = cs.pos_f[j];
+            ncls = cs.cls_f[j];
+        }
+    };
+    fetch();
+    double t = a.n_ticks ? a.tick_t[0] : 0.0;
+    uint32_t k = 0;
+    for (; k < a.n_ticks; k++) {
+        // 1. arrivals: a prefix of the rest of the FIFO order
+        for (;;) {
+            const bool arrived = A + tid < n && na <= t;
+            const uint32_t wc = (uint32_t)__popcll(__ballot(arrived));
+            if (lane == 0) S.aw[par][w] = wc;
+            if (arrived) {
+                atomicOr((unsigned long long *)&S.elig[npos >> 6], 1ull << (npos & 63u));
+                atomicMin(&S.head[ncls], npos);
+                S.flag[ncls] = 1;
+            }
+            lds_sync();
+            uint32_t c = 0;
+#pragma unroll
+            for (uint32_t v = 0; v < kNW; v++) c += S.aw[par][v];
+            par ^= 1u;
+            A += c;
+            P += c;
+            if (c) fetch();
+            if (c < kTPB) break;
+        }
+        t = a.tick_t[k + 1 < a.n_ticks ? k + 1 : k];   // the next tick's
+        const uint32_t m = P < batch ? P : batch;
+        if (m == 0) continue;   // uniform; the flags carry over
+        ph++;
+        const uint32_t cur = ph & 1u;
+
+        // 2. keys of the touched classes
+#pragma unroll
+        for (int q = 0; q < kPer; q++) {
+            const uint32_t c = (uint32_t)q * kTPB + tid;
+            if (c < C) {
+                const bool fl = S.flag[c] != 0;
+                if (fl || S.moved[gf[q]] == ph - 1u) {
+                    const double tb = kOne ? tb1 : cs.ctb[c], sc = kOne ? sc1 : cs.cs[c];
+                    const double wmax = kOne ? wmax1 : (double)cs.rec[ce[q] - 1].x;   // a class has a member
+                    const double B = S.B[gf[q]];
+                    uint32_t p = H[q];
+                    if (fl) {
+                        S.flag[c] = 0;
+                        const uint32_t h0 = S.head[c];
+                        p = ce[q];
+                        if (h0 < ce[q]) {
+                            uint32_t wi = h0 >> 6;
+                            uint64_t bits = S.elig[wi] & (~0ull << (h0 & 63u));
+                            for (;;) {
+                                if (bits) {
+                                    p = wi * 64u + (uint32_t)__ffsll((unsigned long long)bits) - 1u;
+                                    break;
+                                }
+                                wi++;
+                                if (wi * 64u >= ce[q]) break;
+                                bits = S.elig[wi];
+                            }
+                            if (p > ce[q]) p = ce[q];
+                            S.head[c] = p;
+                        }
+                    }
+                    double wd = wd1, F = F1;
+                    if (p < ce[q] && (!kOne || p != H[q])) {
+                        const uint4 v = cs.rec[p];
+                        wd = (double)v.x;
+                        J[q] = v.y;
+                        F = length_factor(wd);
+                        if constexpr (kOne) {
+                            wd1 = wd;
+                            F1 = F;
+                        }
+                    }
+                    H[q] = p;
+                    double e0 = tb * B;
+                    e0 = e0 * sc;
+                    E[q] = e0;
+                    const double fmax = kOne ? fmax1 : length_factor(wmax);
+                    double top = e0 * fmax;
+                    top = wmax + top;
+                    if (!(e0 >= 0.0 && top <= kBudgetTop)) S.fail = 1;
+                    K[q] = ~0ull;
+                    if (p < ce[q]) {
+                        double b = e0 * F;
+                        b = wd + b;
+                        K[q] = ordered_bits(b);
+                    }
+                }
+            }
+        }
+
+        // 3. the classes at or below tau
+        uint32_t n1;
+        bool stop = false;
+        for (uint32_t tries = 0;; tries++) {
+            uint32_t add = 0;
+            uint64_t in[kPer];
+#pragma unroll
+            for (int q = 0; q < kPer; q++) {
+                const bool has = K[q] != ~0ull;
+                in[q] = __ballot(has && !pair_lt(tK, tJ, K[q], J[q]));
+                add += (uint32_t)__popcll(in[q]) | ((uint32_t)__popcll(__ballot(has)) << 16);
+            }
+            if (add) {   // uniform in the wave
+                uint32_t base = 0;
+                if (lane == 0) base = atomicAdd(&S.gathered[cur], add) & 0xFFFFu;
+                base = readlane32(base, 0);
+#pragma unroll
+                for (int q = 0; q < kPer; q++) {
+                    const uint32_t s = base + (uint32_t)__popcll(in[q] & lanemask_lt());
+                    base += (uint32_t)__popcll(in[q]);
+                    if (((in[q] >> lane) & 1ull) && s < kDirCand) {
+                        S.c.k[s] = K[q];
+                        S.c.j[s] = J[q];
+                        S.c.c[s] = (uint32_t)q * kTPB + tid;
+                        S.c.h[s] = H[q];
+                        S.c.e[s] = ce[q];
+                        S.c.gf[s] = gf[q];
+                        S.c.E[s] = E[q];
+                        S.c.TS[s] = TS[q];
+                    }
+                }
+            }
+            lds_sync();
+            n1 = S.gathered[cur] & 0xFFFFu;
+            const uint32_t fin = S.gathered[cur] >> 16;
+            // a class breaks the conditions (or tau was just chosen: not
+            // reached, no two pairs are equal)
+            stop = S.fail != 0 || tries > 1;
+            if (stop || (n1 <= kDirCand && n1 >= (m < fin ? m : fin))) break;
+            // a tau with kDirHigh to kDirCand classes at or below it
+            tK = ~0ull;
+            tJ = kNone;
+            if (fin > kDirCand) {
+                uint64_t pK = 0, mK = 0;
+                uint32_t pJ = 0, mJ = 0, under = 0;
+                for (int d = 11; d >= 0; d--) {
+                    if (tid < 256) S.hist[tid] = 0;
+                    lds_sync();
+#pragma unroll
+                    for (int q = 0; q < kPer; q++)
+                        if (K[q] != ~0ull && (K[q] & mK) == pK && (J[q] & mJ) == pJ)
+                            atomicAdd(&S.hist[pair_digit(K[q], J[q], d)], 1u);
+                    lds_sync();
+                    const uint32_t x = tid < 256 ? S.hist[tid] : 0u;
+                    uint32_t tot;
+                    const uint32_t ex = under + lds_scan(x, S.sw, tot);
+                    if (tid < 256 && ex < kDirHigh && kDirHigh <= ex + x) {
+                        S.bin[0] = tid;
+                        S.bin[1] = ex;
+                        S.bin[2] = x;
+                    }
+                    lds_sync();
+                    const uint32_t b = S.bin[0], upto = S.bin[1] + S.bin[2];
+                    under = S.bin[1];
+                    if (d >= 4) {
+                        pK |= (uint64_t)b << (8 * (d - 4));
+                        mK |= 0xFFull << (8 * (d - 4));
+                    } else {
+                        pJ |= b << (8 * d);
+                        mJ |= 0xFFu << (8 * d);
+                    }
+                    if (upto <= kDirCand) break;
+                }
+                tK = pK | ~mK;
+                tJ = pJ | ~mJ;
+            }
+            lds_sync();
+            if (tid == 0) S.gathered[cur] = 0;
+            lds_sync();
+        }
+        if (stop) break;
+        if (tid == 0) {
+            // the next tick's counters (nobody uses them before its barriers)
+            S.gathered[cur ^ 1u] = 0;
+            S.cand[cur ^ 1u] = 0;
+        }
+        const uint32_t R = m < n1 ? m : n1;
+        rank_small(S.c.k, S.c.j, n1, [&](uint32_t i, uint32_t r) {
+            if (r < m) S.sel[r] = i;
+            if (n1 > kDirHigh && r == kDirAim - 1u) {
+                S.tk = S.c.k[i];
+                S.tj = S.c.j[i];
+            }
+        });
+        lds_sync();
+        if (n1 > kDirHigh) {
+            tK = S.tk;
+            tJ = S.tj;
+        }
+
+        // 4. the windows of the m best classes, two per wave (a half-wave
+        //    each), as in the pool engine (eight lanes each, in rounds, took
+        //    14.2 ms: a second round is another read of global memory)
+        {
+            const uint32_t half = lane >> 5, hl = lane & 31u, r = w + kNW * half;
+            const bool act = r < R;
+            uint32_t cl = 0, gw = 0, h = 0, e = 0, want = 0;
+            double E0 = 0.0, TS = 0.0;
+            if (act) {
+                const uint32_t ci = S.sel[r];
+                cl = S.c.c[ci];
+                gw = S.c.gf[ci];
+                h = S.c.h[ci];
+                e = S.c.e[ci];
+                E0 = S.c.E[ci];
+                TS = S.c.TS[ci];
+                want = m - r;
+            }
+            uint64_t mk = ~0ull;
+            uint32_t mj = kNone;
+            if (R == m) {
+                const uint32_t im = S.sel[m - 1];
+                mk = S.c.k[im];
+                mj = S.c.j[im];
+            }
+            // the window's hl-th member: from the 64 list positions at h where
+            // they hold it, else 32 bitmap words at a time
+            uint32_t got = 0, p = 0;
+            uint64_t run = 0;
+            if (act) {
+                const uint32_t wi = h >> 6, sh = h & 63u;
+                run = S.elig[wi] >> sh;
+                if (sh && (wi + 1) * 64u < e) run |= S.elig[wi + 1] << (64u - sh);
+                if (e - h < 64) run &= (1ull << (e - h)) - 1ull;
+                got = (uint32_t)__popcll(run);
+            }
+            if (!__any(got < want && h + 64u < e)) {
+                got = got < want ? got : want;
+                p = h + nth_bit(run, hl);
+            } else {
+                got = 0;
+                for (uint32_t wb = h >> 6;; wb += 32) {
+                    const bool need = act && got < want && wb * 64u < e;
+                    if (!__any(need)) break;
+                    const uint32_t wi = wb + hl;
+                    uint64_t bits = 0;
+                    if (need && wi * 64u < e) {
+                        bits = S.elig[wi];
+                        if (wi == (h >> 6)) bits &= ~0ull << (h & 63u);
+                        const uint32_t below = e - wi * 64u;
+                        if (below < 64) bits &= (1ull << below) - 1ull;
+                    }
+                    const uint32_t cnt = (uint32_t)__popcll(bits);
+                    const uint32_t scan = wave_incl_scan_dpp(cnt);
+                    const uint32_t lo = readlane32(scan, 31), hi = readlane32(scan, 63);
+                    const uint32_t incl = half ? scan - lo : scan, tot = half ? hi - lo : lo;
+                    // the word of member hl: the first whose inclusive count passes it
+                    uint32_t at = 0;
+                    const uint32_t tgt = hl - got;   // used for got <= hl < got + tot
+#pragma unroll
+                    for (uint32_t s = 16; s >= 1; s >>= 1) {
+                        const uint32_t v = (uint32_t)__shfl((int)incl, (int)((half << 5) + at + s - 1u), 64);
+                        if (v <= tgt) at += s;
+                    }
+                    const int src = (int)((half << 5) + at);
+                    const uint64_t wbits = (uint64_t)(uint32_t)__shfl((int)(uint32_t)bits, src, 64) |
+                                           ((uint64_t)(uint32_t)__shfl((int)(uint32_t)(bits >> 32), src, 64) << 32);
+                    const uint32_t wex = (uint32_t)__shfl((int)(incl - cnt), src, 64);
+                    if (need && hl >= got && hl < got + tot) p = (wb + at) * 64u + nth_bit(wbits, tgt - wex);
+                    got = got + tot < want ? got + tot : want;
+                }
+            }
+            bool keep = false;
+            uint64_t Kw = 0;
+            uint32_t Jw = 0, id = 0, obs = 0;
+            double x = 0.0;
+            if (act && hl < got) {
+                const uint4 v = cs.rec[p];
+                Jw = v.y;
+                obs = v.z;
+                id = v.w;
+                const double wv = (double)v.x;
+                const double Fw = length_factor(wv);
+                double b = E0 * Fw;
+                b = wv + b;
+                Kw = ordered_bits(b);
+                x = TS * Fw;
+                keep = hl == 0 || !pair_lt(mk, mj, Kw, Jw);
+            }
+            const uint64_t kb = __ballot(keep);
+            if (kb) {
+                uint32_t base = 0;
+                if (lane == 0) base = atomicAdd(&S.cand[cur], (uint32_t)__popcll(kb));
+                base = readlane32(base, 0);
+                if (keep) {
+                    const uint32_t s = base + (uint32_t)__popcll(kb & lanemask_lt());
+                    S.w.k[s] = Kw;
+                    S.w.j[s] = Jw;
+                    S.w.x[s] = x;
+                    S.w.id[s] = id;
+                    S.w.obs[s] = obs;
+                    S.w.p[s] = p;
+                    S.w.c[s] = cl;
+                    S.w.gf[s] = gw;
+                }
+            }
+        }
+        lds_sync();
+        const uint32_t nc = S.cand[cur];
+        if (nc < m) break;   // not reached: the windows hold the first m
+        if (nc <= 128) {
+            rank_small(S.w.k, S.w.j, nc, [&](uint32_t i, uint32_t r) {
+                if (r < m) S.pick[r] = i;
+            });
+        } else {
+            for (uint32_t i = w; i < nc; i += kNW) {
+                const uint32_t r = rank_in(S.w.k, S.w.j, nc, S.w.k[i], S.w.j[i], m);
+                if (lane == 0 && r < m) S.pick[r] = i;
+            }
+        }
+        lds_sync();
+
+        // the next arrivals are in: waited for here, so that the next tick does
+        // not wait for the stores below as well
+        asm volatile("" : "+v"(na), "+v"(npos), "+v"(ncls), "+v"(t));
+        // 5. the last wave stores the batch; the first clears its bits, flags
+        //    its classes and runs Eq. (5) with the ratio of Eq. (6) (lane i:
+        //    the batch's i-th event): each group's first event walks that
+        //    group's events in dispatch order
+        if (w == kNW - 1 && lane < m) {
+            const uint32_t id = S.w.id[S.pick[lane]];
+            if (total + lane < n) a.seq[total + lane] = id;
+            a.tick_of[id] = (int32_t)k;
+        }
+        if (w == 0) {
+            uint32_t g = kNone;
+            double c = 0.0;
+            uint32_t use = 0;
+            if (lane < m) {
+                const uint32_t i = S.pick[lane], p = S.w.p[i];
+                const double x = S.w.x[i], o = (double)S.w.obs[i];
+                g = S.w.gf[i];
+                S.flag[S.w.c[i]] = 1;
+                atomicAnd((unsigned long long *)&S.elig[p >> 6], ~(1ull << (p & 63u)));
+                c = S.B[g];
+                use = isfinite(x) && x > 0.0 ? 1u : 0u;
+                S.t2[lane] = use ? a.alpha * (o / x) : 0.0;
+            }
+            const uint64_t same = same_group_lanes(g, m, C);
+            const bool lead = lane < m && (same & lanemask_lt()) == 0;
+            const uint64_t used = __ballot(use != 0);
+            uint64_t bits = lead ? same & used : 0ull;
+            const bool moves = bits != 0ull;
+            // four events' terms in flight (LDS is in order per wave)
+            while (bits) {
+                double v[4];
+                bool has[4];
+#pragma unroll
+                for (int u = 0; u < 4; u++) {
+                    has[u] = bits != 0ull;
+                    v[u] = S.t2[has[u] ? __ffsll((unsigned long long)bits) - 1 : 0];
+                    bits &= bits - 1ull;
+                }
+#pragma unroll
+                for (int u = 0; u < 4; u++) {
+                    const double t1 = oma * c;
+                    c = has[u] ? t1 + v[u] : c;
+                }
+            }
+            if (moves) {
+                S.B[g] = c;
+                S.moved[g] = ph;
+            }
+        }
+        P -= m;
+        total += m;
+    }
+    if (tid == 0) a.n_dispatched[0] = total;
+    // the factors go back to the state array
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kPer; q++) {
+        const uint32_t c = (uint32_t)q * kTPB + tid;
+        if (c < C && gf[q] == c) a.state[cs.cg[c]] = S.B[c];
+    }
+    return Resume{k, A, total};
+}
+
+// LDS of the four engines (a run uses one at a time).
 union EngineLds {
     ListLds l;
     QueueLds q;
     ClassLds c;
+    DirectLds d;
 };
 
 // One workgroup per run: the queue engine where the run has its tier runs,
@@ -1519,13 +2098,20 @@ __device__ __forceinline__ void engine_run(const EngineArgs &a, const ClassShare
     if (a.rpos) {
         if (a.batch <= kQLdsBatch && a.n_groups <= kQLdsGroups) engine_queues<true>(a, lds.q);
         else engine_queues<false>(a, lds.q);
-    } else if (a.cls_head) {
-        const Resume r = engine_class(a, cs, lds.c);
-        __syncthreads();
-        if (r.k < a.n_ticks) engine_list(a, lds.l, r.k, r.A, r.total);
-    } else {
-        engine_list(a, lds.l);
+        return;
     }
+    Resume r = {0, 0, 0};
+    if (a.cls_head) {
+        // the direct engine up to kDirC classes and kDirN requests, the pool
+        // engine above
+        const uint32_t C = a.n <= kDirN ? cs.ctl[0] : kNone;
+        r = C <= kTPB    ? engine_direct<1>(a, cs, lds.d)
+            : C <= kDirC ? engine_direct<kDirC / kTPB>(a, cs, lds.d)
+                         : engine_class(a, cs, lds.c);
+        if (r.k >= a.n_ticks) return;
+        __syncthreads();
+    }
+    engine_list(a, lds.l, r.k, r.A, r.total);
 }
 
 static_assert(sizeof(EngineBatch) + sizeof(ClassShared) <= 4096, "kernel arguments within 4 KB");
@@ -1556,9 +2142,10 @@ struct ClassBuild {
     const uint32_t *fifo, *counts, *tenant, *group, *observed;
     const uint8_t *category;
     const double *arrival, *t_base, *s_tenant;
-    uint32_t *ctl, *fpos, *clist, *lpos, *lw, *lf, *lobs, *pos_f, *cls_f, *cls_pos, *cstart, *cg, *gfirst,
+    uint32_t *ctl, *fpos, *clist, *lpos, *pos_f, *cls_f, *cls_pos, *cstart, *cg, *gfirst,
         *gend, *bcnt;
     double *wkey, *ckey, *arr_f, *ctb, *cs;
+    uint4 *rec;
 };
 
 // FIFO position of each request; the two keys of the class sort (words,
@@ -1589,9 +2176,7 @@ __global__ __launch_bounds__(kTPB) void k_cls_mark(const ClassBuild b)
     if (p < b.n) {
         const uint32_t id = b.clist[p];
         b.lpos[id] = p;
-        b.lw[p] = b.counts[id];
-        b.lf[p] = b.fpos[id];
-        b.lobs[p] = b.observed[id];
+        b.rec[p] = make_uint4(b.counts[id], b.fpos[id], b.observed[id], id);
         first = p == 0 || b.ckey[id] != b.ckey[b.clist[p - 1]];
     }
     const uint32_t c = (uint32_t)__syncthreads_count(first);
@@ -1740,11 +2325,11 @@ uint32_t grid_for(uint64_t n)
 
 constexpr uint64_t kCandBytes = (uint64_t)kMaxQ * kSimMaxBatch * (8 + 4 + 4);
 
-// The class structure: 14 arrays of n words (cstart has n + 1), 5 of n
-// doubles, the block counts and the control words.
+// The class structure: 10 arrays of n words (cstart has n + 1), 5 of n
+// doubles, the entries of 4 words, the block counts and the control words.
 uint64_t cls_shared_bytes(uint64_t n)
 {
-    return 13 * align_up(n * 4, 256) + align_up((n + 1) * 4, 256) + 5 * align_up(n * 8, 256) +
+    return 9 * align_up(n * 4, 256) + align_up(n * 16, 256) + align_up((n + 1) * 4, 256) + 5 * align_up(n * 8, 256) +
            align_up((n / kTPB + 1) * 4, 256) + 256;
 }
 
@@ -1845,9 +2430,10 @@ hipError_t sim_launch(const SimArgs *runs, uint32_t n_runs, void *ws, uint32_t *
     cb.fpos = take32(n);
     cb.clist = take32(n);
     cb.lpos = take32(n);
-    cb.lw = take32(n);
-    cb.lf = take32(n);
-    cb.lobs = take32(n);
+    // the class lists' entries; their first words hold the requests by (words,
+    // FIFO position) between the two sorts before them
+    cb.rec = reinterpret_cast<uint4 *>(take((uint64_t)n * 16));
+    uint32_t *seq_words = reinterpret_cast<uint32_t *>(cb.rec);
     cb.pos_f = take32(n);
     cb.cls_f = take32(n);
     cb.cls_pos = take32(n);
@@ -1855,14 +2441,13 @@ hipError_t sim_launch(const SimArgs *runs, uint32_t n_runs, void *ws, uint32_t *
     cb.cg = take32(n);
     cb.gfirst = take32(n);
     cb.gend = take32(n);
-    uint32_t *seq_words = take32(n);   // the requests by (words, FIFO position)
     cb.bcnt = take32(n / kTPB + 1);
     cb.wkey = take64(n);
     cb.ckey = take64(n);
     cb.arr_f = take64(n);
     cb.ctb = take64(n);
     cb.cs = take64(n);
-    const ClassShared cshared = {cb.ctl, cb.clist, cb.lw, cb.lf, cb.lobs, cb.pos_f, cb.cls_f, cb.arr_f,
+    const ClassShared cshared = {cb.ctl, cb.rec, cb.pos_f, cb.cls_f, cb.arr_f,
                                  cb.cstart, cb.ctb, cb.cs, cb.cg, cb.gfirst, cb.gend};
     EngineArgs *staged = reinterpret_cast<EngineArgs *>(take((uint64_t)n_runs * sizeof(EngineArgs)));
     // the runs' arguments, built here and launched chunk by chunk below

@@ -372,3 +372,21 @@ def test_queue_engine_tiers_and_batches(ds, oracle, policy):
         w = tuple(1 + (q * 7) % 5 for q in range(tiers))
         both(ds, oracle, policy, ticks=ticks, batch=batch, alpha=0.1, weights=w, tier_priority=prio,
              aging_rate=0.4, **x)
+
+
+@pytest.mark.parametrize("classes,n,f_ref", [(1023, 5000, 1024.0), (1024, 5000, 1000.0), (1025, 5000, 1024.0),
+                                             (4096, 9000, 1000.0), (4097, 9000, 1024.0),
+                                             (300, 1 << 18, 1024.0), (300, (1 << 18) + 1, 1000.0)])
+def test_sjf_class_counts(ds, oracle, classes, n, f_ref):
+    """The class and request counts at which SJF's loop changes how it holds
+    the classes, with many equal budgets (few word counts, two tenant scales,
+    more heads at or below the cut than it gathers), and word factors with an
+    exact reciprocal of f_ref and without one."""
+    rng = np.random.default_rng(classes + n)
+    tenant = np.concatenate([np.arange(classes), rng.integers(0, classes, n - classes)]).astype(np.uint32)
+    rng.shuffle(tenant)
+    both(ds, oracle, SJF, ticks=np.linspace(0.01, 1.0, 40 if n > 100000 else 330), batch=32, alpha=0.1, f_ref=f_ref,
+         arrival=np.round(rng.uniform(0, 0.6, n), 3), tier=np.zeros(n, np.uint8),
+         counts=rng.integers(0, 40, n).astype(np.uint32), category=np.zeros(n, np.uint8), tenant=tenant,
+         group=tenant % 97, observed=rng.integers(0, 400, n).astype(np.uint32), t_base=np.array([100.0]),
+         s_tenant=rng.choice([0.5, 1.0], classes), state=np.ones(97))
