@@ -17,7 +17,7 @@ ARCH = "gfx950"
 
 SOURCES = ["api.hip", "characterize.hip", "sort.hip", "calibrate.hip", "score.hip", "order.hip", "stats.hip",
            "sim.hip", "ssort.hip", "calchunk.hip", "agmerge.hip",
-           "lsort.hip"]
+           "lsort.hip", "norder.hip"]
 
 HIP_FLAGS = [
     "--offload-arch=" + ARCH, "-O3", "-std=c++17", "-fPIC", "-Wall",

@@ -108,6 +108,12 @@ size_t ssort_ws_bytes(uint64_t n, uint32_t nsorts);   // 0 above kSsMaxN
 hipError_t ssort_launch(const SortInput &in, const SortJob *jobs, uint32_t nsorts, bool serial,
                         void *ws, hipStream_t s, const SsPartitions *parts = nullptr);
 
+// The orders of at most kNoMaxN requests by counting, in one launch without
+// waits or workspace (perm[p] NULL: not wanted; not Weighted's smooth mode,
+// whose period table this path does not build).
+constexpr uint32_t kNoMaxN = 6144;
+hipError_t norder_launch(const SortInput &in, uint32_t *const perm[5], double *const key[5], hipStream_t s);
+
 // The orders of kSsMaxN < n <= kLsMaxN requests, several in the same
 // launches: sorts (Fifo; Budget, Aging over in.fifo) by (key, position)
 // with sampled splitters, and partitions (Class, Tier over in.fifo) placed

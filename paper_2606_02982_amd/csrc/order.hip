@@ -9,7 +9,8 @@
 //             of the smooth interleaving's period table)
 //   SJF       stable sort of the FIFO sequence by budget
 //   Aging     stable sort of the FIFO sequence by the aged score
-// Up to kSsMaxN requests FIFO, SJF and Aging are sample sorts by the
+// Up to kNoMaxN requests every place is counted in one launch. Up to kSsMaxN
+// requests FIFO, SJF and Aging are sample sorts by the
 // composite key (policy key, arrival, index), all in the same three
 // launches, and the FIFO sort's last launch also places Priority and
 // Weighted. Above that, the FIFO permutation is sorted first (unless the
@@ -139,6 +140,19 @@ hipError_t order_launch(const OrderArgs &a, void *ws, uint32_t *flag, hipStream_
         hipLaunchKernelGGL(k_copy_fifo, dim3(blocks), dim3(256), 0, s, a.fifo_in, a.arrival, n, a.perm[0],
                            a.key[0], wait.clear ? wait.status : nullptr);
         in.wait.clear = false;
+    }
+    // Counting up to 6,144 requests, where it is the faster one for every set
+    // of policies (five orders of 6,144 31 us against 37, of 8,192 about 50
+    // against 40); not with the smooth mode, whose period table the sample
+    // sorts' launches build. A given fifo_in is the order that is counted.
+    // (DS_SERIAL_SORT and DS_NO_WAIT exercise the sorts.)
+    if (n <= kNoMaxN && !a.serial_sort && !wait.no_wait &&
+        !((a.mask & (1u << 2)) && a.wrr_mode == kWrrSmooth)) {
+        uint32_t *perm[5];
+        for (int p = 0; p < 5; p++) perm[p] = a.perm[p];
+        if (a.fifo_in) perm[0] = nullptr;   // copied above
+        if ((a.mask & ~1u) == 0 && !perm[0]) return hipGetLastError();
+        return norder_launch(in, perm, a.key, s);
     }
     if (n <= kSsMaxN) {
         // one batch of sample sorts: FIFO (carrying Priority and Weighted),

@@ -331,3 +331,40 @@ def test_aging_merge_path(ds, oracle, case):
         perm, key = ds.order(4, t, a, key=True, params=params, validate=True)
     assert np.array_equal(host(perm, np.uint32), w_perm)
     assert np.array_equal(host(key), w_key)
+
+
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 255, 257, 2048, 2049, 4096, 4097, 6143, 6144, 6145])
+@pytest.mark.parametrize("case", ["random", "ties", "constant", "wide"])
+def test_small_batches_counted(ds, oracle, n, case):
+    """Up to 6,144 requests every place is counted in one launch: sizes at the
+    ends of its groups, blocks and range, each set of policies, with a given
+    FIFO order and without, against the oracle and the sorts."""
+    rng = np.random.default_rng(n)
+    Q = 16 if case == "wide" else 3
+    tier, arr, bud = _batch(n, n, tiers=Q)
+    if case == "ties":
+        arr = rng.choice([-0.0, 0.0, 1.0, 2.0], n)
+        bud = rng.choice([-0.0, 0.0, 7.0, np.inf], n)
+    elif case == "constant":
+        arr[:], bud[:], tier[:] = 5.0, 9.0, 2
+    elif case == "wide":
+        arr = rng.choice([-1.0, 1.0], n) * 10.0 ** rng.uniform(-300, 300, n)
+        bud = rng.choice([-1.0, 1.0], n) * 10.0 ** rng.uniform(-300, 300, n)
+        arr[::7], arr[3::11] = np.inf, -np.inf
+    w, prio = tuple(1 + (3 * q) % 7 for q in range(Q)), tuple(float(q // 2) for q in range(Q))
+    okw = dict(weights=w, tier_priority=prio, aging_rate=0.5, t_now=6.0, aging_floor=-np.inf)
+    want = [oracle.order(p, tier, arr, bud, **okw) for p in POLICIES]
+    stride = oracle.order(6, tier, arr, weights=w, tier_priority=prio)
+    t, a, b = dev(tier), dev(arr), dev(bud)
+    fifo = dev(want[0][0].astype(np.uint32))
+    for mask in range(1, 32):
+        pols = tuple(p for p in POLICIES if (mask >> p) & 1)
+        print("counted n=%d %s policies=%s" % (n, case, pols), flush=True)
+        for kw in ({}, {"fifo": fifo}, {"weighted_mode": "stride"}, {"serial_sort": True}):
+            if "serial_sort" in kw and mask != 31:
+                continue
+            perms, keys = ds.order_multi(pols, t, a, b, keys=True, n_tiers=Q, **okw, **kw)
+            for p in pols:
+                perm, key = stride if p == 2 and "weighted_mode" in kw else want[p]
+                assert np.array_equal(host(perms[p], np.uint32), perm), (p, kw.keys())
+                assert np.array_equal(host(keys[p]), key), (p, kw.keys())
