@@ -107,10 +107,12 @@ typedef enum {
  * (above 65536 groups, and above 4096 with DS_NO_WAIT) and ds_simulate split their work into tiles that wait,
  * each for at most about 0.2 s, on counts published by tiles of smaller
  * index (decoupled look-back); the orders of more than 2^18 and at most
- * 2^22 requests have no such waits (with DS_NO_WAIT at most 2^20). ds_calibrate of at most 64 chunks of
+ * 2^22 requests have no such waits (with DS_NO_WAIT at most 2^20), nor,
+ * without DS_NO_WAIT and outside Weighted's smooth mode, those of at most
+ * 6144. ds_calibrate of at most 64 chunks of
  * 512, 1024 or 2048 events (and at most 16384 chunk-group pairs) runs in one
  * launch whose chunks wait the same way for the maps of the chunks before
- * them. In normal operation no wait runs out (a tile waits only on tiles
+ * them (up to 2048 events are one chunk without DS_NO_WAIT). In normal operation no wait runs out (a tile waits only on tiles
  * that have already started and publish before they wait). If one does:
  *  - in a sample-sort scatter (up to 2^18 requests), the call finishes on
  *    the single-workgroup path instead, with exact results;

@@ -22,7 +22,8 @@
 //                 sorts and scans its sub-tile once, publishes its chunk's
 //                 maps, reads those of the chunks before it (a bounded wait
 //                 for words not yet written), and applies the updates; a
-//                 small launch before it marks the words unwritten.
+//                 small launch before it marks the words unwritten. Up to
+//                 kOneBlock events a single chunk, and no such launch.
 //   large tables:
 //   k_calc_own    per chunk (one block, or one per range of 8192 groups): the
 //                 waves own the groups between them, and each composes its
@@ -1139,6 +1140,11 @@ __global__ __launch_bounds__(kT) void k_calc_apply(CalArgs a)
 // between the stores of a block is needed.
 constexpr uint64_t kUnset = 0x7FF4DEADBEEF0001ull;
 constexpr uint32_t kOneChunks = 64;   // chunks of the one-launch path at most
+// Events that one block takes as a single chunk, without the unset words and
+// their launch. Replays of a graph, chunks of 512 and one block: 500 events
+// 7.8 and 6.2 us, 1,000 10.6 and 7.5, 2,048 11.7 and 9.3 (8 groups); 3,000 12.2
+// and 12.3, 4,096 12.4 and 13.4 (1 group 9.9 and 14.4).
+constexpr uint32_t kOneBlock = 4 * kT;
 constexpr uint32_t kOneR = 16;   // chunk maps per thread loaded at once
 
 __device__ __forceinline__ uint64_t ld_relaxed64(const uint64_t *p)
@@ -1168,6 +1174,7 @@ __global__ __launch_bounds__(kT) void k_calc_one(CalArgs a)
     __shared__ double sv[kG];           // each group's factor (initial, then at the current point)
     __shared__ uint8_t su[kG];          // the group has a usable event so far
     const uint32_t t = threadIdx.x, c = blockIdx.x;
+    if (a.C == 1 && a.clear && a.status && t == 0) *a.status = 0;   // (else by k_calc_unset)
     // the initial factors are read before this block publishes anything: the
     // last block overwrites them only after every other block has published
     for (uint32_t g = t; g < a.G; g += kT) {
@@ -1439,6 +1446,15 @@ hipError_t calc_launch(const uint32_t *group, const double *est, const uint32_t 
     if (one) {
         // one sub-tile per chunk: the words the chunks publish are unset
         // first, then one launch does the rest
+        // (up to kOneBlock events one chunk of them all: nothing is published,
+        // so nothing to unset. DS_NO_WAIT exercises the waits between chunks.)
+        if (n <= kOneBlock && !a.no_wait) {
+            a.C = 1;
+            if (n <= kT) hipLaunchKernelGGL(k_calc_one<1>, dim3(1), dim3(kT), 0, s, a);
+            else if (n <= 2 * kT) hipLaunchKernelGGL(k_calc_one<2>, dim3(1), dim3(kT), 0, s, a);
+            else hipLaunchKernelGGL(k_calc_one<4>, dim3(1), dim3(kT), 0, s, a);
+            return hipGetLastError();
+        }
         const uint32_t nw = (uint32_t)(tb / 8 + (uint64_t)a.C * G);
         const uint32_t fb = (uint32_t)(cdiv(nw, 256) < 256 ? cdiv(nw, 256) : 256);
         hipLaunchKernelGGL(k_calc_unset, dim3(fb), dim3(256), 0, s, reinterpret_cast<uint64_t *>(a.aggA), nw,

@@ -223,3 +223,29 @@ def test_large_tables(ds, oracle, E, G, skew):
             assert np.isnan(got[~kept]).all()
             ok, worst = rel_close(got[kept], want, RTOL)
             assert ok, "%s: worst relative difference %.3g" % (outs, worst)
+
+
+@pytest.mark.parametrize("E", [1, 511, 512, 513, 1024, 1025, 2047, 2048, 2049])
+@pytest.mark.parametrize("G", [1, 9, 4096])
+def test_one_block(ds, oracle, E, G):
+    """Up to 2,048 events one block takes them all: the sizes at which its
+    events per thread change, with events that are skipped, against the oracle
+    (1e-12 relative) and with a wait status left by an earlier call cleared."""
+    print("one block E=%d G=%d" % (E, G), flush=True)
+    rng = np.random.default_rng(E + G)
+    group = rng.integers(0, G, E).astype(np.uint32)
+    est = rng.uniform(1.0, 100.0, E)
+    est[rng.random(E) < 0.1] = 0.0
+    obs = rng.integers(0, 300, E).astype(np.uint32)
+    state = rng.uniform(0.5, 2.0, G)
+    w_st, w_tr = oracle.calibrate(group, est, obs, 0.1, state)
+    ws = ds.workspace(ds.OP_CALIBRATE, E, G)
+    args = dev(group), dev(est), dev(obs), 0.1
+    ds.calibrate(*args, dev(state), ws=ws, no_wait=True)   # every chunk after the first gives up
+    assert (ds.wait_status(ws) != 0) == (E > 512)
+    st, tr = ds.calibrate(*args, dev(state), ws=ws)
+    assert ds.wait_status(ws) == 0
+    ok, worst = rel_close(host(tr), w_tr, RTOL)
+    assert ok, "trace worst relative difference %.3g" % worst
+    ok, worst = rel_close(host(st), w_st, RTOL)
+    assert ok, "state worst relative difference %.3g" % worst
