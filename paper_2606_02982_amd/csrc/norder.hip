@@ -18,9 +18,9 @@
 // Bound by issue, n^2 / 64 row-group steps of some 10 vector and 12 scalar
 // instructions over 1,024 SIMDs. Five orders, calls back to back: 1,024
 // requests 49 us with the sample sorts and 11 here (bound by the host's
-// launches), 4,096 39 and 17.7 (23.3 with two 64-bit comparisons per key),
-// 6,144 37 and 31; 8,192 40 and about 50. FIFO alone: 4,096 23 and 9.3,
-// 6,144 24 and 12.
+// launches), 4,096 39 and 18.0 (23.3 with two 64-bit comparisons per key),
+// 6,144 37 and 32 (the waits behind the masks are 3% of it); 8,192 40 and
+// about 50. FIFO alone: 4,096 23 and 9.2, 6,144 24 and 12.
 #include "common.h"
 #include "kernels.h"
 #include "wrrplan.h"
@@ -64,8 +64,11 @@ __device__ __forceinline__ double no_score(const SortInput &in, double a, double
 // The lanes of two groups whose key is below x, or equal to it where the
 // lane's bit in t is set: the borrow of k - x - t, which the subtractions
 // take and give as wave masks. (Written with comparisons, each key takes two
-// of them, in 64 bits, and two scalar operations to combine them.) A mask is
-// read by a vector instruction two wait states after one wrote it.
+// of them, in 64 bits, and two scalar operations to combine them.) A vector
+// instruction may read a mask two wait states after another one wrote it at the
+// earliest. The compiler keeps that distance for its own instructions, but it
+// does not see the writes in here: the waits at both ends are for a mask it
+// wrote just before and for one it counts or spills just behind.
 __device__ __forceinline__ void below2(uint64_t k0, uint64_t k1, uint64_t x, uint64_t t0, uint64_t t1, uint64_t &m0,
                                        uint64_t &m1)
 {
@@ -76,7 +79,8 @@ __device__ __forceinline__ void below2(uint64_t k0, uint64_t k1, uint64_t x, uin
         "v_subb_co_u32_e64 %[d], %[o1], %[l1], %[xl], %[t1]\n\t"
         "s_nop 0\n\t"
         "v_subb_co_u32_e64 %[d], %[o0], %[h0], %[xh], %[o0]\n\t"
-        "v_subb_co_u32_e64 %[d], %[o1], %[h1], %[xh], %[o1]"
+        "v_subb_co_u32_e64 %[d], %[o1], %[h1], %[xh], %[o1]\n\t"
+        "s_nop 1"
         : [d] "=&v"(d), [o0] "=&s"(o0), [o1] "=&s"(o1)
         : [l0] "v"((uint32_t)k0), [h0] "v"((uint32_t)(k0 >> 32)), [l1] "v"((uint32_t)k1),
           [h1] "v"((uint32_t)(k1 >> 32)), [xl] "v"((uint32_t)x), [xh] "v"((uint32_t)(x >> 32)), [t0] "s"(t0),
@@ -92,7 +96,8 @@ __device__ __forceinline__ void below2(uint32_t k0, uint32_t k1, uint32_t x, uin
     uint64_t o0, o1;
     asm("s_nop 1\n\t"
         "v_subb_co_u32_e64 %[d], %[o0], %[k0], %[x], %[t0]\n\t"
-        "v_subb_co_u32_e64 %[d], %[o1], %[k1], %[x], %[t1]"
+        "v_subb_co_u32_e64 %[d], %[o1], %[k1], %[x], %[t1]\n\t"
+        "s_nop 1"
         : [d] "=&v"(d), [o0] "=&s"(o0), [o1] "=&s"(o1)
         : [k0] "v"(k0), [k1] "v"(k1), [x] "v"(x), [t0] "s"(t0), [t1] "s"(t1));
     m0 = o0;

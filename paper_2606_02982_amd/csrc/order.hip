@@ -141,9 +141,10 @@ hipError_t order_launch(const OrderArgs &a, void *ws, uint32_t *flag, hipStream_
                            a.key[0], wait.clear ? wait.status : nullptr);
         in.wait.clear = false;
     }
-    // Counting up to 6,144 requests, where it is the faster one for every set
-    // of policies (five orders of 6,144 31 us against 37, of 8,192 about 50
-    // against 40); not with the smooth mode, whose period table the sample
+    // Counting up to 6,144 requests, one limit for every set of policies: the
+    // five orders of 6,144 take 32 us against 37, of 8,192 about 50 against 40
+    // (fewer policies cost less, and their line lies higher: FIFO alone takes
+    // 12 us against 24 at 6,144); not with the smooth mode, whose period table the sample
     // sorts' launches build. A given fifo_in is the order that is counted.
     // (DS_SERIAL_SORT and DS_NO_WAIT exercise the sorts.)
     if (n <= kNoMaxN && !a.serial_sort && !wait.no_wait &&
