@@ -616,9 +616,10 @@ __global__ __launch_bounds__(kOT) void k_calc_own(CalArgs a)
             lds_sync();
             for (uint32_t i = ph.lo; i < ph.hi; i += 64) {
                 const bool live = i + lane < ph.hi;
+                // (no entry behind the last lane's: the places of earlier rounds hold maps by now)
                 const uint32_t q = live ? i + lane : ph.lo;
-                const uint32_t m = stm[q], key = m >> 12, g = key * kOW + w, k = m & 127u;
-                double cA = pw64[k], cB = stb[q];
+                const uint32_t m = live ? stm[q] : 0u, key = m >> 12, g = key * kOW + w, k = m & 127u;
+                double cA = pw64[k], cB = live ? stb[q] : 0.0;
                 uint64_t cs = match_bits<kKeyBits>(key, __ballot(live));
                 if (!live) cs = 0;
                 uint32_t rank;

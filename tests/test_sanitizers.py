@@ -7,6 +7,9 @@
    and a driver that exercises every entry point's argument checks and the
    workspace-size and status functions (tests/sanitize/abi_host_checks.c).
    Those calls return before touching a GPU, so both run without one.
+3. The large-table calibration kernels themselves, built for the CPU against a
+   stand-in of the HIP header (tests/sanitize/cpu) with every index checked
+   (tests/sanitize/calchunk_checks.cpp).
 """
 import os
 import shutil
@@ -62,3 +65,13 @@ def test_abi_host_side_under_asan_ubsan(tmp_path):
     # the HIP runtime keeps allocations until exit: leak checks off here
     env = dict(os.environ, ASAN_OPTIONS="detect_leaks=0")
     assert "ok" in run([exe], env=env, timeout=300)
+
+
+def test_calibration_kernels_on_the_cpu(tmp_path):
+    if not shutil.which("g++"):
+        pytest.skip("g++ not available")
+    exe = str(tmp_path / "calchunk_checks")
+    run(["g++", "-std=c++17", "-O1", "-g", "-fsanitize=undefined", "-fno-sanitize-recover=all", "-ffp-contract=off",
+         "-w", "-I" + os.path.join(HERE, "cpu"), "-I" + os.path.join(ROOT, "include"), "-o", exe,
+         os.path.join(HERE, "calchunk_checks.cpp")])
+    assert "ok" in run([exe], timeout=300)
