@@ -808,9 +808,9 @@ __global__ __launch_bounds__(64 * kScanW) void k_calc_scan(CalArgs a)
         sA[w][lane] = agg.a;
         sB[w][lane] = agg.b;
         sU[w][lane] = agg.u;
+        double v = in ? a.state[g] : 0.0;   // (by every wave before the barrier, behind which one overwrites it)
         __syncthreads();
         if (!in) return;
-        double v = a.state[g];
         bool touched = false;
         for (uint32_t q = 0; q < kScanW; q++) {
             if (!sU[q][lane]) continue;
@@ -860,9 +860,9 @@ __global__ __launch_bounds__(64 * kScanW) void k_calc_scan(CalArgs a)
     sA[w][lane] = agg.a;
     sB[w][lane] = agg.b;
     sU[w][lane] = agg.u;
+    double v = in ? a.state[g] : 0.0;   // (before the barrier, as above)
     __syncthreads();
     if (!in) return;
-    double v = a.state[g];
     bool touched = false;
     for (uint32_t q = 0; q < kScanW; q++) {
         if (!sU[q][lane]) continue;

@@ -88,12 +88,51 @@ void chunk(uint32_t n, uint32_t G, uint32_t spread)
     failures += bad != 0;
 }
 
+// The carries of C chunks alone, from given maps of every chunk.
+void scan(uint32_t C, uint32_t G)
+{
+    std::vector<uint32_t> K((size_t)C * G);
+    std::vector<double> B((size_t)C * G), carry((size_t)C * G), state(G), pw(1024), want(G);
+    ds::CalArgs a;
+    memset(&a, 0, sizeof a);
+    a.C = C;
+    a.G = G;
+    a.oma = 0.9;
+    a.aggK = K.data();
+    a.aggB = B.data();
+    a.carry = carry.data();
+    a.state = state.data();
+    a.pw = pw.data();
+    for (uint32_t t = 0; t < 1024; t++) pw[t] = pow(a.oma, (double)(t & 255u) * (double)(1u << (8 * (t >> 8))));
+    for (uint32_t i = 0; i < C * G; i++) {
+        K[i] = (i * 7u) % 5u;
+        B[i] = K[i] ? 0.1 * (double)(i % 13u + 1u) : 0.0;
+    }
+    uint32_t bad = 0;
+    for (uint32_t g = 0; g < G; g++) state[g] = want[g] = 1.0 + g;
+    std::vector<double> wc((size_t)C * G);
+    for (uint32_t c = 0; c < C; c++)
+        for (uint32_t g = 0; g < G; g++) {
+            wc[(size_t)c * G + g] = want[g];
+            if (K[(size_t)c * G + g]) want[g] = pow(a.oma, K[(size_t)c * G + g]) * want[g] + B[(size_t)c * G + g];
+        }
+    hipLaunchKernelGGL(ds::k_calc_scan, dim3((G + 63) / 64), dim3(64 * ds::kScanW), 0, nullptr, a);
+    for (uint32_t i = 0; i < C * G; i++) bad += !close(carry[i], wc[i]);
+    for (uint32_t g = 0; g < G; g++) bad += !close(state[g], want[g]);
+    printf("scan: C %u G %u, last wave %s: %u wrong\n", C, G, emu::last_wave_first ? "first" : "last", bad);
+    fflush(stdout);
+    failures += bad != 0;
+}
+
 }  // namespace
 
 int main()
 {
     for (int order = 0; order < 2; order++) {
         emu::last_wave_first = order != 0;
+        scan(3, 70);
+        scan(200, 64);   // a wave's stretch in registers
+        scan(400, 64);   // and read twice
         chunk(3 * 4096 + 77, 4096, 40);
         chunk(2 * 4096, 4096, 250);
         calibrate("uniform", 9001, 4096, 0.0, 1, true);
