@@ -248,7 +248,8 @@ ds_status ds_characterize_score_noalloc(const uint8_t *text, uint64_t text_bytes
  *  state      device, n_groups double; in: factors before the events (1.0
  *             initially), out: after. Groups without events are unchanged.
  *  trace      device, n_events double, or NULL
- *  ws         workspace of ds_workspace_bytes(DS_OP_CALIBRATE, n_events, n_groups)
+ *  ws         workspace of ds_workspace_bytes(DS_OP_CALIBRATE, n_events, n_groups);
+ *             see there for smaller ones
  */
 ds_status ds_calibrate(const uint32_t *group, const double *est, const uint32_t *observed,
                        uint64_t n_events, double alpha, uint32_t n_groups,
@@ -533,8 +534,13 @@ ds_status ds_simulate_multi(uint32_t n_runs, uint32_t n, const double *arrival, 
 #define DS_READ_BW_WORDS 32768
 ds_status ds_read_bandwidth(const void *buf, uint64_t bytes, uint32_t *xor_out, ds_stream stream);
 
-/* Workspace size for op at size n (prompts, events or requests); n_groups
- * is used by DS_OP_CALIBRATE only. */
+/* Workspace size for op at size n (prompts, events or requests); n_groups is
+ * used by DS_OP_CALIBRATE, DS_OP_ERROR_STATS and (the number of runs)
+ * DS_OP_SIMULATE_MULTI. For ds_calibrate the size falls neither with the events
+ * nor with the groups, so that one workspace serves every smaller call.
+ * ds_calibrate also takes less than this and is then slower: with few groups
+ * (up to 32, and up to 63 just above 2^18 events) no room for 12 bytes per
+ * event, above 4096 groups about 26 bytes per event and 8 per group. */
 size_t ds_workspace_bytes(ds_op op, uint64_t n, uint32_t n_groups);
 
 /* Static description of a status code. */

@@ -163,12 +163,12 @@ ds_status ds_calibrate_ex(const uint32_t *group, const double *est, const uint32
     if (!aligned(group, 4) || !aligned(est, 8) || !aligned(observed, 4) || !aligned(state, 8) ||
         (trace && !aligned(trace, 8)) || (trace_before && !aligned(trace_before, 8)))
         return DS_ERR_ALIGN;
-    ds_status st = check_ws(ws, ws_bytes, ds_workspace_bytes(DS_OP_CALIBRATE, n_events, n_groups));
+    ds_status st = check_ws(ws, ws_bytes, kFlagBytes + cal_need_bytes(n_events, n_groups));
     if (st != DS_OK) return st;
     hipStream_t s = static_cast<hipStream_t>(stream);
     return run_waits(ws, flags, s, [&](uint32_t *flag) {
         return cal_launch(group, est, observed, (uint32_t)n_events, alpha, n_groups, state, trace,
-                          trace_before, after_flag(ws), flag, s, wait_cfg(ws, flags));
+                          trace_before, after_flag(ws), ws_bytes - kFlagBytes, flag, s, wait_cfg(ws, flags));
     });
 }
 

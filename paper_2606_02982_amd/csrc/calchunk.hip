@@ -36,7 +36,7 @@
 //                 factor before chunk c is M(c-1, g) o ... o M(0, g) applied
 //                 to its initial factor (sixteen stretches of chunks composed
 //                 by sixteen waves, then chained in order); writes those
-//                 carries and the final factor.
+//                 carries over the maps' offsets, and the final factor.
 //   k_calc_ev     per event: its chunk's carry through its map; without the
 //                 event, followed by the exact update t1 = (1 - alpha) c,
 //                 t2 = alpha r, c = t1 + t2.
@@ -64,6 +64,9 @@ constexpr uint32_t kSmallTable = 16384;  // C x G at most of the one-launch path
 // 4 groups 19.4 and 27.7 us, 16 groups 24.8 and 27.8, 32 groups 33.8 and 27.1;
 // 524,288 events, 4 groups 30.0 and 30.3, 16 groups 34.1 and 30.4.
 constexpr uint32_t kSmallPair = 8192;
+// C x G at most of k_calc_agg and k_calc_apply with chunks of any length, which
+// a workspace without room for k_calc_own's maps of every event gets.
+constexpr uint32_t kFewTable = 16384;
 constexpr uint32_t kCarryR = 4;          // chunk maps per thread held in registers for the carry
 
 constexpr int kOT = 1024;                // k_calc_own: threads per block
@@ -86,9 +89,8 @@ struct CalArgs {
     double *aggA, *aggB;     // [C][G]: M(c, g) = x -> A x + B; A < 0: no usable event
     uint32_t *aggK;          // large tables instead of aggA: A = (1 - alpha)^K; 0: no usable event
     uint32_t R;              // large tables: ranges of kRangeGroups groups (1: one block per chunk)
-    double *carry;           // [C][G]: factor of g before chunk c
+    double *carry;           // large tables: [C][G]: factor of g before chunk c, in the place of aggB
     double *s0;              // [G] the initial factors (small tables: no k_calc_scan)
-    uint32_t small;          // a small table
     double *state;           // [G] in: before all events, out: after
     double *trace, *trace_before;
     uint32_t *status;        // the call's wait status word, or NULL: set by a wait that runs out
@@ -981,10 +983,9 @@ __global__ __launch_bounds__(kT) void k_calc_apply(CalArgs a)
     __shared__ SubShared<kE> sh;
     __shared__ double trb[kSub];   // trace_before staging (the trace goes to sh.b)
     __shared__ double sv[kG];      // each group's factor at the current point of the chunk
-    __shared__ uint8_t su[kG];     // small tables: the group has a usable event so far
+    __shared__ uint8_t su[kG];     // the group has a usable event so far
     const uint32_t t = threadIdx.x, c = blockIdx.x;
-    // small tables: the carry is the maps of the chunks before this one,
-    // composed in order (tpg threads per group, each over a contiguous range
+    // the carry is the maps of the chunks before this one, composed in order (tpg threads per group, each over a contiguous range
     // of chunks, kCarryR maps loaded at a time, then an ordered tree of
     // shuffles), applied to the initial factor; a chunk without usable
     // events of the group leaves it untouched. The first kCarryR maps are
@@ -992,7 +993,7 @@ __global__ __launch_bounds__(kT) void k_calc_apply(CalArgs a)
     // that both loads are in flight together.
     uint32_t tpg = 1;
     while (tpg < 64 && tpg * 2 * a.G <= (uint32_t)kT) tpg *= 2;
-    const bool quick = a.small && a.G <= (uint32_t)kT / tpg;
+    const bool quick = a.G <= (uint32_t)kT / tpg;
     double cA[kCarryR], cB[kCarryR];
     const uint32_t cjb = (t % tpg) * c / tpg, cje = (t % tpg + 1) * c / tpg;
     if (quick) {
@@ -1007,7 +1008,7 @@ __global__ __launch_bounds__(kT) void k_calc_apply(CalArgs a)
                 cB[r] = a.aggB[(uint64_t)j * a.G + g];
             }
         }
-    } else if (a.small) {
+    } else {
         for (uint32_t g = t; g < a.G; g += kT) {
             double v = a.s0[g];
             bool u = false;
@@ -1022,8 +1023,6 @@ __global__ __launch_bounds__(kT) void k_calc_apply(CalArgs a)
             sv[g] = v;
             su[g] = (uint8_t)u;
         }
-    } else {
-        for (uint32_t g = t; g < a.G; g += kT) sv[g] = a.carry[(uint64_t)c * a.G + g];
     }
     const uint64_t c0 = (uint64_t)c * a.L;
     const uint64_t c1 = c0 + a.L < a.E ? c0 + a.L : a.E;
@@ -1097,7 +1096,7 @@ __global__ __launch_bounds__(kT) void k_calc_apply(CalArgs a)
             const uint32_t g = sub.key[e];
             if (sub.flag[e]) cv = g < a.G ? sv[g] : nan;
             trb[sub.slot[e]] = cv;
-            if (a.small && sub.ok[e]) su[g] = 1;
+            if (sub.ok[e]) su[g] = 1;
             if (sub.ok[e]) {
                 // the exact sequential update
                 const double t1 = a.oma * cv;
@@ -1122,7 +1121,7 @@ __global__ __launch_bounds__(kT) void k_calc_apply(CalArgs a)
         }
         lds_sync();
     }
-    if (a.small && c + 1 == a.C) {
+    if (c + 1 == a.C) {
         // the factors after all events: the groups with a usable event in
         // some chunk (the others keep theirs untouched)
         for (uint32_t g = t; g < a.G; g += kT)
@@ -1367,12 +1366,53 @@ static void chunking(uint64_t n, uint32_t G, uint32_t sub, uint32_t &L, uint32_t
     C = (uint32_t)cdiv(n ? n : 1, L);
 }
 
-// Whether chunks of 512 events make a small table.
-static bool small_table(uint64_t n, uint32_t G)
+// The kernels that take n events of G groups.
+enum class Route { One, Small, Own };
+
+struct CalcPlan {
+    Route route;
+    uint32_t e;      // One: events per thread
+    uint32_t L, C;   // events per chunk, chunks
+};
+
+// few: k_calc_agg and k_calc_apply wherever their table is at most kFewTable.
+static CalcPlan calc_plan(uint64_t n, uint32_t G, bool few)
 {
-    uint32_t L, C;
-    chunking(n, G, kT, L, C);
-    return G <= kG && L == (uint32_t)kT && (uint64_t)C * G <= kSmallPair;
+    CalcPlan p;
+    p.e = one_e(n, G);
+    if (p.e) {
+        p.route = Route::One;
+        p.L = kT * p.e;
+        p.C = (uint32_t)cdiv(n ? n : 1, p.L);
+        return p;
+    }
+    p.route = Route::Small;
+    chunking(n, G, kT, p.L, p.C);
+    const uint64_t entries = (uint64_t)p.C * G;
+    if (G <= kG && ((p.L == (uint32_t)kT && entries <= kSmallPair) || (few && entries <= kFewTable))) return p;
+    p.route = Route::Own;
+    chunking(n, G, kOStep, p.L, p.C);
+    return p;
+}
+
+// Bytes of a table of `entries` maps, and of the other arrays.
+static size_t calc_bytes(Route route, uint64_t entries, uint64_t n, uint32_t G)
+{
+    if (route != Route::Own) return 2 * align_up(entries * 8, 256) + align_up((uint64_t)G * 8, 256);
+    return align_up(entries * 4, 256) + align_up(entries * 8, 256) + align_up(1024 * 8, 256) + align_up(n * 8, 256) +
+           align_up(n * 4, 256);
+}
+
+size_t calc_own_bytes(uint64_t n, uint32_t G)
+{
+    const CalcPlan p = calc_plan(n, G, false);
+    return calc_bytes(p.route, (uint64_t)p.C * G, n, G);
+}
+
+size_t calc_need_bytes(uint64_t n, uint32_t G)
+{
+    const CalcPlan p = calc_plan(n, G, true);
+    return calc_bytes(p.route, (uint64_t)p.C * G, n, G);
 }
 
 // Non-decreasing in n and in G: the tables of the most chunks that any call
@@ -1383,17 +1423,15 @@ size_t calc_ws_bytes(uint64_t n, uint32_t G)
         const uint64_t chunks = cdiv(n ? n : 1, sub), most = (chunks < kMaxChunks ? chunks : kMaxChunks) * g;
         return most < cap ? most : cap;
     };
-    uint64_t entries = table(kT, kMaxTable, G < kG ? G : kG);
-    if (G > kG && entries < table(kOStep, kMaxTableR, G)) entries = table(kOStep, kMaxTableR, G);
-    const size_t base = 3 * align_up(entries * 8, 256) + align_up((uint64_t)G * 8, 256);
-    // the large tables' per-event maps and power tables (k_calc_ev)
-    const bool large = one_e(n, G) == 0 && !small_table(n, G);
-    return large ? base + align_up(1024 * 8, 256) + align_up(n * 8, 256) + align_up(n * 4, 256) : base;
+    const size_t small = calc_bytes(Route::Small, table(kT, kSmallTable, G < kG ? G : kG), n, G < kG ? G : kG);
+    if (calc_plan(n, G, false).route != Route::Own) return small;
+    const size_t own = calc_bytes(Route::Own, table(kOStep, G > kG ? kMaxTableR : kMaxTable, G), n, G);
+    return own > small ? own : small;
 }
 
 hipError_t calc_launch(const uint32_t *group, const double *est, const uint32_t *obs, uint32_t n,
                        double alpha, uint32_t G, double *state, double *trace, double *trace_before,
-                       void *ws, hipStream_t s, WaitCfg wait)
+                       void *ws, size_t ws_bytes, hipStream_t s, WaitCfg wait)
 {
     if (n == 0) return hipSuccess;
     if (G == 0 || G > kCalGroupsChunked) return hipErrorInvalidValue;
@@ -1407,35 +1445,40 @@ hipError_t calc_launch(const uint32_t *group, const double *est, const uint32_t 
     a.oma = 1.0 - alpha;
     // few chunks of one sub-tile each: one launch (after the unset words);
     // else sub-tiles of 512 events when the table of chunk maps stays small
-    // (the carries are then formed in k_calc_apply), else steps of 4096
-    const uint32_t one = one_e(n, G);
-    if (one) {
-        a.L = kT * one;
-        a.C = (uint32_t)cdiv(n, a.L);
-        a.small = 1;
-    } else {
-        a.small = small_table(n, G) ? 1u : 0u;
-        chunking(n, G, a.small ? kT : kOStep, a.L, a.C);
-    }
+    // (the carries are then formed in k_calc_apply), else steps of 4096, which
+    // keep 12 bytes of every event. In few groups the sub-tiles need none of
+    // these, in any number of events, and serve a workspace without the room.
+    const CalcPlan plan = calc_plan(n, G, ws_bytes < calc_own_bytes(n, G));
+    const uint32_t one = plan.e;
+    a.L = plan.L;
+    a.C = plan.C;
+    if (ws_bytes < calc_bytes(plan.route, (uint64_t)a.C * G, n, G)) return hipErrorInvalidValue;
     a.R = G > kG ? (uint32_t)cdiv(G, kRangeGroups) : 1u;
     a.passes = G < 256 ? 1u : 2u;   // keys 0..G fit in 8 or 16 bits
     a.keybits = 1;
     while ((1u << a.keybits) <= G) a.keybits++;
     uint8_t *p = static_cast<uint8_t *>(ws);
-    const uint64_t tb = align_up((uint64_t)a.C * G * 8, 256);
-    a.aggA = reinterpret_cast<double *>(p);
-    a.aggK = reinterpret_cast<uint32_t *>(p);
-    a.aggB = reinterpret_cast<double *>(p + tb);
-    a.carry = reinterpret_cast<double *>(p + 2 * tb);
-    a.s0 = reinterpret_cast<double *>(p + 3 * tb);
-    // per-event maps (large tables): after the other arrays
-    {
-        uint8_t *q = p + 3 * tb + align_up((uint64_t)G * 8, 256);
-        a.pw = reinterpret_cast<double *>(q);
-        q += align_up(1024 * 8, 256);
-        a.xb = reinterpret_cast<double *>(q);
-        q += align_up((uint64_t)n * 8, 256);
-        a.xk = reinterpret_cast<uint32_t *>(q);
+    auto take = [&p](uint64_t bytes) {
+        uint8_t *q = p;
+        p += align_up(bytes, 256);
+        return q;
+    };
+    const uint64_t entries = (uint64_t)a.C * G;
+    a.aggA = nullptr;
+    a.aggK = nullptr;
+    a.carry = a.s0 = a.pw = a.xb = nullptr;
+    a.xk = nullptr;
+    if (plan.route == Route::Own) {
+        a.aggK = reinterpret_cast<uint32_t *>(take(entries * 4));
+        a.aggB = reinterpret_cast<double *>(take(entries * 8));
+        a.carry = a.aggB;   // (each thread of k_calc_scan has read a map when it writes the carry there)
+        a.pw = reinterpret_cast<double *>(take(1024 * 8));
+        a.xb = reinterpret_cast<double *>(take((uint64_t)n * 8));
+        a.xk = reinterpret_cast<uint32_t *>(take((uint64_t)n * 4));
+    } else {
+        a.aggA = reinterpret_cast<double *>(take(entries * 8));
+        a.aggB = reinterpret_cast<double *>(take(entries * 8));
+        a.s0 = reinterpret_cast<double *>(take((uint64_t)G * 8));
     }
     a.state = state;
     a.trace = trace;
@@ -1456,14 +1499,14 @@ hipError_t calc_launch(const uint32_t *group, const double *est, const uint32_t 
             else hipLaunchKernelGGL(k_calc_one<4>, dim3(1), dim3(kT), 0, s, a);
             return hipGetLastError();
         }
-        const uint32_t nw = (uint32_t)(tb / 8 + (uint64_t)a.C * G);
+        const uint32_t nw = (uint32_t)(align_up(entries * 8, 256) / 8 + entries);
         const uint32_t fb = (uint32_t)(cdiv(nw, 256) < 256 ? cdiv(nw, 256) : 256);
         hipLaunchKernelGGL(k_calc_unset, dim3(fb), dim3(256), 0, s, reinterpret_cast<uint64_t *>(a.aggA), nw,
                            a.clear ? a.status : nullptr);
         if (one == 1) hipLaunchKernelGGL(k_calc_one<1>, dim3(a.C), dim3(kT), 0, s, a);
         else if (one == 2) hipLaunchKernelGGL(k_calc_one<2>, dim3(a.C), dim3(kT), 0, s, a);
         else hipLaunchKernelGGL(k_calc_one<4>, dim3(a.C), dim3(kT), 0, s, a);
-    } else if (a.small) {
+    } else if (plan.route == Route::Small) {
         hipLaunchKernelGGL(k_calc_agg<1>, dim3(a.C), dim3(kT), 0, s, a);
         hipLaunchKernelGGL(k_calc_apply<1>, dim3(a.C), dim3(kT), 0, s, a);
     } else {

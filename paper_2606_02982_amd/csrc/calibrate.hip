@@ -1,7 +1,8 @@
 // Stage 2: EMA calibration factors, Eq. (5) with the ratio of Eq. (6), over
 // completion events in completion order, per calibration group. This file
-// serves more than kCalGroupsChunked groups (and the diagnostic DS_NO_WAIT
-// above kCalGroupsLds); up to that, calchunk.hip.
+// serves more than kCalGroupsChunked groups (and above kCalGroupsLds a
+// workspace without room for the chunks, and the diagnostic DS_NO_WAIT); up to
+// that, calchunk.hip.
 //
 // The recurrence c <- (1 - alpha) c + alpha r is, per group, a composition
 // of affine maps x -> a x + b (a = 1 - alpha, b = alpha * obs / est; the
@@ -264,21 +265,30 @@ uint32_t bits_for(uint32_t G)
 
 }  // namespace
 
+// The partition's arrays, with a sort workspace of `sort` bytes.
+static size_t part_bytes(size_t sort, uint64_t n, uint32_t n_groups)
+{
+    const uint64_t T = cdiv(n, kTile);
+    return sort + align_up(n * 4, 256) + align_up((uint64_t)n_groups * 8, 256) + 2 * align_up(T * sizeof(Map), 256);
+}
+
+size_t cal_need_bytes(uint64_t n, uint32_t n_groups)
+{
+    return n_groups <= kCalGroupsLds ? calc_need_bytes(n, n_groups) : part_bytes(sort_ws_bytes(n, 1), n, n_groups);
+}
+
 size_t cal_ws_bytes(uint64_t n, uint32_t n_groups)
 {
-    if (n_groups <= kCalGroupsLds) return calc_ws_bytes(n, n_groups);
-    uint64_t T = cdiv(n, kTile);
+    const size_t chunked = calc_ws_bytes(n, n_groups < kCalGroupsChunked ? n_groups : kCalGroupsChunked);
+    if (n_groups <= kCalGroupsLds) return chunked;
     // (the sort's tiles grow above kSsMaxN keys: its size must not fall there)
     const size_t sort = n > kSsMaxN ? std::max(sort_ws_bytes(n, 1), sort_ws_bytes(kSsMaxN, 1)) : sort_ws_bytes(n, 1);
-    const size_t part = sort + align_up(n * 4, 256) +
-                        align_up((uint64_t)n_groups * 8, 256) + 2 * align_up(T * sizeof(Map), 256);
-    const size_t chunked = n_groups <= kCalGroupsChunked ? calc_ws_bytes(n, n_groups) : 0;
-    return part > chunked ? part : chunked;
+    return std::max(part_bytes(sort, n, n_groups), chunked);
 }
 
 hipError_t cal_launch(const uint32_t *group, const double *est, const uint32_t *obs, uint32_t n,
                       double alpha, uint32_t G, double *state, double *trace, double *trace_before,
-                      void *ws, uint32_t *flag, hipStream_t s, WaitCfg wait)
+                      void *ws, size_t ws_bytes, uint32_t *flag, hipStream_t s, WaitCfg wait)
 {
     if (flag) {
         uint32_t vb = (uint32_t)(cdiv(n, 256) < 1024 ? cdiv(n, 256) : 1024);
@@ -286,10 +296,12 @@ hipError_t cal_launch(const uint32_t *group, const double *est, const uint32_t *
         return hipGetLastError();
     }
     if (n == 0) return hipSuccess;
+    // The chunks where the workspace holds them (1,048,575 events, 20,011 groups
+    // 63 us, with the partition 157), else the partition, which needs less.
     // (DS_NO_WAIT exercises the partition's waits: the chunks above
     // kCalGroupsLds groups wait for nothing)
-    if (G <= kCalGroupsLds || (G <= kCalGroupsChunked && !wait.no_wait))
-        return calc_launch(group, est, obs, n, alpha, G, state, trace, trace_before, ws, s, wait);
+    if (G <= kCalGroupsLds || (G <= kCalGroupsChunked && !wait.no_wait && calc_own_bytes(n, G) <= ws_bytes))
+        return calc_launch(group, est, obs, n, alpha, G, state, trace, trace_before, ws, ws_bytes, s, wait);
     const uint32_t T = (uint32_t)cdiv(n, kTile);
     const uint32_t kb = bits_for(G);
     uint8_t *p = static_cast<uint8_t *>(ws);

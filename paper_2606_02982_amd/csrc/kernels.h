@@ -189,16 +189,19 @@ hipError_t am_partition(const SortInput &in, uint32_t *run_pos, uint32_t *run_st
 // (up to kCalGroupsLds one block holds every group's map in LDS).
 constexpr uint32_t kCalGroupsLds = 4096;
 constexpr uint32_t kCalGroupsChunked = 65536;
-size_t calc_ws_bytes(uint64_t n, uint32_t n_groups);
+size_t calc_ws_bytes(uint64_t n, uint32_t n_groups);     // non-decreasing in both
+size_t calc_own_bytes(uint64_t n, uint32_t n_groups);    // what the fastest way uses
+size_t calc_need_bytes(uint64_t n, uint32_t n_groups);   // what a call has to have
 // wait.status (may be NULL): zeroed by the first kernel when wait.clear, set
 // when a chunk's wait for the maps of the chunks before it runs out.
 hipError_t calc_launch(const uint32_t *group, const double *est, const uint32_t *obs, uint32_t n,
                        double alpha, uint32_t n_groups, double *state, double *trace,
-                       double *trace_before, void *ws, hipStream_t s, WaitCfg wait = {});
-size_t cal_ws_bytes(uint64_t n, uint32_t n_groups);
+                       double *trace_before, void *ws, size_t ws_bytes, hipStream_t s, WaitCfg wait = {});
+size_t cal_ws_bytes(uint64_t n, uint32_t n_groups);      // non-decreasing in both
+size_t cal_need_bytes(uint64_t n, uint32_t n_groups);    // a call with less is refused
 hipError_t cal_launch(const uint32_t *group, const double *est, const uint32_t *obs,
                       uint32_t n, double alpha, uint32_t n_groups, double *state,
-                      double *trace, double *trace_before, void *ws, uint32_t *flag,
+                      double *trace, double *trace_before, void *ws, size_t ws_bytes, uint32_t *flag,
                       hipStream_t s, WaitCfg wait = {});
 
 // ---- stage 3: score --------------------------------------------------------------

@@ -36,7 +36,7 @@ void calibrate(const char *name, uint32_t n, uint32_t G, double share, uint32_t 
     std::vector<char> ws(ds::calc_ws_bytes(n, G) + 256);
     void *w = (void *)(((uintptr_t)ws.data() + 255) & ~(uintptr_t)255);
     if (ds::calc_launch(group.data(), est.data(), obs.data(), n, alpha, G, state.data(), trace.data(),
-                        before ? tb.data() : nullptr, w, nullptr, {}) != hipSuccess)
+                        before ? tb.data() : nullptr, w, ds::calc_ws_bytes(n, G), nullptr, {}) != hipSuccess)
         failures++;
     uint32_t bad = 0;
     for (uint32_t g = 0; g < G; g++) bad += !close(state[g], want[g]);

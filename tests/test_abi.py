@@ -293,12 +293,12 @@ def test_param_struct_layouts_match_the_header(ds, tmp_path):
 def test_workspace_sizes_do_not_fall(ds):
     # a workspace sized for the largest batch serves every smaller one, also
     # where a larger batch takes another path
-    edges = [1, 4096, 131072, 131073, 262144, 262145, 425984, 430000, (1 << 20) - 1, 1 << 20, (1 << 20) + 1,
+    edges = [1, 4096, 100000, 131072, 131073, 262144, 262145, 425984, 430000, (1 << 20) - 1, 1 << 20, (1 << 20) + 1,
              3 << 20, 1 << 22, (1 << 22) + 1, 5 << 20, 1 << 24, (1 << 24) + 1]
     for op in (ds.OP_ORDER, ds.OP_ORDER_MULTI):
         sizes = [ds.workspace_bytes(op, n) for n in edges]
         assert sizes == sorted(sizes), (op, sizes)
-    groups = (1, 16, 64, 300, 4096, 4097, 20011, 65536)
+    groups = (1, 16, 64, 300, 4096, 4097, 20011, 65536, 65537, 100000, 1 << 20)
     for G in groups:
         sizes = [ds.workspace_bytes(ds.OP_CALIBRATE, n, G) for n in edges]
         assert sizes == sorted(sizes), (G, sizes)

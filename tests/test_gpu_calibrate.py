@@ -6,6 +6,7 @@ calibration contract states (1e-12 relative, per event and final state).
 """
 import numpy as np
 import pytest
+import torch
 
 from tests import wl
 from tests.gpu_util import dev, host, rel_close
@@ -249,3 +250,30 @@ def test_one_block(ds, oracle, E, G):
     assert ok, "trace worst relative difference %.3g" % worst
     ok, worst = rel_close(host(st), w_st, RTOL)
     assert ok, "state worst relative difference %.3g" % worst
+
+
+# (events, groups, workspace bytes): what the call took before the chunks of
+# more groups and the maps of every event, which then have no room
+@pytest.mark.parametrize("E,G,nbytes", [(262145, 4, 25856), (500000, 16, 188672), (1 << 22, 1, 12800),
+                                        (262145, 63, 389376), (100000, 4097, 5382912), (100000, 20011, 5510144),
+                                        (65536, 65536, 4767488), (5000, 65536, 2833408), (262145, 65536, 10553856),
+                                        (262145, 300, 5008128), (262145, 4096, 19997440)])
+def test_smaller_workspaces(ds, oracle, E, G, nbytes):
+    """A workspace of that size is taken still, and nothing behind it touched:
+    states and traces against the oracle."""
+    print("workspace E=%d G=%d bytes=%d" % (E, G, nbytes), flush=True)
+    rng = np.random.default_rng(E + G)
+    group = rng.integers(0, G, E).astype(np.uint32)
+    est = rng.uniform(1.0, 500.0, E)
+    est[rng.random(E) < 0.05] = 0.0
+    obs = rng.integers(0, 1000, E).astype(np.uint32)
+    state = rng.uniform(0.5, 1.5, G)
+    w_st, w_tr, w_before = oracle.calibrate(group, est, obs, 0.1, state, with_before=True)
+    buf = torch.full((nbytes + 65536,), 0xA5, dtype=torch.uint8, device="cuda")
+    st, tr, before = ds.calibrate(dev(group), dev(est), dev(obs), 0.1, dev(state), trace=True, trace_before=True,
+                                  ws=buf[:nbytes])
+    assert ds.wait_status(buf) == 0
+    for got, want, what in ((st, w_st, "state"), (tr, w_tr, "trace"), (before, w_before, "trace before")):
+        ok, worst = rel_close(host(got), want, RTOL)
+        assert ok, "%s: worst relative difference %.3g" % (what, worst)
+    assert bool((buf[nbytes:] == 0xA5).all())
