@@ -58,12 +58,19 @@ constexpr uint32_t kMaxTable = 1u << 20; // C x G entries at most (C >= 1)
 constexpr uint32_t kMaxTableR = 1u << 21;   // the same above kCalGroupsLds groups
 constexpr uint32_t kMaxChunks = 512;
 constexpr uint32_t kSmallTable = 16384;  // C x G at most of the one-launch path
-// C x G at most of k_calc_agg and k_calc_apply, and one sub-tile per chunk:
+// C x G at most of k_calc_agg and k_calc_apply with one sub-tile per chunk:
 // every k_calc_apply block reads the maps of all chunks before it. Measured
-// against k_calc_own and its two launches (with the trace): 262,144 events,
-// 4 groups 19.4 and 27.7 us, 16 groups 24.8 and 27.8, 32 groups 33.8 and 27.1;
-// 524,288 events, 4 groups 30.0 and 30.3, 16 groups 34.1 and 30.4.
-constexpr uint32_t kSmallPair = 8192;
+// against k_calc_own and its two launches, with a trace: 131,073 events, 40
+// groups 22.0 and 23.9 us, 50 groups 24.5 and 24.0; 150,000, 32 groups 23.8 and
+// 25.0, 40 groups 26.2 and 24.3; 262,144, 4 groups 18.2 and 28, 20 groups 25.4
+// and 25.4. Without one (k_calc_own then has one other launch): 131,073, 24
+// groups 18.3 and 19.5, 32 groups 20.0 and 20.1.
+constexpr uint32_t kSmallTraced = 10240, kSmallPair = 8192;
+// The same with two sub-tiles per chunk and a trace: 262,145 events (a chunk per
+// compute unit and one more), 1 group 20.3 and 26.8, 24 groups 23.7 and 25.5, 32
+// groups 26.0 and 25.8; 300,000, 1 group 26.9 and 27.2, 4 groups 27.3 and 26.6;
+// 524,288, 2 groups 27.6 and 29.8. (Three: 600,000, 1 group 37.8 and 31.0.)
+constexpr uint32_t kPairTraced = 1024, kPairTraced256 = 6400;
 // C x G at most of k_calc_agg and k_calc_apply with chunks of any length, which
 // a workspace without room for k_calc_own's maps of every event gets.
 constexpr uint32_t kFewTable = 16384;
@@ -1376,7 +1383,7 @@ struct CalcPlan {
 };
 
 // few: k_calc_agg and k_calc_apply wherever their table is at most kFewTable.
-static CalcPlan calc_plan(uint64_t n, uint32_t G, bool few)
+static CalcPlan calc_plan(uint64_t n, uint32_t G, bool few, bool traced)
 {
     CalcPlan p;
     p.e = one_e(n, G);
@@ -1388,8 +1395,11 @@ static CalcPlan calc_plan(uint64_t n, uint32_t G, bool few)
     }
     p.route = Route::Small;
     chunking(n, G, kT, p.L, p.C);
-    const uint64_t entries = (uint64_t)p.C * G;
-    if (G <= kG && ((p.L == (uint32_t)kT && entries <= kSmallPair) || (few && entries <= kFewTable))) return p;
+    uint64_t most = 0;
+    if (few) most = kFewTable;
+    else if (p.L == (uint32_t)kT) most = traced ? kSmallTraced : kSmallPair;
+    else if (p.L == 2u * kT && traced) most = p.C <= 257 ? kPairTraced256 : kPairTraced;
+    if (G <= kG && (uint64_t)p.C * G <= most) return p;
     p.route = Route::Own;
     chunking(n, G, kOStep, p.L, p.C);
     return p;
@@ -1405,13 +1415,13 @@ static size_t calc_bytes(Route route, uint64_t entries, uint64_t n, uint32_t G)
 
 size_t calc_own_bytes(uint64_t n, uint32_t G)
 {
-    const CalcPlan p = calc_plan(n, G, false);
+    const CalcPlan p = calc_plan(n, G, false, false);
     return calc_bytes(p.route, (uint64_t)p.C * G, n, G);
 }
 
 size_t calc_need_bytes(uint64_t n, uint32_t G)
 {
-    const CalcPlan p = calc_plan(n, G, true);
+    const CalcPlan p = calc_plan(n, G, true, false);
     return calc_bytes(p.route, (uint64_t)p.C * G, n, G);
 }
 
@@ -1424,7 +1434,7 @@ size_t calc_ws_bytes(uint64_t n, uint32_t G)
         return most < cap ? most : cap;
     };
     const size_t small = calc_bytes(Route::Small, table(kT, kSmallTable, G < kG ? G : kG), n, G < kG ? G : kG);
-    if (calc_plan(n, G, false).route != Route::Own) return small;
+    if (calc_plan(n, G, false, false).route != Route::Own) return small;
     const size_t own = calc_bytes(Route::Own, table(kOStep, G > kG ? kMaxTableR : kMaxTable, G), n, G);
     return own > small ? own : small;
 }
@@ -1448,11 +1458,14 @@ hipError_t calc_launch(const uint32_t *group, const double *est, const uint32_t 
     // (the carries are then formed in k_calc_apply), else steps of 4096, which
     // keep 12 bytes of every event. In few groups the sub-tiles need none of
     // these, in any number of events, and serve a workspace without the room.
-    const CalcPlan plan = calc_plan(n, G, ws_bytes < calc_own_bytes(n, G));
+    CalcPlan plan = calc_plan(n, G, false, trace || trace_before);
+    if (ws_bytes < calc_bytes(plan.route, (uint64_t)plan.C * G, n, G)) {
+        plan = calc_plan(n, G, true, false);
+        if (ws_bytes < calc_bytes(plan.route, (uint64_t)plan.C * G, n, G)) return hipErrorInvalidValue;
+    }
     const uint32_t one = plan.e;
     a.L = plan.L;
     a.C = plan.C;
-    if (ws_bytes < calc_bytes(plan.route, (uint64_t)a.C * G, n, G)) return hipErrorInvalidValue;
     a.R = G > kG ? (uint32_t)cdiv(G, kRangeGroups) : 1u;
     a.passes = G < 256 ? 1u : 2u;   // keys 0..G fit in 8 or 16 bits
     a.keybits = 1;

@@ -277,3 +277,25 @@ def test_smaller_workspaces(ds, oracle, E, G, nbytes):
         ok, worst = rel_close(host(got), want, RTOL)
         assert ok, "%s: worst relative difference %.3g" % (what, worst)
     assert bool((buf[nbytes:] == 0xA5).all())
+
+
+@pytest.mark.parametrize("E,G", [(131073, 39), (131073, 40), (131073, 31), (262145, 24), (262145, 25), (263169, 3),
+                                 (263169, 4), (524288, 2), (524288, 3), (524289, 1)])
+@pytest.mark.parametrize("outs", ["state", "trace", "both"])
+def test_few_groups_many_events(ds, oracle, E, G, outs):
+    """The sizes between which chunks of one or two sub-tiles change to steps of
+    4,096 events, which depend on whether a trace is wanted."""
+    print("few groups E=%d G=%d %s" % (E, G, outs), flush=True)
+    rng = np.random.default_rng(E + G)
+    group = rng.integers(0, G, E).astype(np.uint32)
+    est = rng.uniform(1.0, 500.0, E)
+    obs = rng.integers(0, 1000, E).astype(np.uint32)
+    state = rng.uniform(0.5, 1.5, G)
+    want = oracle.calibrate(group, est, obs, 0.1, state, with_before=True)
+    got = ds.calibrate(dev(group), dev(est), dev(obs), 0.1, dev(state), trace=outs != "state",
+                       trace_before=outs == "both")
+    for a, b in zip(got, want):
+        if a is None:
+            continue
+        ok, worst = rel_close(host(a), b, RTOL)
+        assert ok, "worst relative difference %.3g" % worst
