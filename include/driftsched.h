@@ -540,7 +540,9 @@ ds_status ds_read_bandwidth(const void *buf, uint64_t bytes, uint32_t *xor_out, 
  * nor with the groups, so that one workspace serves every smaller call.
  * ds_calibrate also takes less than this and is then slower: with few groups
  * (up to 32, and up to 63 just above 2^18 events) no room for 12 bytes per
- * event, above 4096 groups about 26 bytes per event and 8 per group. */
+ * event, above 4096 groups 32 to 55 bytes per event and 8 per group. ds_order of
+ * more than 2^20 requests also takes 64.5 MB, or 31 bytes per request where that
+ * is more, and then sorts by radix passes. */
 size_t ds_workspace_bytes(ds_op op, uint64_t n, uint32_t n_groups);
 
 /* Static description of a status code. */

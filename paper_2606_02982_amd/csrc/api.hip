@@ -389,7 +389,7 @@ static ds_status order_common(uint32_t mask, uint32_t n, const uint8_t *tier,
         }
     if (!aligned(arrival, 8) || (budget && !aligned(budget, 8)) || (fifo_in && !aligned(fifo_in, 4)))
         return DS_ERR_ALIGN;
-    st = check_ws(ws, ws_bytes, ds_workspace_bytes(op, n, 0));
+    st = check_ws(ws, ws_bytes, kFlagBytes + order_need_bytes(n, op == DS_OP_ORDER ? 1 : 4));
     if (st != DS_OK) return st;
     OrderArgs a;
     memset(&a, 0, sizeof(a));
@@ -415,7 +415,7 @@ static ds_status order_common(uint32_t mask, uint32_t n, const uint8_t *tier,
     }
     hipStream_t s = static_cast<hipStream_t>(stream);
     return run_waits(ws, flags, s, [&](uint32_t *flag) {
-        return order_launch(a, after_flag(ws), flag, s, wait_cfg(ws, flags));
+        return order_launch(a, after_flag(ws), ws_bytes - kFlagBytes, flag, s, wait_cfg(ws, flags));
     });
 }
 

@@ -214,6 +214,10 @@ hipError_t score_launch(uint32_t n, const uint32_t *counts, const uint8_t *categ
 
 // ---- stage 4: order ---------------------------------------------------------------
 size_t order_ws_bytes(uint64_t n, uint32_t npolicies);
+// A call with less is refused. Up to kLsNeedN requests the sample sorts have
+// to fit, above them a smaller workspace is taken, for radix sorts.
+constexpr uint32_t kLsNeedN = 1u << 20;
+size_t order_need_bytes(uint64_t n, uint32_t npolicies);
 struct OrderArgs {
     uint32_t mask;             // bit p: produce the order of policy p
     uint32_t n;
@@ -230,7 +234,7 @@ struct OrderArgs {
     double *key[5];
     bool serial_sort;          // sample-sort path: sort in one workgroup
 };
-hipError_t order_launch(const OrderArgs &a, void *ws, uint32_t *flag, hipStream_t s,
+hipError_t order_launch(const OrderArgs &a, void *ws, size_t ws_bytes, uint32_t *flag, hipStream_t s,
                         WaitCfg wait = {});
 
 // ---- estimation error and class histogram ------------------------------------------

@@ -66,33 +66,42 @@ __global__ void k_order_validate(OrderArgs a, uint32_t *__restrict__ flag)
 
 }  // namespace
 
-size_t order_ws_bytes(uint64_t n, uint32_t npolicies)
+// Bytes of the batch over the FIFO sequence, behind the FIFO permutation: the
+// FIFO-ordered copies of arrival, budget and tier, the Aging runs and the
+// sorts (0 outside (kSsMaxN, kLsMaxN]).
+static size_t batch_bytes(uint64_t n)
 {
-    // sample sorts: the FIFO sort and each policy's; radix sorts: the FIFO
-    // permutation, then the policy sorts (sharing the sort workspace with the
-    // FIFO sort, which runs before them on the stream)
-    const uint32_t np = npolicies < 1 ? 1 : npolicies;
-    const uint32_t nss = np + 1 > kSsMaxSorts ? kSsMaxSorts : np + 1;
-    const uint32_t nrs = np > kMaxSorts ? kMaxSorts : np;
-    const size_t sample = ssort_ws_bytes(n < kSsMaxN ? n : kSsMaxN, nss);
-    const size_t rs = sort_ws_bytes(n, nrs);
-    // (FIFO-ordered copies of arrival, budget and tier for the batch over the
-    // FIFO sequence, and the Aging runs)
     const size_t lb = lsort_ws_bytes(n, 1, 2);
-    const size_t ls = lb ? 2 * align_up(n * 8, 256) + align_up(n, 256) + align_up(n * 8, 256) +
-                               align_up(n * 4, 256) + align_up(17 * 4, 256) + am_steps_bytes(n) +
-                               lsort_sample_bytes(n) + lb
-                         : 0;
-    // (the Aging runs take the radix sorts' place after them)
-    const size_t am = n > kSsMaxN && n <= kAmMaxN ? am_ws_bytes(n) : 0;
-    const size_t radix = align_up(n * 4, 256) + std::max(std::max(ls, rs), am);
-    // the larger of the two, and of the largest sample sorts, keeps the size
-    // non-decreasing in n
-    if (n > kLsMaxN) return std::max(radix, order_ws_bytes(kLsMaxN, npolicies));
-    return n <= kSsMaxN ? sample : (radix > sample ? radix : sample);
+    return lb ? 2 * align_up(n * 8, 256) + align_up(n, 256) + align_up(n * 8, 256) + align_up(n * 4, 256) +
+                    align_up(17 * 4, 256) + am_steps_bytes(n) + lsort_sample_bytes(n) + lb
+              : 0;
 }
 
-hipError_t order_launch(const OrderArgs &a, void *ws, uint32_t *flag, hipStream_t s, WaitCfg wait)
+// Above kSsMaxN requests: the FIFO permutation and the largest of `batch`,
+// `runs` and the radix sorts, which share their workspace with the FIFO sort
+// that runs before them on the stream; not less than the largest sample sorts.
+static size_t large_bytes(uint64_t n, uint32_t npolicies, size_t batch, size_t runs)
+{
+    const uint32_t np = npolicies < 1 ? 1 : npolicies, nss = np + 1 > kSsMaxSorts ? kSsMaxSorts : np + 1;
+    const size_t rs = sort_ws_bytes(n, np > kMaxSorts ? kMaxSorts : np);
+    return std::max(ssort_ws_bytes(kSsMaxN, nss), align_up(n * 4, 256) + std::max(std::max(batch, rs), runs));
+}
+
+// The size does not fall with n.
+size_t order_ws_bytes(uint64_t n, uint32_t npolicies)
+{
+    if (n <= kSsMaxN) return ssort_ws_bytes(n, npolicies + 1 > kSsMaxSorts ? kSsMaxSorts : npolicies + 1);
+    // (the Aging runs take the radix sorts' place after them)
+    const size_t bytes = large_bytes(n, npolicies, batch_bytes(n), n <= kAmMaxN ? am_ws_bytes(n) : 0);
+    return n > kLsMaxN ? std::max(bytes, order_ws_bytes(kLsMaxN, npolicies)) : bytes;
+}
+
+size_t order_need_bytes(uint64_t n, uint32_t npolicies)
+{
+    return n <= kLsNeedN ? order_ws_bytes(n, npolicies) : large_bytes(n, npolicies, 0, 0);
+}
+
+hipError_t order_launch(const OrderArgs &a, void *ws, size_t ws_bytes, uint32_t *flag, hipStream_t s, WaitCfg wait)
 {
     const uint32_t n = a.n;
     if (flag) {
@@ -180,17 +189,21 @@ hipError_t order_launch(const OrderArgs &a, void *ws, uint32_t *flag, hipStream_
     uint8_t *p = static_cast<uint8_t *>(ws);
     uint32_t *fifo_ws = reinterpret_cast<uint32_t *>(p);
     void *sort_ws = p + align_up((uint64_t)n * 4, 256);
+    const size_t sort_bytes = ws_bytes - align_up((uint64_t)n * 4, 256);
     // Aging alone over a given FIFO order (a dispatch tick's re-sort): its runs
     // and places straight from it. Measured against the batch below with the
     // class partition alone: 400,000 requests 31 and 41 us, 1,048,576 55 and 67.
-    if (a.fifo_in && (a.mask & 0x1Eu) == (1u << 4) && n <= kAmMaxN) {
+    const bool runs_fit = n <= kAmMaxN && am_ws_bytes(n) <= sort_bytes;
+    if (a.fifo_in && (a.mask & 0x1Eu) == (1u << 4) && runs_fit) {
         in.fifo = a.fifo_in;
         return am_launch(in, n_classes, a.perm[4], a.key[4], sort_ws, s,
                          in.wait.clear ? in.wait.status : nullptr);
     }
-    // (DS_NO_WAIT above 2^20 exercises the radix passes' waits: the sample
-    // sorts wait for nothing)
-    if (n <= (wait.no_wait ? 1u << 20 : kLsMaxN)) {
+    // Sample sorts where the workspace holds them (above kLsNeedN requests the
+    // radix sorts need less than half: SJF of 4,194,304 requests 413 us against
+    // 773). (DS_NO_WAIT above kLsNeedN exercises the radix passes'
+    // waits: the sample sorts wait for nothing)
+    if (n <= (wait.no_wait ? kLsNeedN : kLsMaxN) && batch_bytes(n) <= sort_bytes) {
         // the FIFO sort, then every other policy over the FIFO sequence in
         // one batch of sample sorts and partitions (lsort.hip)
         uint8_t *q = static_cast<uint8_t *>(sort_ws);
@@ -247,8 +260,9 @@ hipError_t order_launch(const OrderArgs &a, void *ws, uint32_t *flag, hipStream_
 
     // the policy sorts over the FIFO sequence; Aging as the merge of the
     // priority classes' runs of that sequence (agmerge.hip), in the sort
-    // workspace, or above kAmMaxN as one more radix sort
-    const bool aging_merge = (a.mask & (1u << 4)) && n <= kAmMaxN;
+    // workspace, or where they do not fit, and above kAmMaxN, as one more radix
+    // sort
+    const bool aging_merge = (a.mask & (1u << 4)) && runs_fit;
     SortJob jobs[kMaxSorts];
     uint32_t nj = 0;
     if (a.mask & (1u << 1)) jobs[nj++] = {SortKind::Class, 8, a.key[1], a.perm[1]};

@@ -1,4 +1,4 @@
-"""Stage 4 between 2^18 and 2^20 requests on the GPU against the oracle.
+"""Stage 4 between 2^18 and 2^22 requests on the GPU against the oracle.
 
 In this range FIFO and SJF are sample sorts by (key, position) with exact
 bucket sizes (a bucket larger than the in-LDS limit is sorted through global
@@ -10,7 +10,9 @@ exactly.
 """
 import numpy as np
 import pytest
+import torch
 
+from tests.gpu_util import dev
 from tests.test_gpu_order import POLICIES, _batch, check
 
 pytestmark = pytest.mark.gpu
@@ -146,3 +148,26 @@ def test_layouts_above_2_20(ds, oracle, pol, pattern):
     rng = np.random.default_rng(n + len(pattern))
     tier, arr, bud = _layout(pattern, n, rng)
     check(ds, oracle, pol, tier, arr, bud, t_now=100.0, aging_rate=0.01, aging_floor=-np.inf)
+
+
+# what ds_order took before the sample sorts of more than 2^20 requests, which
+# then have no room
+@pytest.mark.parametrize("n,nbytes", [(1048577, 64411136), (2097152, 65057536), (4194304, 127972096),
+                                      (4194305, 127981568)])
+@pytest.mark.parametrize("pol", POLICIES)
+def test_smaller_workspaces(ds, n, nbytes, pol):
+    """A workspace of that size is taken still, nothing behind it touched, and
+    the order and keys are those of a workspace with room for the fast way,
+    with the FIFO order given and without."""
+    print("workspace n=%d bytes=%d policy=%d" % (n, nbytes, pol), flush=True)
+    tier, arr, bud = (dev(x) for x in _batch(n, n))
+    kw = dict(key=True, aging_rate=0.5, t_now=10.0)
+    full = torch.empty(ds.workspace_bytes(ds.OP_ORDER, n), dtype=torch.uint8, device="cuda")
+    fifo = ds.order(ds.FIFO, tier, arr, bud, ws=full, **kw)[0].clone()
+    buf = torch.full((nbytes + 65536,), 0xA5, dtype=torch.uint8, device="cuda")
+    for given in (None, fifo):
+        want = ds.order(pol, tier, arr, bud, fifo=given, ws=full, **kw)
+        got = ds.order(pol, tier, arr, bud, fifo=given, ws=buf[:nbytes], **kw)
+        assert ds.wait_status(buf) == 0
+        assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+        assert bool((buf[nbytes:] == 0xA5).all())
