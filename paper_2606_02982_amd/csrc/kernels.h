@@ -180,7 +180,7 @@ hipError_t am_launch(const SortInput &in, uint32_t n_classes, uint32_t *perm, do
 // class in FIFO order, run_start (17) each class's first entry and n.
 // The places alone, over runs formed elsewhere (runs.cstart[K..16] = n).
 hipError_t am_rank_launch(const SortInput &in, uint32_t n_classes, const LsRuns &runs, uint32_t *perm,
-                          double *key_out, hipStream_t s);
+                          double *key_out, void *scratch, hipStream_t s);
 size_t am_partition_ws_bytes(uint64_t n);
 hipError_t am_partition(const SortInput &in, uint32_t *run_pos, uint32_t *run_start, void *ws, hipStream_t s);
 

@@ -255,7 +255,7 @@ hipError_t order_launch(const OrderArgs &a, void *ws, size_t ws_bytes, uint32_t 
         hipError_t err = lsort_launch(in, jobs, nj, batch_ws, s, a.fifo_in ? nullptr : &cp, nullptr,
                                       aging ? &runs : nullptr, sjf_drawn ? &sjf : nullptr);
         if (err != hipSuccess || !aging) return err;
-        return am_rank_launch(in, n_classes, runs, a.perm[4], a.key[4], s);
+        return am_rank_launch(in, n_classes, runs, a.perm[4], a.key[4], batch_ws, s);   // (the batch is done with it)
     }
 
     // the policy sorts over the FIFO sequence; Aging as the merge of the

@@ -171,3 +171,26 @@ def test_smaller_workspaces(ds, n, nbytes, pol):
         assert ds.wait_status(buf) == 0
         assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
         assert bool((buf[nbytes:] == 0xA5).all())
+
+
+@pytest.mark.parametrize("shares", [(0.99, 0.01), (0.001, 0.999), (0.9, 0.06, 0.04), (0.5, 0.3) + (0.04,) * 5,
+                                    (0.1,) * 10, (1 / 11,) * 11, (0.9,) + (0.1 / 12,) * 12, (1 / 16,) * 16,
+                                    (0.6, 0.0, 0.0, 0.0) + (0.4 / 12,) * 12],
+                         ids=lambda s: "%d classes" % len(s))
+@pytest.mark.parametrize("rate,floor", [(0.0, -np.inf), (10.0, -np.inf), (0.1, 0.5)])
+def test_aging_class_mixes(ds, oracle, shares, rate, floor):
+    """Runs of every ratio (tiles of 1,024, 512 and 256 entries and runs too
+    short for tiles), at 11 classes and more merged in two steps: apart, fully
+    overlapping, and cut by the floor; with and without a given FIFO order."""
+    n, k = 300007, len(shares)
+    print("mix %s rate %g floor %g" % (shares, rate, floor), flush=True)
+    rng = np.random.default_rng(k + int(10 * rate))
+    tier = rng.choice(k, n, p=np.array(shares) / sum(shares)).astype(np.uint8)
+    arr = np.round(rng.uniform(0.0, 60.0, n), 4)
+    kw = dict(n_tiers=k, weights=(1,) * k, tier_priority=tuple(float(q) for q in range(k)), t_now=60.0,
+              aging_rate=rate, aging_floor=floor)
+    check(ds, oracle, ds.AGING, tier, arr, arr, **kw)
+    fifo = dev(np.lexsort((np.arange(n), arr)).astype(np.uint32))
+    want = oracle.order(ds.AGING, tier, arr, **{a: b for a, b in kw.items() if a != "n_tiers"})[0]
+    got = ds.order(ds.AGING, dev(tier), dev(arr), fifo=fifo, **kw)[0]
+    assert np.array_equal(got.cpu().numpy().view(np.uint32), want)
