@@ -104,6 +104,18 @@ def test_tiny_and_empty_prompts(ds, oracle):
     check(ds, oracle, text, offsets)
 
 
+@pytest.mark.parametrize("run", [1, 7, 8, 9, 62, 63, 64, 65, 300])
+def test_runs_of_empty_prompts(ds, oracle, run):
+    # repeated offsets, beside separators that they cut, over windows of 64
+    # offsets that begin or end inside a run
+    ws = "\u3000".encode()
+    prompts = []
+    for k in range(120):
+        prompts += [b"a" + ws[:2]] + [b""] * (run + k % 3) + [ws[2:] + b"b c" * (k % 40)] + [b""] * (k % 5) + [ws]
+    text, offsets = pack(prompts)
+    check(ds, oracle, text, offsets)
+
+
 def test_bytes_outside_prompts_and_ragged_tail(ds, oracle):
     rng = np.random.default_rng(6)
     body = synth.make_text(rng.integers(1, 300, 500).astype(np.uint32), 9, 0.05)
