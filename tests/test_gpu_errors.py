@@ -172,7 +172,7 @@ def test_group_ranges(ds, oracle, n, G, skew):
     assert got[-1, 0] == first[-1, 0]
 
 
-@pytest.mark.parametrize("n", [1, 15, 16, 17, 4095, 100001])
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 4095, 24575, 24576, 100001])
 @pytest.mark.parametrize("shift", [0, 1, 16])
 def test_class_histogram_alignment(ds, oracle, n, shift):
     # 16-byte loads need both arrays aligned; views that are not take byte loads
