@@ -122,7 +122,7 @@ __device__ __forceinline__ void add_events(Sums &S, uint32_t slot, uint32_t key,
 // partial layout: [block][4][G + 1] (count, sum |d|, sum d^2, sum obs/x);
 // slot G holds the all-events sums.
 //
-// kOwn false (G <= 256, or no groups): every wave has sums of its own, and
+// kOwn false (G <= 256): every wave has sums of its own, and
 // where there is room rep = 256 / G (a power of two, at most 64) of them per
 // group, one per lane mod rep, so that lanes of one wave seldom meet.
 // kOwn true: wave w owns the groups g = w (mod 16). A step's 2048 events are
@@ -304,6 +304,55 @@ __global__ __launch_bounds__(kEA) void k_err_final(const double *__restrict__ pa
     const uint32_t lane = (uint32_t)lane_id(), w = threadIdx.x >> 6;
     const uint64_t g = (uint64_t)blockIdx.x * kFS + (lane & (kFS - 1));
     const uint32_t k = lane / kFS;
+// The all-events sums alone (no groups): 256 threads, and 1,024 above 2^20
+// events, where 256 leave too few loads in flight. k_err_accum's cleared and
+// folded LDS cost a small call a third: 2,000 events 8.4 us, 6.0 here; 1,048,576
+// 11.6 and 9.4; 4,194,304 21.9 and 18.1.
+template <uint32_t kTh>
+__global__ __launch_bounds__(kTh) void k_err_all(uint64_t n, const double *__restrict__ est,
+                                                 const double *__restrict__ factor,
+                                                 const uint32_t *__restrict__ obs, double *__restrict__ partial)
+{
+    constexpr uint32_t kPer = kStep / kTh, kW = kTh / 64;
+    __shared__ double wsum[4][kW];
+    const uint64_t per = cdiv(n, gridDim.x);
+    const uint64_t e0 = (uint64_t)blockIdx.x * per;
+    const uint64_t e1 = e0 + per < n ? e0 + per : n;
+    const uint32_t t = threadIdx.x;
+    double v[4] = {0.0, 0.0, 0.0, 0.0};
+    for (uint64_t b0 = e0; b0 < e1; b0 += kStep) {
+        double x[kPer], f[kPer], o[kPer];
+#pragma unroll
+        for (uint32_t u = 0; u < kPer; u++) {
+            const uint64_t e = b0 + u * kTh + t;
+            const bool in = e < e1;
+            x[u] = in ? est[e] : 0.0;   // 0: not usable
+            f[u] = in && factor ? factor[e] : 1.0;
+            o[u] = in ? (double)obs[e] : 0.0;
+        }
+#pragma unroll
+        for (uint32_t u = 0; u < kPer; u++) {
+            x[u] = x[u] * f[u];
+            if (!usable(x[u])) continue;
+            const double d = x[u] - o[u];
+            v[0] += 1.0;
+            v[1] += fabs(d);
+            v[2] += d * d;
+            v[3] += o[u] / x[u];
+        }
+    }
+    for (uint32_t k = 0; k < 4; k++) {
+        v[k] = wave_sum_f64(v[k]);
+        if (lane_id() == 0) wsum[k][t >> 6] = v[k];
+    }
+    __syncthreads();
+    if (t < 4) {
+        double s = 0.0;
+        for (uint32_t k = 0; k < kW; k++) s += wsum[t][k];
+        partial[(uint64_t)blockIdx.x * 4 + t] = s;
+    }
+}
+
     double s = 0.0;
     if (g < slots && (g == G || with_groups)) {
         double v[kMaxBlocks / kWaves];
@@ -347,6 +396,25 @@ __device__ __forceinline__ void hist_add(uint32_t *h, uint32_t c, uint32_t k, ui
 
 // hist[c * 3 + k]: requests of category c in class k. kWide: both arrays are
 // 16-byte aligned, 16 requests per load; otherwise byte loads. 4,194,304
+// The one row of k_err_all's partials: a wave, lanes on blocks.
+__global__ __launch_bounds__(64) void k_err_final_all(const double *__restrict__ partial, uint32_t blocks,
+                                                      double *__restrict__ stats)
+{
+    const uint32_t lane = threadIdx.x;
+    double v[4] = {0.0, 0.0, 0.0, 0.0};
+    for (uint32_t b = lane; b < blocks; b += 64)
+#pragma unroll
+        for (uint32_t k = 0; k < 4; k++) v[k] += partial[(uint64_t)b * 4 + k];
+#pragma unroll
+    for (uint32_t k = 0; k < 4; k++) v[k] = wave_sum_f64(v[k]);
+    if (lane != 0) return;
+    const double n = v[0], nan = __builtin_nan("");
+    stats[0] = n;
+    stats[1] = n > 0.0 ? v[1] / n : nan;
+    stats[2] = n > 0.0 ? sqrt(v[2] / n) : nan;
+    stats[3] = n > 0.0 ? v[3] / n : nan;
+}
+
 // requests: 17.2 us with byte loads, 10.0 us with wide ones (128 blocks of
 // 1,024 threads 12.2; copies of the cells per lane 9.7, not worth their code).
 template <bool kWide>
@@ -419,7 +487,16 @@ hipError_t err_launch(uint64_t n, const double *est, const double *factor, const
     }
     double *partial = static_cast<double *>(ws);
     const uint32_t blocks = err_blocks(n, G);
-    // up to 256 groups every wave's sums fit LDS beside the others'
+    if (G == 0) {
+        if (n <= 1u << 20)
+            hipLaunchKernelGGL(k_err_all<256>, dim3(blocks), dim3(256), 0, s, n, est, factor, obs, partial);
+        else
+            hipLaunchKernelGGL(k_err_all<kEA>, dim3(blocks), dim3(kEA), 0, s, n, est, factor, obs, partial);
+        hipLaunchKernelGGL(k_err_final_all, dim3(1), dim3(64), 0, s, (const double *)partial, blocks, stats);
+        return hipGetLastError();
+    }
+    // up to 256 groups every wave's sums fit LDS beside the others'; up to 512
+    // a wave owns at most 32 groups and keeps eight sums of each
     if (G <= kWaveSlots) {
         uint32_t rep = 64;
         while (rep > 1 && rep * G > kWaveSlots) rep >>= 1;

@@ -172,6 +172,17 @@ def test_group_ranges(ds, oracle, n, G, skew):
     assert got[-1, 0] == first[-1, 0]
 
 
+@pytest.mark.parametrize("n", [1, 255, 2047, 2049, 524289, (1 << 20) + 1, 1200007])
+def test_all_events_alone(ds, oracle, n):
+    # no groups: two block sizes, with a ragged last step
+    rng = np.random.default_rng(n)
+    est = rng.uniform(0.5, 4000, n)
+    est[rng.random(n) < 0.05] = np.inf
+    obs = rng.integers(0, 5000, n)
+    check_stats(ds, oracle, est, obs)
+    check_stats(ds, oracle, est, obs, factor=rng.uniform(0.5, 1.5, n))
+
+
 @pytest.mark.parametrize("n", [1, 15, 16, 17, 4095, 24575, 24576, 100001])
 @pytest.mark.parametrize("shift", [0, 1, 16])
 def test_class_histogram_alignment(ds, oracle, n, shift):
