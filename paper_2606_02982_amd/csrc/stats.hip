@@ -10,8 +10,9 @@
 // groups per pass over its range) and the all-events sums in registers; it
 // stores its partial sums, and a last kernel adds the blocks' partials in a
 // fixed order and forms MAE = sum|d| / count, RMSE = sqrt(sum d^2 / count),
-// mean bias = sum(obs / x) / count. No sum uses floating-point atomics: every
-// order of addition is fixed by the data and the launch shape, so results
+// mean bias = sum(obs / x) / count. The sums in LDS are added to by LDS adds,
+// each by one wave alone and in the order of its lanes, so that every order of
+// addition is fixed by the data and the launch shape: results
 // are the same from run to run and agree with any sequential sum within the
 // rounding of an n-term sum.
 #include "common.h"
@@ -30,7 +31,6 @@ constexpr uint32_t kWaveSlots = kSlots / kWaves;
 constexpr uint32_t kU = 2;                  // events per thread per step
 constexpr uint32_t kStep = kU * kEA;
 constexpr uint32_t kChunks = kStep / 64;
-constexpr uint32_t kLight = 4;              // lanes on one sum that are added up one by one
 constexpr uint32_t kNone = 0xFFFFFFFFu;
 
 __device__ __forceinline__ bool usable(double x) { return isfinite(x) && x > 0.0; }
@@ -78,19 +78,22 @@ template <typename T> __device__ __forceinline__ void lds_add(T *p, T v)
 }
 
 // Adds one event per lane (where ok) to the sum at `slot`. Lanes share a
-// slot exactly when they share `key` (< 256), and no other wave touches the
-// slot, so a wave settles its collisions by itself: up to kLight lanes of one
-// slot add in lane order, one instruction after another; a slot with more
-// (one tenant holding most of the events) is added up across the wave in a
-// tree first.
+// key (< 256) exactly when they share a slot, or with kCopies copies of a
+// group's sums (copy = lane mod kCopies) a group; no other wave touches the
+// slot, so a wave settles its collisions by itself: lanes of one slot add in
+// lane order, one instruction after another; a key with many lanes (one tenant
+// holding most of the events) is added up across the wave in a tree first.
+template <uint32_t kCopies>
 __device__ __forceinline__ void add_events(Sums &S, uint32_t slot, uint32_t key, bool ok, double a,
                                            double q, double r)
 {
+    constexpr uint32_t kHeavy = kCopies > 1 ? 2 * kCopies : 4;                 // more lanes take the tree
+    constexpr uint32_t kLight = kCopies > 1 ? 64 / kCopies : kHeavy;           // lanes on one slot otherwise
     const uint32_t lane = (uint32_t)lane_id();
     uint64_t peers = match_bits<8>(key, __ballot(ok));
     if (!ok) peers = 0;
     for (;;) {
-        const uint64_t heavy = __ballot((uint32_t)__popcll(peers) > kLight);
+        const uint64_t heavy = __ballot((uint32_t)__popcll(peers) > kHeavy);
         if (!heavy) break;
         const int l = __builtin_ctzll(heavy);
         const uint64_t m = readlane64(peers, l);
@@ -105,6 +108,10 @@ __device__ __forceinline__ void add_events(Sums &S, uint32_t slot, uint32_t key,
             lds_add(&S.r[slot], tr);
         }
         if (in) peers = 0;
+    }
+    if constexpr (kCopies > 1) {
+        static_assert(kCopies == 8, "the lanes of a copy");
+        peers &= 0x0101010101010101ull << (lane & (kCopies - 1));
     }
     const uint32_t rank = peers ? (uint32_t)__popcll(peers & lanemask_lt()) : kNone;
     if (rank == 0) lds_add(&S.n[slot], (uint32_t)__popcll(peers));
@@ -125,7 +132,9 @@ __device__ __forceinline__ void add_events(Sums &S, uint32_t slot, uint32_t key,
 // kOwn false (G <= 256): every wave has sums of its own, and
 // where there is room rep = 256 / G (a power of two, at most 64) of them per
 // group, one per lane mod rep, so that lanes of one wave seldom meet.
-// kOwn true: wave w owns the groups g = w (mod 16). A step's 2048 events are
+// kOwn true: wave w owns the groups g = w (mod 16), with kCopies sums of each
+// (8 up to 512 groups, where a wave's 64 events else meet on 16 to 32 sums:
+// 65,536 events of 257 groups 33.6 us with one, 17.4 with eight). A step's 2048 events are
 // split by owner, stably, through LDS (4 ballots per 64 events, one table of
 // counts that every wave scans for itself: two barriers a step), and each
 // wave adds up its own events in event order. The next step's loads are in
@@ -139,7 +148,7 @@ __device__ __forceinline__ void add_events(Sums &S, uint32_t slot, uint32_t key,
 // error statistics as a whole, before and after: 4,194,304 events, 4 groups
 // 464 and 27 us, 256 groups 202 and 30, 4,096 groups 648 and 93, one group
 // holding every event 1,740 and 205; 65,536 events, 1,000 groups 27 and 19.
-template <bool kOwn>
+template <bool kOwn, uint32_t kCopies = 1>
 __global__ __launch_bounds__(kEA) void k_err_accum(uint64_t n, const double *__restrict__ est,
                                                    const double *__restrict__ factor,
                                                    const uint32_t *__restrict__ obs,
@@ -190,7 +199,7 @@ __global__ __launch_bounds__(kEA) void k_err_accum(uint64_t n, const double *__r
                         sr += r;
                     }
                     const uint32_t key = (s.g[u] * rep + (lane & (rep - 1))) & (kWaveSlots - 1);
-                    if (G) add_events(S, w * kWaveSlots + key, key, ok && s.g[u] < G, a, q, r);
+                    add_events<1>(S, w * kWaveSlots + key, key, ok && s.g[u] < G, a, q, r);
                 }
             } else {
                 // the wave's two chunks of 64 events by owner
@@ -240,17 +249,24 @@ __global__ __launch_bounds__(kEA) void k_err_accum(uint64_t n, const double *__r
                         sr += r;
                     }
                     const bool own = in && g < cn;
-                    add_events(S, own ? g : 0u, (g / kWaves) & (kWaveSlots - 1), own, a, q, r);
+                    const uint32_t key = (g / kWaves) & (kWaveSlots - 1);   // (the wave's groups)
+                    const uint32_t slot = kCopies > 1 ? (key * kCopies + lane % kCopies) * kWaves + w : g;
+                    add_events<kCopies>(S, own ? slot : 0u, key, own, a, q, r);
                 }
             }
         }
         __syncthreads();
         if constexpr (kOwn) {
             for (uint32_t i = t; i < cn; i += kEA) {
-                mine[0 * slots + c0 + i] = (double)S.n[i];
-                mine[1 * slots + c0 + i] = S.a[i];
-                mine[2 * slots + c0 + i] = S.q[i];
-                mine[3 * slots + c0 + i] = S.r[i];
+                double m[4] = {0.0, 0.0, 0.0, 0.0};
+                for (uint32_t k = 0; k < kCopies; k++) {
+                    const uint32_t j = ((i / kWaves) * kCopies + k) * kWaves + (i & (kWaves - 1));
+                    m[0] += (double)S.n[j];
+                    m[1] += S.a[j];
+                    m[2] += S.q[j];
+                    m[3] += S.r[j];
+                }
+                for (uint32_t k = 0; k < 4; k++) mine[k * slots + c0 + i] = m[k];
             }
             __syncthreads();
         } else if (t < kWaveSlots) {
@@ -288,22 +304,6 @@ __global__ __launch_bounds__(kEA) void k_err_accum(uint64_t n, const double *__r
     }
 }
 
-// stats[4 g ..]: a block per 16 group slots. Lane = (slot, which sum), wave =
-// a sixteenth of the blocks' partials (64-byte and longer runs of a row,
-// sixteen loads in flight), then the sixteen in order, then the means.
-// (4,097 slots x 256 blocks: a wave per slot, lanes on blocks, took 26.6 us,
-// this 11.2.)
-constexpr uint32_t kFS = 16;
-
-__global__ __launch_bounds__(kEA) void k_err_final(const double *__restrict__ partial,
-                                                   uint32_t blocks, uint32_t G,
-                                                   uint32_t with_groups, double *__restrict__ stats)
-{
-    __shared__ double part[kWaves][64];
-    const uint64_t slots = (uint64_t)G + 1;
-    const uint32_t lane = (uint32_t)lane_id(), w = threadIdx.x >> 6;
-    const uint64_t g = (uint64_t)blockIdx.x * kFS + (lane & (kFS - 1));
-    const uint32_t k = lane / kFS;
 // The all-events sums alone (no groups): 256 threads, and 1,024 above 2^20
 // events, where 256 leave too few loads in flight. k_err_accum's cleared and
 // folded LDS cost a small call a third: 2,000 events 8.4 us, 6.0 here; 1,048,576
@@ -353,6 +353,22 @@ __global__ __launch_bounds__(kTh) void k_err_all(uint64_t n, const double *__res
     }
 }
 
+// stats[4 g ..]: a block per 16 group slots. Lane = (slot, which sum), wave =
+// a sixteenth of the blocks' partials (64-byte and longer runs of a row,
+// sixteen loads in flight), then the sixteen in order, then the means.
+// (4,097 slots x 256 blocks: a wave per slot, lanes on blocks, took 26.6 us,
+// this 11.2.)
+constexpr uint32_t kFS = 16;
+
+__global__ __launch_bounds__(kEA) void k_err_final(const double *__restrict__ partial,
+                                                   uint32_t blocks, uint32_t G,
+                                                   uint32_t with_groups, double *__restrict__ stats)
+{
+    __shared__ double part[kWaves][64];
+    const uint64_t slots = (uint64_t)G + 1;
+    const uint32_t lane = (uint32_t)lane_id(), w = threadIdx.x >> 6;
+    const uint64_t g = (uint64_t)blockIdx.x * kFS + (lane & (kFS - 1));
+    const uint32_t k = lane / kFS;
     double s = 0.0;
     if (g < slots && (g == G || with_groups)) {
         double v[kMaxBlocks / kWaves];
@@ -380,22 +396,6 @@ __global__ __launch_bounds__(kTh) void k_err_all(uint64_t n, const double *__res
         *out = __builtin_nan("");
 }
 
-__global__ void k_err_validate(uint64_t n, const uint32_t *__restrict__ group, uint32_t G,
-                               uint32_t *__restrict__ flag)
-{
-    uint32_t bad = 0;
-    for (uint64_t e = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (uint64_t)gridDim.x * blockDim.x)
-        if (group[e] >= G) bad = 1;
-    if (bad) atomicOr(flag, 1u);
-}
-
-__device__ __forceinline__ void hist_add(uint32_t *h, uint32_t c, uint32_t k, uint32_t n_cat)
-{
-    if (c < n_cat && k < 3) atomicAdd(&h[c * 3 + k], 1u);
-}
-
-// hist[c * 3 + k]: requests of category c in class k. kWide: both arrays are
-// 16-byte aligned, 16 requests per load; otherwise byte loads. 4,194,304
 // The one row of k_err_all's partials: a wave, lanes on blocks.
 __global__ __launch_bounds__(64) void k_err_final_all(const double *__restrict__ partial, uint32_t blocks,
                                                       double *__restrict__ stats)
@@ -415,6 +415,22 @@ __global__ __launch_bounds__(64) void k_err_final_all(const double *__restrict__
     stats[3] = n > 0.0 ? v[3] / n : nan;
 }
 
+__global__ void k_err_validate(uint64_t n, const uint32_t *__restrict__ group, uint32_t G,
+                               uint32_t *__restrict__ flag)
+{
+    uint32_t bad = 0;
+    for (uint64_t e = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (uint64_t)gridDim.x * blockDim.x)
+        if (group[e] >= G) bad = 1;
+    if (bad) atomicOr(flag, 1u);
+}
+
+__device__ __forceinline__ void hist_add(uint32_t *h, uint32_t c, uint32_t k, uint32_t n_cat)
+{
+    if (c < n_cat && k < 3) atomicAdd(&h[c * 3 + k], 1u);
+}
+
+// hist[c * 3 + k]: requests of category c in class k. kWide: both arrays are
+// 16-byte aligned, 16 requests per load; otherwise byte loads. 4,194,304
 // requests: 17.2 us with byte loads, 10.0 us with wide ones (128 blocks of
 // 1,024 threads 12.2; copies of the cells per lane 9.7, not worth their code).
 template <bool kWide>
@@ -503,8 +519,8 @@ hipError_t err_launch(uint64_t n, const double *est, const double *factor, const
         hipLaunchKernelGGL(k_err_accum<false>, dim3(blocks), dim3(kEA), 0, s, n, est, factor, obs,
                            group, G, rep, partial);
     } else {
-        hipLaunchKernelGGL(k_err_accum<true>, dim3(blocks), dim3(kEA), 0, s, n, est, factor, obs,
-                           group, G, 1u, partial);
+        const auto accum = G <= 2 * kWaveSlots ? k_err_accum<true, 8> : k_err_accum<true>;
+        hipLaunchKernelGGL(accum, dim3(blocks), dim3(kEA), 0, s, n, est, factor, obs, group, G, 1u, partial);
     }
     hipLaunchKernelGGL(k_err_final, dim3((uint32_t)cdiv((uint64_t)G + 1, kFS)), dim3(kEA), 0, s,
                        (const double *)partial, blocks, G, group ? 1u : 0u, stats);

@@ -142,12 +142,12 @@ def test_class_histogram_validate(ds):
                            validate=True)
 
 
-@pytest.mark.parametrize("n,G", [(2047, 256), (2049, 257), (70001, 64), (70001, 65), (70001, 4096),
+@pytest.mark.parametrize("n,G", [(2047, 256), (2049, 257), (70001, 300), (30001, 512), (30001, 513), (70001, 64), (70001, 65), (70001, 4096),
                                  (600000, 4097), (600000, 1)])
 @pytest.mark.parametrize("skew", ["even", "one", "mixed"])
 def test_group_ranges(ds, oracle, n, G, skew):
     # sums per wave (with copies per lane) up to 256 groups, groups split over
-    # the waves above, 4096 groups per pass; lanes of a wave that share a
+    # the waves above (with copies up to 512), 4096 groups per pass; lanes of a wave that share a
     # group one by one, or most of them (one group holds most events), and
     # events outside any group, which count in the last row alone
     rng = np.random.default_rng(n * 3 + G)
