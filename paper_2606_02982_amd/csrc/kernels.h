@@ -147,7 +147,6 @@ struct LsRuns {
 struct LsSample {
     uint64_t *srt_k;
     uint32_t *srt_i;
-    uint16_t *rpart;
     uint64_t *smp_k;
     uint32_t *smp_j;
     bool draw;

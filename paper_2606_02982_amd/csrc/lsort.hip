@@ -7,8 +7,8 @@
 //
 //   k_ls_gather   the keys of S = 8 per bucket positions, one in each of S
 //                 equal strata of [0, n) (so the sample is in sequence order),
-//                 sorted in blocks of 1024 (a bitonic network per wave, then
-//                 four merges in LDS).
+//                 sorted in blocks of 256 or 1024 (a bitonic network per wave,
+//                 then merges in LDS).
 //   k_ls_sample   each sample's rank in each sorted block, one binary search
 //                 in LDS.
 //   k_ls_place    each sample at its rank (its ranks in the blocks added): the
@@ -54,8 +54,12 @@ namespace {
 constexpr uint32_t kLsAvg = 1024;                  // target pairs per bucket
 constexpr uint32_t kLsMaxB = kLsMaxN / kLsAvg;     // 4096 buckets at most
 constexpr uint32_t kLsOver = 8;                    // samples per bucket
-constexpr uint32_t kSB = 1024;                     // samples per sorted block
 constexpr uint32_t kLsMaxS = kLsMaxB * kLsOver;    // 32768
+// Samples per sorted block (template parameter kSB) and the largest sample
+// that takes the small ones: a block of 1024 costs two more merges (10.5 us
+// for 6.0 in k_ls_gather), which the fewer blocks to search pay back only
+// where the sample is large.
+constexpr uint32_t kSBSmall = 256, kSBLarge = 1024, kSBSmallMaxS = 8192;
 constexpr uint32_t kLsCap = 4096;                  // buckets ranked in LDS up to this size
 static_assert(kLsMaxB <= 65536, "a bucket index is stored in 16 bits");
 
@@ -260,6 +264,7 @@ __device__ __forceinline__ uint64_t shfl_xor_u64(uint64_t x, int m)
 // with a bitonic network across the lanes, then pairs of sorted stretches
 // merged in LDS (each pair's place: its own and its rank in the other).
 __global__ __launch_bounds__(kSB) void k_ls_gather(LsArgs a)
+template <uint32_t kSB>
 {
     __shared__ uint64_t mk[2][kSB];
     __shared__ uint16_t mi[2][kSB];
@@ -309,6 +314,7 @@ __global__ __launch_bounds__(kSB) void k_ls_gather(LsArgs a)
 constexpr uint32_t kSmE = 2;
 
 __global__ __launch_bounds__(kSB) void k_ls_sample(LsArgs a)
+template <uint32_t kSB>
 {
     __shared__ uint64_t sk[kSB];
     __shared__ uint16_t si[kSB];
@@ -347,6 +353,7 @@ __global__ __launch_bounds__(kSB) void k_ls_sample(LsArgs a)
 
 // Each sample at its rank (the sum of its ranks in the blocks).
 __global__ __launch_bounds__(256) void k_ls_place(LsArgs a)
+template <uint32_t kSB>
 {
     const LsRow &R = a.r[a.srow[blockIdx.y]];
     const uint32_t e = blockIdx.x * 256u + threadIdx.x, S = R.S;
@@ -1145,7 +1152,7 @@ LsLayout ls_layout(uint64_t n)
     if (l.B < 2) l.B = 2;
     l.hgt = 0;
     while ((1u << l.hgt) < l.B) l.hgt++;
-    l.S = (uint32_t)align_up((uint64_t)kLsOver * l.B, kSB);   // <= kLsMaxS; S <= n
+    l.S = (uint32_t)align_up((uint64_t)kLsOver * l.B, kSBLarge);   // <= kLsMaxS; S <= n
     l.tiles = (uint32_t)cdiv(n, l.B <= kSmallB ? kTile<kSmallB> : kTile<kLsMaxB>);
     return l;
 }
@@ -1156,7 +1163,7 @@ size_t lsort_sample_bytes(uint64_t n)
 {
     if (n <= kSsMaxN || n > kLsMaxN) return 0;
     const LsLayout l = ls_layout(n);
-    return 2 * align_up(l.S * 8, 256) + 2 * align_up(l.S * 4, 256) + align_up((uint64_t)l.S / kSB * l.S * 2, 256);
+    return 2 * align_up(l.S * 8, 256) + 2 * align_up(l.S * 4, 256);
 }
 
 LsSample lsort_sample_at(uint64_t n, void *p)
@@ -1171,8 +1178,6 @@ LsSample lsort_sample_at(uint64_t n, void *p)
     y.smp_j = reinterpret_cast<uint32_t *>(q);
     q += align_up(l.S * 4, 256);
     y.srt_i = reinterpret_cast<uint32_t *>(q);
-    q += align_up(l.S * 4, 256);
-    y.rpart = reinterpret_cast<uint16_t *>(q);
     y.draw = true;
     return y;
 }
@@ -1186,7 +1191,6 @@ size_t lsort_ws_bytes(uint64_t n, uint32_t nsort, uint32_t npart)
     const uint64_t tiles = cdiv(n, kTile<kSmallB>);
     const uint64_t sort = 2 * align_up(l.B * 4, 256) + align_up(tiles * l.B * 4, 256) +
                           2 * align_up(l.S * 8, 256) + 2 * align_up(l.S * 4, 256) +
-                          align_up((uint64_t)l.S / kSB * l.S * 2, 256) +
                           align_up(n * 2, 256) +
                           2 * (align_up(n * 8, 256) + align_up(n * 4, 256)) +
                           align_up(n * 4, 256) + align_up(n, 256) + align_up(n * 8, 256);   // payloads
@@ -1249,7 +1253,6 @@ hipError_t lsort_launch(const SortInput &in, const SortJob *jobs, uint32_t njobs
             R.tcnt = reinterpret_cast<uint32_t *>(take((uint64_t)l.tiles * l.B * 4));
             R.srt_k = reinterpret_cast<uint64_t *>(take(l.S * 8));
             R.srt_i = reinterpret_cast<uint32_t *>(take(l.S * 4));
-            R.rpart = reinterpret_cast<uint16_t *>(take((uint64_t)l.S / kSB * l.S * 2));
             R.smp_k = reinterpret_cast<uint64_t *>(take(l.S * 8));
             R.smp_j = reinterpret_cast<uint32_t *>(take(l.S * 4));
             if (k == SortKind::Budget && sjf && !sjf->draw) {
@@ -1258,6 +1261,22 @@ hipError_t lsort_launch(const SortInput &in, const SortJob *jobs, uint32_t njobs
                 R.smp_j = sjf->smp_j;
             } else {
                 a.srow[a.nsamp++] = a.nrows - 1;
+// 16-bit words of a row's ranks by block. The FIFO row's rk[1] holds its own
+// and those of a row sampled beside it.
+constexpr uint64_t rank_words(uint64_t S) { return S / (S <= kSBSmallMaxS ? kSBSmall : kSBLarge) * S; }
+static_assert(2 * rank_words(kSBSmallMaxS) * 2 <= (uint64_t)kSsMaxN * 8 &&
+                  2 * rank_words(kLsMaxS) * 2 <= (uint64_t)kSBSmallMaxS / kLsOver * kLsAvg * 8,
+              "the ranks fit the second region buffer");
+
+template <uint32_t kSB>
+void ls_draw(const LsArgs &a, const LsLayout &l, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_ls_gather<kSB>, dim3(l.S / kSB, a.nsamp), dim3(kSB), 0, s, a);
+    hipLaunchKernelGGL(k_ls_sample<kSB>, dim3((uint32_t)(l.S / kSB * cdiv(l.S, kSB * kSmE)), a.nsamp), dim3(kSB), 0,
+                       s, a);
+    hipLaunchKernelGGL(k_ls_place<kSB>, dim3(cdiv(l.S, 256), a.nsamp), dim3(256), 0, s, a);
+}
+
             }
             R.bid = reinterpret_cast<uint16_t *>(take(n * 2));
             for (int e = 0; e < 2; e++) {
@@ -1286,18 +1305,14 @@ hipError_t lsort_launch(const SortInput &in, const SortJob *jobs, uint32_t njobs
         R.hgt = l.hgt;
         R.srt_k = sjf->srt_k;
         R.srt_i = sjf->srt_i;
-        R.rpart = sjf->rpart;
+        R.rpart = a.r[0].rpart + rank_words(l.S);
         R.smp_k = sjf->smp_k;
         R.smp_j = sjf->smp_j;
         a.srow[a.nsamp++] = a.nrows;
     }
     const uint32_t maxb = a.nsort ? l.B : kQ;
-    if (a.nsamp) {
-        hipLaunchKernelGGL(k_ls_gather, dim3(l.S / kSB, a.nsamp), dim3(kSB), 0, s, a);
-        hipLaunchKernelGGL(k_ls_sample, dim3((uint32_t)(l.S / kSB * cdiv(l.S, kSB * kSmE)), a.nsamp), dim3(kSB), 0,
-                           s, a);
-        hipLaunchKernelGGL(k_ls_place, dim3(cdiv(l.S, 256), a.nsamp), dim3(256), 0, s, a);
-    }
+    if (a.nsamp && l.S <= kSBSmallMaxS) ls_draw<kSBSmall>(a, l, s);
+    else if (a.nsamp) ls_draw<kSBLarge>(a, l, s);
     if (l.B <= kSmallB) {
         hipLaunchKernelGGL(k_ls_count<kSmallB>, dim3(l.tiles, a.nrows), dim3(kTT), 0, s, a);
         hipLaunchKernelGGL(k_ls_scan<kSmallB>, dim3(cdiv(maxb, 64), a.nrows), dim3(kScT), 0, s, a);
@@ -1312,3 +1327,4 @@ hipError_t lsort_launch(const SortInput &in, const SortJob *jobs, uint32_t njobs
 }
 
 }  // namespace ds
+            R.rpart = reinterpret_cast<uint16_t *>(R.rk[1]);
