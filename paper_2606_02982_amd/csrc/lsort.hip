@@ -77,6 +77,7 @@ static_assert(kTile<kLsMaxB> <= (1u << kIBits) && kLsMaxB <= (1u << 12), "a plac
 constexpr int kBT = 512, kBW = kBT / 64, kBR = kLsCap / kBT;   // k_ls_bucket
 constexpr uint32_t kBinBits = 11, kBins = 1u << kBinBits;
 constexpr uint32_t kBinMax = 256;                  // larger bins: byte passes instead
+constexpr uint32_t kSeg = 8, kSegBins = kBins / kSeg;   // parts of a bucket between samples
 
 constexpr uint32_t kLsMaxRows = 4;                 // sorts and partitions of one batch
 constexpr uint32_t kQ = 16;                        // partition digits (tiers or classes)
@@ -97,8 +98,8 @@ struct LsRow {
     uint32_t by_req;       // the sample's keys are the budgets of the sampled requests
                            // (request index standing in for the FIFO position)
     uint64_t *srt_k;       // [S] the sample in sorted blocks of kSB: keys
-    uint32_t *srt_i;       // and sample indices
-    uint16_t *rpart;       // [S / kSB][S] each one's rank in each block
+    uint32_t *srt_i;       // and sample indices; from k_ls_scan on whether a bucket's samples repeat a key
+    uint16_t *rpart;       // [S / kSB][S] each one's rank in each block (in rk[1], which is not in use yet)
     uint64_t *smp_k;       // [S] the sample in order
     uint32_t *smp_j;
     uint64_t *rk[2];       // [n] bucket regions, and the large-bucket path's second buffer
@@ -263,8 +264,8 @@ __device__ __forceinline__ uint64_t shfl_xor_u64(uint64_t x, int m)
 // The sample in sorted blocks of kSB by (key, sample index): each wave's 64
 // with a bitonic network across the lanes, then pairs of sorted stretches
 // merged in LDS (each pair's place: its own and its rank in the other).
-__global__ __launch_bounds__(kSB) void k_ls_gather(LsArgs a)
 template <uint32_t kSB>
+__global__ __launch_bounds__(kSB) void k_ls_gather(LsArgs a)
 {
     __shared__ uint64_t mk[2][kSB];
     __shared__ uint16_t mi[2][kSB];
@@ -313,8 +314,8 @@ template <uint32_t kSB>
 // pair order by (key, position).
 constexpr uint32_t kSmE = 2;
 
-__global__ __launch_bounds__(kSB) void k_ls_sample(LsArgs a)
 template <uint32_t kSB>
+__global__ __launch_bounds__(kSB) void k_ls_sample(LsArgs a)
 {
     __shared__ uint64_t sk[kSB];
     __shared__ uint16_t si[kSB];
@@ -352,8 +353,8 @@ template <uint32_t kSB>
 }
 
 // Each sample at its rank (the sum of its ranks in the blocks).
-__global__ __launch_bounds__(256) void k_ls_place(LsArgs a)
 template <uint32_t kSB>
+__global__ __launch_bounds__(256) void k_ls_place(LsArgs a)
 {
     const LsRow &R = a.r[a.srow[blockIdx.y]];
     const uint32_t e = blockIdx.x * 256u + threadIdx.x, S = R.S;
@@ -480,6 +481,23 @@ __global__ __launch_bounds__(kTT) void k_ls_count(LsArgs a)
     for (uint32_t b = t; b < R.B; b += kTT) row[b] = h[b];
 }
 
+// The i-th of kSeg + 1 samples of a bucket: its pairs lie in [sample 0, sample
+// kSeg); the first and the last bucket are open on one side.
+__device__ __forceinline__ void ls_bucket_sample(const LsRow &R, uint32_t bkt, uint32_t i, uint64_t &k, uint32_t &j)
+{
+    const uint32_t s0 = ls_split_rank(R, bkt), s1 = ls_split_rank(R, bkt + 1u);
+    const uint32_t r = s0 + (s1 - s0) * i / kSeg;   // s1 - s0 < 2^15
+    k = ~0ull;
+    j = ~0u;
+    if (r == 0) {
+        k = 0;
+        j = 0;
+    } else if (r < R.S) {   // (the last bucket's end is at S)
+        k = R.smp_k[r];
+        j = R.smp_j[r];
+    }
+}
+
 // Block c: buckets 64 c .. 64 c + 63 over all tiles (at most kMT), staged in
 // LDS; wave w scans the columns w, w + 16, ... (kMT / 64 tiles per lane).
 constexpr int kScT = 1024, kScW = kScT / 64;
@@ -496,6 +514,21 @@ __global__ __launch_bounds__(kScT) void k_ls_scan(LsArgs a)
     const uint32_t t = threadIdx.x, lane = (uint32_t)lane_id(), w = t >> 6;
     const uint32_t b0 = blockIdx.x * 64u, T = a.tiles, B = R.B;
     if (b0 >= B) return;   // a row with fewer buckets than the grid is wide
+    if (!is_part(R.kind) && t < 64 && b0 + t < B) {
+        // neighbouring samples with one key, unless all have it (then the
+        // position alone orders the bucket)
+        uint64_t k0, p, k;
+        uint32_t j;
+        ls_bucket_sample(R, b0 + t, 0, k0, j);
+        p = k0;
+        bool rep = false;
+#pragma unroll
+        for (uint32_t i = 1; i <= kSeg; i++, p = k) {
+            ls_bucket_sample(R, b0 + t, i, k, j);
+            rep |= k == p;
+        }
+        R.srt_i[b0 + t] = rep && k != k0 ? 1u : 0u;
+    }
     constexpr int kPer = kMT<kMB> * 64 / kScT;   // loads per thread, in flight together
     {
         uint32_t x[kPer];
@@ -766,6 +799,8 @@ struct BkLs {
     uint32_t wsum[kBW];
     uint32_t wmax[kBW];
     uint64_t red[4][kBW];
+    uint64_t sk[kSeg + 1];        // the bucket's splitters and kSeg - 1 samples between them
+    uint32_t sj[kSeg + 1];
 };
 
 enum class Red { Min, Max, Or };
@@ -867,7 +902,7 @@ __device__ __forceinline__ void ls_byte_rank(BkLs &sh, const uint64_t *k, const 
 // A bucket of m > kLsCap pairs at [off, off + m): stable byte passes through
 // global memory (the varying bytes of j, then those of the key), chunk by
 // chunk of kLsCap pairs in order; then the values out.
-__device__ void ls_big_bucket(const LsArgs &a, const LsRow &R, BkLs &sh, uint32_t off, uint32_t m)
+__device__ __forceinline__ void ls_big_bucket(const LsArgs &a, const LsRow &R, BkLs &sh, uint32_t off, uint32_t m)
 {
     const uint32_t t = threadIdx.x;
     const int w = (int)(t >> 6), lane = lane_id();
@@ -883,7 +918,7 @@ __device__ void ls_big_bucket(const LsArgs &a, const LsRow &R, BkLs &sh, uint32_
     for (uint32_t i = t; i < kBW * 256u; i += kBT) (&sh.wc[0][0])[i] = 0;
     uint32_t src = 0;
     for (uint32_t pass = 0; pass < 11; pass++) {
-        const bool sel = pass < 3;   // three bytes of j (< 2^20), then eight of the key
+        const bool sel = pass < 3;   // three bytes of j (< 2^22), then eight of the key
         const uint32_t sh8 = 8u * (sel ? pass : pass - 3u);
         if ((((sel ? jor : kor) >> sh8) & 255u) == 0) continue;   // the same in every pair
         // digit counts over the bucket, then their exclusive starts
@@ -935,9 +970,49 @@ __device__ void ls_big_bucket(const LsArgs &a, const LsRow &R, BkLs &sh, uint32_
         ls_emit(a, R, off + i, R.rk[src][off + i], ls_pay_gather(a, R, R.rj[src][off + i]));
 }
 
-// A bucket of m <= kR kBT pairs at [off, off + m), sh.bin zero.
-template <int kR>
-__device__ void ls_bucket(const LsArgs &a, const LsRow &R, BkLs &sh, uint32_t bkt, uint32_t off, uint32_t m)
+// num / den of `bins` (den above num; nondecreasing in num).
+__device__ __forceinline__ uint32_t ls_share(float num, float den, uint32_t bins)
+{
+    const uint32_t x = (uint32_t)(num * ((float)bins / den));
+    return x < bins ? x : bins - 1u;
+}
+
+// The bin of a pair of a bucket whose samples repeat a key: kSegBins bins
+// between neighbouring samples (kA, jA) <= (kB, jB), by j where their keys
+// are equal, else by j for the pairs that share a key with either (a quarter
+// of the bins each) and by the key between. Nondecreasing in (k, j). The
+// bucket's j lie in [jmn, jmx].
+__device__ __forceinline__ uint32_t ls_seg_bin(const BkLs &sh, uint32_t jmn, uint32_t jmx, uint64_t k, uint32_t j)
+{
+    uint32_t s = 0;
+#pragma unroll
+    for (uint32_t i = 1; i < kSeg; i++) s += pair_less(k, j, sh.sk[i], sh.sj[i]) ? 0u : 1u;
+    const uint64_t kA = sh.sk[s], kB = sh.sk[s + 1];
+    const uint32_t jA = sh.sj[s], jB = sh.sj[s + 1];
+    constexpr uint32_t kQuarter = kSegBins / 4;
+    uint32_t x;
+    if (kA == kB) {
+        x = ls_share((float)(j - jA), (float)(jB - jA), kSegBins);
+    } else if (k == kA) {
+        const uint32_t lo = jA > jmn ? jA : jmn;
+        x = ls_share((float)(j - lo), (float)(jmx - lo) + 1.0f, kQuarter);
+    } else if (k == kB) {
+        const uint32_t hi = jB < jmx ? jB : jmx;
+        x = 3u * kQuarter + ls_share((float)(j - jmn), (float)(hi - jmn) + 1.0f, kQuarter);
+    } else {
+        x = kQuarter + ls_share((float)(k - kA), (float)(kB - kA), 2u * kQuarter);
+    }
+    return s * kSegBins + x;
+}
+
+// A bucket of m <= kR kBT pairs at [off, off + m), sh.bin zero. kTied: its
+// samples repeat a key, so that many pairs share one: bins between the samples,
+// by j inside such a key. 2,097,152 arrivals of 3,355 values: the bucket launch
+// 59 us, with byte passes for those buckets 102. (A form of its own: with both
+// in one the bucket launch of 4,194,303 random arrivals took 59.4 us for 56.6.)
+template <int kR, bool kTied>
+__device__ __forceinline__ void ls_bucket(const LsArgs &a, const LsRow &R, BkLs &sh, uint32_t bkt, uint32_t off,
+                                          uint32_t m)
 {
     const uint32_t t = threadIdx.x;
     const int w = (int)(t >> 6), lane = lane_id();
@@ -957,9 +1032,38 @@ __device__ void ls_bucket(const LsArgs &a, const LsRow &R, BkLs &sh, uint32_t bk
     // bucket, or the pairs' own range for the first and the last bucket and
     // where the first choice crowds a bin (no reduction otherwise)
     bool own = bkt == 0 || bkt + 1u == R.B;
+    bool seg = kTied;
+    if (seg && t <= kSeg) ls_bucket_sample(R, bkt, t, sh.sk[t], sh.sj[t]);   // (a barrier below)
     while (m > 1) {
         uint64_t kmn, kmx, jmn, jmx;
-        if (own) {
+        if (seg) {
+            uint32_t lo = ~0u, hi = 0;
+#pragma unroll
+            for (int r = 0; r < kR; r++) {
+                const uint32_t idx = (uint32_t)w * wk + (uint32_t)r * 64u + (uint32_t)lane;
+                if ((uint32_t)r < reff && idx < m) {
+                    lo = j[r] < lo ? j[r] : lo;
+                    hi = j[r] > hi ? j[r] : hi;
+                }
+            }
+#pragma unroll
+            for (int sft = 32; sft >= 1; sft >>= 1) {
+                const uint32_t l = (uint32_t)__shfl_xor((int)lo, sft, 64), h = (uint32_t)__shfl_xor((int)hi, sft, 64);
+                lo = l < lo ? l : lo;
+                hi = h > hi ? h : hi;
+            }
+            if (lane == 0) sh.red[0][w] = ((uint64_t)hi << 32) | lo;
+            __syncthreads();
+#pragma unroll
+            for (int q = 0; q < kBW; q++) {
+                const uint64_t x = sh.red[0][q];
+                lo = (uint32_t)x < lo ? (uint32_t)x : lo;
+                hi = (uint32_t)(x >> 32) > hi ? (uint32_t)(x >> 32) : hi;
+            }
+            kmn = kmx = 0;
+            jmn = lo;
+            jmx = hi;
+        } else if (own) {
             kmn = jmn = ~0ull;
             kmx = jmx = 0;
 #pragma unroll
@@ -993,7 +1097,8 @@ __device__ void ls_bucket(const LsArgs &a, const LsRow &R, BkLs &sh, uint32_t bk
             db[r] = 0;
             if ((uint32_t)r < reff && idx < m) {
                 const uint64_t p = byj ? (uint64_t)j[r] : k[r];
-                const uint32_t q = (uint32_t)((p - pmn) >> shift) & (kBins - 1u);
+                const uint32_t q = seg ? ls_seg_bin(sh, (uint32_t)jmn, (uint32_t)jmx, k[r], j[r])
+                                       : (uint32_t)((p - pmn) >> shift) & (kBins - 1u);
                 db[r] = q | (atomicAdd(&sh.bin[q], 1u) << kBinBits);
             }
         }
@@ -1026,8 +1131,9 @@ __device__ void ls_bucket(const LsArgs &a, const LsRow &R, BkLs &sh, uint32_t bk
             for (int q = 0; q < kBW; q++) maxbin = sh.wmax[q] > maxbin ? sh.wmax[q] : maxbin;
             __syncthreads();
         }
-        if (maxbin > kBinMax && !own) {   // try the pairs' own range
+        if (maxbin > kBinMax && (seg || !own)) {   // try the pairs' own range
             own = true;
+            seg = false;
             for (uint32_t i = t; i < kBins; i += kBT) sh.bin[i] = 0;
             __syncthreads();
             continue;
@@ -1129,6 +1235,7 @@ __global__ __launch_bounds__(kBT, 4) void k_ls_bucket(LsArgs a)
     const uint32_t t = threadIdx.x, bkt = blockIdx.x;
     if (bkt >= R.B) return;   // a row with fewer buckets than the grid is wide
     const uint32_t m = R.size[bkt], off = R.start[bkt];
+    const bool tied = R.srt_i[bkt] != 0;   // (from k_ls_scan)
     for (uint32_t i = t; i <= kBins; i += kBT) sh.bin[i] = 0;
     for (uint32_t i = t; i < kBW * 256u; i += kBT) (&sh.wc[0][0])[i] = 0;
     __syncthreads();
@@ -1137,8 +1244,9 @@ __global__ __launch_bounds__(kBT, 4) void k_ls_bucket(LsArgs a)
         return;
     }
     // (the common sizes with half the registers: no spills at 128)
-    if (m <= 4u * kBT) ls_bucket<4>(a, R, sh, bkt, off, m);
-    else ls_bucket<kBR>(a, R, sh, bkt, off, m);
+    if (m > 4u * kBT) ls_bucket<kBR, false>(a, R, sh, bkt, off, m);
+    else if (tied) ls_bucket<4, true>(a, R, sh, bkt, off, m);
+    else ls_bucket<4, false>(a, R, sh, bkt, off, m);
 }
 
 struct LsLayout {
@@ -1155,6 +1263,22 @@ LsLayout ls_layout(uint64_t n)
     l.S = (uint32_t)align_up((uint64_t)kLsOver * l.B, kSBLarge);   // <= kLsMaxS; S <= n
     l.tiles = (uint32_t)cdiv(n, l.B <= kSmallB ? kTile<kSmallB> : kTile<kLsMaxB>);
     return l;
+}
+
+// 16-bit words of a row's ranks by block. The FIFO row's rk[1] holds its own
+// and those of a row sampled beside it.
+constexpr uint64_t rank_words(uint64_t S) { return S / (S <= kSBSmallMaxS ? kSBSmall : kSBLarge) * S; }
+static_assert(2 * rank_words(kSBSmallMaxS) * 2 <= (uint64_t)kSsMaxN * 8 &&
+                  2 * rank_words(kLsMaxS) * 2 <= (uint64_t)kSBSmallMaxS / kLsOver * kLsAvg * 8,
+              "the ranks fit the second region buffer");
+
+template <uint32_t kSB>
+void ls_draw(const LsArgs &a, const LsLayout &l, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_ls_gather<kSB>, dim3(l.S / kSB, a.nsamp), dim3(kSB), 0, s, a);
+    hipLaunchKernelGGL(k_ls_sample<kSB>, dim3((uint32_t)(l.S / kSB * cdiv(l.S, kSB * kSmE)), a.nsamp), dim3(kSB), 0,
+                       s, a);
+    hipLaunchKernelGGL(k_ls_place<kSB>, dim3(cdiv(l.S, 256), a.nsamp), dim3(256), 0, s, a);
 }
 
 }  // namespace
@@ -1261,28 +1385,13 @@ hipError_t lsort_launch(const SortInput &in, const SortJob *jobs, uint32_t njobs
                 R.smp_j = sjf->smp_j;
             } else {
                 a.srow[a.nsamp++] = a.nrows - 1;
-// 16-bit words of a row's ranks by block. The FIFO row's rk[1] holds its own
-// and those of a row sampled beside it.
-constexpr uint64_t rank_words(uint64_t S) { return S / (S <= kSBSmallMaxS ? kSBSmall : kSBLarge) * S; }
-static_assert(2 * rank_words(kSBSmallMaxS) * 2 <= (uint64_t)kSsMaxN * 8 &&
-                  2 * rank_words(kLsMaxS) * 2 <= (uint64_t)kSBSmallMaxS / kLsOver * kLsAvg * 8,
-              "the ranks fit the second region buffer");
-
-template <uint32_t kSB>
-void ls_draw(const LsArgs &a, const LsLayout &l, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_ls_gather<kSB>, dim3(l.S / kSB, a.nsamp), dim3(kSB), 0, s, a);
-    hipLaunchKernelGGL(k_ls_sample<kSB>, dim3((uint32_t)(l.S / kSB * cdiv(l.S, kSB * kSmE)), a.nsamp), dim3(kSB), 0,
-                       s, a);
-    hipLaunchKernelGGL(k_ls_place<kSB>, dim3(cdiv(l.S, 256), a.nsamp), dim3(256), 0, s, a);
-}
-
             }
             R.bid = reinterpret_cast<uint16_t *>(take(n * 2));
             for (int e = 0; e < 2; e++) {
                 R.rk[e] = reinterpret_cast<uint64_t *>(take(n * 8));
                 R.rj[e] = reinterpret_cast<uint32_t *>(take(n * 4));
             }
+            R.rpart = reinterpret_cast<uint16_t *>(R.rk[1]);
             if (k != SortKind::Fifo) R.rv = reinterpret_cast<uint32_t *>(take(n * 4));
             if (k == SortKind::Fifo && fifo_out_copies) {
                 R.rt = reinterpret_cast<uint8_t *>(take(n));
@@ -1327,4 +1436,3 @@ void ls_draw(const LsArgs &a, const LsLayout &l, hipStream_t s)
 }
 
 }  // namespace ds
-            R.rpart = reinterpret_cast<uint16_t *>(R.rk[1]);

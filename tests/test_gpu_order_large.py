@@ -53,6 +53,15 @@ def _layout(pattern, n, rng):
     elif pattern == "skewed":
         arr = np.where(rng.random(n) < 0.99, 5.0, rng.uniform(-1e6, 1e6, n) * 10.0 ** rng.integers(-30, 30, n))
         bud = np.where(rng.random(n) < 0.99, 100.0, rng.standard_cauchy(n))
+    elif pattern in ("repeated", "repeated_in_order"):
+        # keys of 100 to 2,000 requests each, so that a bucket holds a few
+        # whole keys and parts of two; zeros of both signs among them
+        arr = np.floor(rng.normal(0.0, n / 1500.0, n)) / 4.0
+        arr[rng.random(n) < 0.01] = -0.0
+        bud = np.round(rng.uniform(1, n / 300.0, n)) * 0.5
+        if pattern == "repeated_in_order":
+            arr.sort()
+            bud.sort()
     elif pattern == "clusters":
         arr = rng.choice([0.0, 50.0], n) + rng.uniform(0.0, 1e-9, n)
         bud = rng.choice([100.0, 100.5, 5000.0], n) + np.where(rng.random(n) < 0.5, 0.0,
@@ -61,7 +70,7 @@ def _layout(pattern, n, rng):
 
 
 @pytest.mark.parametrize("pol", POLICIES)
-@pytest.mark.parametrize("pattern", ["ties", "constant", "in_order", "descending", "skewed", "clusters"])
+@pytest.mark.parametrize("pattern", ["ties", "constant", "in_order", "descending", "skewed", "clusters", "repeated", "repeated_in_order"])
 def test_layouts(ds, oracle, pol, pattern):
     n = 400003
     rng = np.random.default_rng(n + len(pattern))
@@ -142,7 +151,7 @@ def test_sizes_above_2_20(ds, oracle, n, pols):
 
 
 @pytest.mark.parametrize("pol", POLICIES)
-@pytest.mark.parametrize("pattern", ["ties", "constant", "skewed", "clusters"])
+@pytest.mark.parametrize("pattern", ["ties", "constant", "skewed", "clusters", "repeated", "repeated_in_order"])
 def test_layouts_above_2_20(ds, oracle, pol, pattern):
     n = 1100003
     rng = np.random.default_rng(n + len(pattern))
