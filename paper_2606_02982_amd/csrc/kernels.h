@@ -174,12 +174,12 @@ inline uint32_t *am_steps_pos(uint64_t *hk, uint64_t n) { return reinterpret_cas
 size_t am_ws_bytes(uint64_t n);
 hipError_t am_launch(const SortInput &in, uint32_t n_classes, uint32_t *perm, double *key_out, void *ws,
                      hipStream_t s, uint32_t *wait_status);
-// The stable partition of the FIFO sequence by in.cls[tier] alone (16
-// classes): run_pos (n) receives the FIFO positions class by class, each
-// class in FIFO order, run_start (17) each class's first entry and n.
 // The places alone, over runs formed elsewhere (runs.cstart[K..16] = n).
 hipError_t am_rank_launch(const SortInput &in, uint32_t n_classes, const LsRuns &runs, uint32_t *perm,
                           double *key_out, void *scratch, hipStream_t s);
+// The stable partition of the FIFO sequence by in.cls[tier] alone (16
+// classes): run_pos (n) receives the FIFO positions class by class, each
+// class in FIFO order, run_start (17) each class's first entry and n.
 size_t am_partition_ws_bytes(uint64_t n);
 hipError_t am_partition(const SortInput &in, uint32_t *run_pos, uint32_t *run_start, void *ws, hipStream_t s);
 

@@ -1,8 +1,8 @@
 // Dispatch orders of kSsMaxN < n <= kLsMaxN (2^22) requests (Sec. "Scheduling
 // Engine"): one sample sort per policy over a sequence of positions j, by
 // the pair (key(j), j), which is the stable order by key. FIFO sorts the
-// requests by arrival; SJF (and Aging) sort the FIFO sequence by budget (or
-// aged score), so that ties keep FIFO order. Keys and values are those of
+// requests by arrival; SJF sorts the FIFO sequence by budget, so
+// that ties keep FIFO order (Aging follows from the classes' runs, agmerge.hip). Keys and values are those of
 // produce() (keys.h).
 //
 //   k_ls_gather   the keys of S = 8 per bucket positions, one in each of S
@@ -82,7 +82,7 @@ constexpr uint32_t kSeg = 8, kSegBins = kBins / kSeg;   // parts of a bucket bet
 constexpr uint32_t kLsMaxRows = 4;                 // sorts and partitions of one batch
 constexpr uint32_t kQ = 16;                        // partition digits (tiers or classes)
 
-// One row of a batch: a sort (Fifo, Budget, Aging: buckets by sampled
+// One row of a batch: a sort (Fifo, Budget: buckets by sampled
 // splitters) or a partition (Class, Tier: the stable partition of the
 // sequence by a digit below kQ, placed straight at the policy's positions).
 struct LsRow {
@@ -159,7 +159,6 @@ __device__ __forceinline__ uint64_t ls_key(const LsArgs &a, const LsRow &R, uint
         const uint32_t q0 = a.pf.tier[j], q = q0 < kQ ? q0 : kQ - 1u;
         switch (R.kind) {
         case SortKind::Budget: return ordered_bits(a.pf.bud[j]);
-        case SortKind::Aging: return ordered_bits(ls_aged(a.in, a.pf.arr[j], q));
         case SortKind::Class: return a.in.cls[q];
         default: return q;   // Tier
         }
@@ -179,7 +178,6 @@ __device__ __forceinline__ void ls_key_out(const LsArgs &a, const LsRow &R, uint
     switch (R.kind) {
     case SortKind::Fifo: R.key_out[i] = a.in.arrival[i]; break;
     case SortKind::Budget: R.key_out[i] = a.in.budget[i]; break;
-    case SortKind::Aging: R.key_out[i] = ls_aged(a.in, a.in.arrival[i], q); break;
     case SortKind::Class: R.key_out[i] = a.in.prio[q]; break;
     default: break;
     }
@@ -1353,7 +1351,7 @@ hipError_t lsort_launch(const SortInput &in, const SortJob *jobs, uint32_t njobs
             if (part != (pass == 1)) continue;
             if (!jobs[i].out && !(k == SortKind::Class && aging_runs)) return hipErrorInvalidValue;
             if (k != SortKind::Fifo && !in.fifo) return hipErrorInvalidValue;
-            if (k != SortKind::Fifo && k != SortKind::Budget && k != SortKind::Aging && !part)
+            if (k != SortKind::Fifo && k != SortKind::Budget && !part)
                 return hipErrorInvalidValue;
             LsRow &R = a.r[a.nrows++];
             R.kind = k;

@@ -1534,6 +1534,9 @@ __device__ __forceinline__ Resume engine_class(const EngineArgs &a, const ClassS
 // of which the pool's upkeep was 26%, the touched classes' keys 16% and the
 // windows 22%; 13.7 ms here (keys 12%, gathering and ranking 26%, windows
 // 27%, candidates 17%, factors 13%). With 4,096 classes 25.8 ms and 24.5 ms.
+// Both limits come from the LDS (147 KB with four classes per thread). What is
+// gained falls with the classes, whose constants are read again from global memory
+// above 1024, to 1.05x at 4096; one more of either and the pool engine runs.
 constexpr uint32_t kDirC = 4096;         // classes
 constexpr uint32_t kDirN = 1u << 18;     // requests (the bitmap's words in LDS)
 constexpr uint32_t kDirCand = 128;       // gathered classes: two per lane
@@ -1560,7 +1563,7 @@ struct DirectLds {
     uint32_t pick[kClsMaxBatch];         // window candidate of each dispatch place
     double t2[kClsMaxBatch];             // alpha x its Eq. (6) ratio
     uint64_t tk;                         // a lower tau, and its FIFO position
-    uint32_t tj, lower;
+    uint32_t tj;
     uint32_t aw[2][kNW];                 // arrivals per wave
     uint32_t gathered[2], cand[2];       // counters, by the parity of the tick
     uint32_t fail, sw[kNW], hist[256], bin[3];
@@ -1653,7 +1656,6 @@ __device__ __forceinline__ Resume engine_direct(const EngineArgs &a, const Class
     }
     if (tid == 0) {
         S.fail = 0;
-        S.lower = 0;
     }
     bool ok = true;
 #pragma unroll
