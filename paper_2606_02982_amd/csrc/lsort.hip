@@ -1,9 +1,9 @@
 // Dispatch orders of kSsMaxN < n <= kLsMaxN (2^22) requests (Sec. "Scheduling
 // Engine"): one sample sort per policy over a sequence of positions j, by
 // the pair (key(j), j), which is the stable order by key. FIFO sorts the
-// requests by arrival; SJF sorts the FIFO sequence by budget, so
-// that ties keep FIFO order (Aging follows from the classes' runs, agmerge.hip). Keys and values are those of
-// produce() (keys.h).
+// requests by arrival; SJF sorts the FIFO sequence by budget, so that ties keep
+// FIFO order (Aging follows from the classes' runs, agmerge.hip). Keys and values
+// are those of produce() (keys.h).
 //
 //   k_ls_gather   the keys of S = 8 per bucket positions, one in each of S
 //                 equal strata of [0, n) (so the sample is in sequence order),
@@ -44,7 +44,6 @@
 
 #include "common.h"
 #include "kernels.h"
-#include "keys.h"
 #include "lookback.h"
 #include "wrrplan.h"
 
@@ -141,7 +140,7 @@ __device__ __forceinline__ uint32_t ls_pos(uint32_t s, uint32_t n, uint32_t S)
 }
 
 // The aged score of a request with arrival x and tier q, each operation
-// rounded separately (no fused multiply-add), as in produce().
+// rounded separately (no fused multiply-add), as in produce() (keys.h).
 __device__ __forceinline__ double ls_aged(const SortInput &in, double x, uint32_t q)
 {
     double w = in.t_now - x;
@@ -152,43 +151,43 @@ __device__ __forceinline__ double ls_aged(const SortInput &in, double x, uint32_
     return e;
 }
 
-// The key of position j of the row's sequence (the digit, for a partition).
+// The request at position j of the sequence, and the value it contributes to
+// the output.
+__device__ __forceinline__ uint32_t ls_value(const LsArgs &a, const LsRow &R, uint32_t j)
+{
+    if (R.kind == SortKind::Fifo) return j;
+    const uint32_t i = a.in.fifo[j];
+    return i < a.n ? i : 0u;
+}
+
+// The key of position j of a sort's sequence.
 __device__ __forceinline__ uint64_t ls_key(const LsArgs &a, const LsRow &R, uint32_t j)
 {
-    if (R.kind != SortKind::Fifo && a.pf.tier) {
-        const uint32_t q0 = a.pf.tier[j], q = q0 < kQ ? q0 : kQ - 1u;
-        switch (R.kind) {
-        case SortKind::Budget: return ordered_bits(a.pf.bud[j]);
-        case SortKind::Class: return a.in.cls[q];
-        default: return q;   // Tier
-        }
-    }
-    uint64_t k;
-    uint32_t v;
-    produce(a.in, R.kind, nullptr, a.n, j, k, v);
-    return k;
+    if (R.kind == SortKind::Fifo) return ordered_bits(a.in.arrival[j]);
+    return ordered_bits(a.pf.tier ? a.pf.bud[j] : a.in.budget[ls_value(a, R, j)]);
+}
+
+// The digit of position j of a partition's sequence, below kQ. (Kept apart
+// from the keys, and a selection: as a switch over the kinds of both, in the
+// 4096-bucket scatter the compiler left the Tier row's digit unset for some of
+// a thread's positions.)
+__device__ __forceinline__ uint32_t ls_digit(const LsArgs &a, const LsRow &R, uint32_t j)
+{
+    const uint32_t q0 = a.pf.tier ? a.pf.tier[j] : a.in.tier[ls_value(a, R, j)], q = q0 < kQ ? q0 : kQ - 1u;
+    const uint32_t c = a.in.cls[q];
+    return R.kind == SortKind::Class ? c : q;
 }
 
 // The per-request key output of request i (Weighted's round is written
 // where the request is placed).
 __device__ __forceinline__ void ls_key_out(const LsArgs &a, const LsRow &R, uint32_t i)
 {
-    const uint32_t q0 = R.kind == SortKind::Fifo || R.kind == SortKind::Budget ? 0u : a.in.tier[i];
-    const uint32_t q = q0 < kQ ? q0 : kQ - 1u;
-    switch (R.kind) {
-    case SortKind::Fifo: R.key_out[i] = a.in.arrival[i]; break;
-    case SortKind::Budget: R.key_out[i] = a.in.budget[i]; break;
-    case SortKind::Class: R.key_out[i] = a.in.prio[q]; break;
-    default: break;
+    if (R.kind == SortKind::Class) {
+        const uint32_t q = a.in.tier[i];
+        R.key_out[i] = a.in.prio[q < kQ ? q : kQ - 1u];
+    } else {
+        R.key_out[i] = R.kind == SortKind::Fifo ? a.in.arrival[i] : a.in.budget[i];
     }
-}
-
-// The value position j contributes to the output.
-__device__ __forceinline__ uint32_t ls_value(const LsArgs &a, const LsRow &R, uint32_t j)
-{
-    if (R.kind == SortKind::Fifo) return j;
-    const uint32_t i = a.in.fifo[j];
-    return i < a.n ? i : 0u;
 }
 
 // A region entry's payload: its value, and for the FIFO sort's copies the
@@ -401,7 +400,7 @@ __device__ __forceinline__ void ls_count_part(const LsArgs &a, const LsRow &R, u
 #pragma unroll
     for (int r = 0; r < kR; r++) {
         const uint32_t idx = (uint32_t)r * kTT + t;
-        d[r] = idx < cnt ? (uint32_t)ls_key(a, R, base + idx) : kQ;   // kQ: no position
+        d[r] = idx < cnt ? ls_digit(a, R, base + idx) : kQ;   // kQ: no position
     }
     if (R.key_out && R.kind == SortKind::Class) {
 #pragma unroll
@@ -603,7 +602,7 @@ __device__ __forceinline__ void ls_place_part(const LsArgs &a, const LsRow &R, u
     for (int r = 0; r < kR; r++) {
         const uint32_t idx = (uint32_t)w * kWK + (uint32_t)r * 64u + (uint32_t)lane;
         const uint32_t j = base + (idx < cnt ? idx : 0u);
-        d[r] = (uint32_t)ls_key(a, R, j);   // < kQ
+        d[r] = ls_digit(a, R, j);
         v[r] = ls_value(a, R, j);
     }
     if (t < (kTT / 64) * kQ) (&wc[0][0])[t] = 0;
