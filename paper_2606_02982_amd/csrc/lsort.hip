@@ -174,8 +174,8 @@ __device__ __forceinline__ uint64_t ls_key(const LsArgs &a, const LsRow &R, uint
 __device__ __forceinline__ uint32_t ls_digit(const LsArgs &a, const LsRow &R, uint32_t j)
 {
     const uint32_t q0 = a.pf.tier ? a.pf.tier[j] : a.in.tier[ls_value(a, R, j)], q = q0 < kQ ? q0 : kQ - 1u;
-    const uint32_t c = a.in.cls[q];
-    return R.kind == SortKind::Class ? c : q;
+    if (R.kind == SortKind::Class) return a.in.cls[q];
+    return q;
 }
 
 // The per-request key output of request i (Weighted's round is written
