@@ -476,14 +476,17 @@ uint32_t blocks_for(uint64_t n, uint32_t cap)
 }  // namespace
 
 // Blocks of the error kernel: about 2048 events each, at most kMaxBlocks,
-// and fewer when the partial sums of many groups would be large.
+// and fewer when the partial sums of many groups would be large; at most 2^31
+// events each.
 static uint32_t err_blocks(uint64_t n, uint32_t G)
 {
     uint64_t b = cdiv(n ? n : 1, 2048);
     const uint64_t cap = (1ull << 22) / ((uint64_t)G + 1);   // <= 128 MB of partials
     if (b > kMaxBlocks) b = kMaxBlocks;
     if (b > cap) b = cap;
-    return (uint32_t)(b < 1 ? 1 : b);
+    // (a block counts a group's events in 32 bits)
+    const uint64_t least = cdiv(n ? n : 1, 1ull << 31);
+    return (uint32_t)(b < least ? least : b);
 }
 
 size_t err_ws_bytes(uint64_t n, uint32_t n_groups)

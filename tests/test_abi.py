@@ -305,3 +305,11 @@ def test_workspace_sizes_do_not_fall(ds):
     for n in edges:
         sizes = [ds.workspace_bytes(ds.OP_CALIBRATE, n, G) for G in groups]
         assert sizes == sorted(sizes), (n, sizes)
+
+
+@pytest.mark.parametrize("n,G", [(7 << 31, 1 << 20), ((7 << 31) + 1, 1 << 20), (1 << 33, 1 << 20), (1 << 22, 1 << 20)])
+def test_error_stats_blocks_count_in_32_bits(ds, n, G):
+    # a block counts a group's events in 32 bits: at most 2^31 events per block,
+    # each with four partial sums of 8 bytes per group and overall
+    blocks = ds.workspace_bytes(ds.OP_ERROR_STATS, n, G) // (4 * (G + 1) * 8)
+    assert blocks * (1 << 31) >= n

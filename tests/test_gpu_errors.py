@@ -58,7 +58,7 @@ def test_empty_and_skipped(ds):
 
 @pytest.mark.parametrize("n,G", [(1, 1), (1000, 3), (70000, 1023), (70000, 1024), (300000, 5000)])
 def test_random(ds, oracle, n, G):
-    # 1023 groups (+ the "all" row) fit the per-block LDS sums; 1024 do not
+    # 4096 groups per pass over a block's events
     rng = np.random.default_rng(n + G)
     est = rng.uniform(0.5, 4000, n)
     est[rng.random(n) < 0.02] = 0.0
