@@ -326,9 +326,10 @@ __device__ __forceinline__ void process_set(WaveState &st, const RangeCtx &rc, c
     if (bnd)
         for_boundaries(st, rc, pos + kSet, lane, [&](uint64_t m) {
             const uint32_t wrel = st.win - pos;
-            // empty prompts start where the next one does: each place once
-            // (65,536 empty prompts in a row: 4.6 ms offset by offset, 0.67 so)
-            if (__popcll(m) > 8) m &= __ballot(wave_shr1(st.win, kFar) != st.win);
+            // empty prompts start where the next one does: in a window full of
+            // starts each place once (65,536 empty prompts in a row: 4.6 ms
+            // offset by offset, 0.67 so)
+            if (m == ~0ull) m = __ballot(wave_shr1(st.win, kFar) != st.win);
             for (; m; m &= m - 1) {
                 const uint32_t rel = readlane32(wrel, __builtin_ctzll(m));
                 const uint32_t bit = 1u << (8u * (rel & 3u) + 4u * ((rel >> 10) & 1u) + ((rel >> 2) & 3u));
