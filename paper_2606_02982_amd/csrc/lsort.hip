@@ -34,10 +34,10 @@
 //                 places in the output.
 // What bounds it: latency inside the blocks and, above 2^20, the scatter's short
 // runs (two pairs per tile and bucket). Five orders, before and after the
-// 1024-thread tiles, the sorted sample blocks and the bins between splitters:
-// 1,048,576 requests 214 and 188 us; 4,194,303 (radix sorts before) 1,077 and
-// 583 us, of which at 4,194,303 two count launches 85, two scatters 213, two
-// bucket launches 174, the Aging places 61.
+// 1024-thread tiles, the sorted sample blocks and the bins between splitters or
+// samples: 1,048,576 requests 214 and 181 us; 4,194,303 (radix sorts before)
+// 1,077 and 560 us, of which at 4,194,303 two count launches 81, two scatters
+// 199, two bucket launches 161, the Aging places 58.
 // No atomics on global memory and no wait on another block; the bucket
 // sizes are exact, so nothing overflows.
 #include <string.h>
