@@ -203,3 +203,24 @@ def test_aging_class_mixes(ds, oracle, shares, rate, floor):
     want = oracle.order(ds.AGING, tier, arr, **{a: b for a, b in kw.items() if a != "n_tiers"})[0]
     got = ds.order(ds.AGING, dev(tier), dev(arr), fifo=fifo, **kw)[0]
     assert np.array_equal(got.cpu().numpy().view(np.uint32), want)
+
+
+@pytest.mark.parametrize("n", [300001, 1048577])
+@pytest.mark.parametrize("tiers", [3, 16])
+def test_partitions_over_a_given_order(ds, oracle, n, tiers):
+    # the digits and budgets are gathered through the given order, not read from
+    # copies in FIFO order; both tile sizes, the last tier and shared classes
+    rng = np.random.default_rng(n + tiers)
+    tier = rng.integers(0, tiers, n).astype(np.uint8)
+    arr = rng.uniform(0.0, 100.0, n)
+    bud = np.round(rng.uniform(1, 3000, n), 1)
+    kw = dict(weights=tuple(1 + q % 4 for q in range(tiers)), tier_priority=tuple(float(q % 5) for q in range(tiers)),
+              aging_rate=0.1, t_now=100.0)
+    fifo = dev(np.lexsort((np.arange(n), arr)).astype(np.uint32))
+    pols = (ds.PRIORITY, ds.WEIGHTED, ds.SJF, ds.AGING)
+    got, _ = ds.order_multi(pols, dev(tier), dev(arr), dev(bud), fifo=fifo, n_tiers=tiers, **kw)
+    for pol in pols:
+        want = oracle.order(pol, tier, arr, bud, **kw)[0].astype(np.int32)
+        assert np.array_equal(got[pol].cpu().numpy(), want), pol
+        one = ds.order(pol, dev(tier), dev(arr), dev(bud), fifo=fifo, n_tiers=tiers, **kw)[0]
+        assert np.array_equal(one.cpu().numpy(), want), pol
